@@ -49,28 +49,31 @@ __global__ void k_scale_beta(int64_t, const int32_t *, const double2 *, int, con
 __global__ void k_diag_bm_inv(int64_t, const int32_t *, const int32_t *, const int32_t *, const double2 *,
                               const double2 *, const double2 *, const double2 *, const double2 *, double, double2,
                               double, double2 *);
-__global__ void k_p2p_n(int, const int32_t *, const int32_t *, const int32_t *, int, const double4 *, const double4 *,
-                        const double2 *, const double2 *, double, double, const int32_t *, const int32_t *,
-                        const double2 *, const double2 *, const double2 *, const double2 *, double2 *, double2 *);
 __global__ void k_local_derivs(int64_t, int, const double2 *, double, double2 *, double2 *, double2 *);
 __global__ void k_l2p_n(int, int, const int32_t *, const double4 *, const double4 *, const double4 *, const double2 *,
                         const double2 *, const double2 *, const double2 *, double, const double *, const double2 *,
-                        const double2 *, const int32_t *, int64_t, const double2 *, const double2 *, const double2 *,
+                        const double2 *, int, const int32_t *, int64_t, const double2 *, const double2 *, const double2 *,
                         double2 *, int);
 __global__ void k_diag2_inv(int64_t, const int32_t *, const int32_t *, const double2 *, const double2 *,
                             const double2 *, const double2 *, double, double, double2 *);
 __global__ void k_mul_diag2(int64_t, const int32_t *, const double2 *, const double2 *, double2 *);
-void launch_p2p(int nr, bool fp32, int nleaf, const int32_t *leaf_start, const int32_t *nbr_start,
+int p2p_splits_of(int nleaf);
+void launch_p2p(int nr, bool fp32, int nleaf, int nsplit, const int32_t *leaf_start, const int32_t *nbr_start,
                 const int32_t *nbr_list, int all_leaves, const double4 *ec, const double4 *en, const double2 *sigma,
                 const double2 *mu, double k, double rc2, const int32_t *near_start, const int32_t *near_col,
                 const void *nL, const void *nM, double2 *y, hipStream_t st);
+void launch_p2p_n(int nleaf, int nsplit, const int32_t *leaf_start, const int32_t *nbr_start, const int32_t *nbr_list,
+                  int all_leaves, const double4 *ec, const double4 *en, const double2 *sigma, const double2 *mu,
+                  double k, double rc2, const int32_t *near_start, const int32_t *near_col, const double2 *nL,
+                  const double2 *nM, const double2 *nLp, const double2 *nMp, double2 *y, double2 *yn, hipStream_t st);
 bool p2m_fits(int nr, int p);
 void launch_p2m(int nr, int nleaf, int p, const int32_t *leaf_start, const double4 *center, const double4 *ec,
                 const double4 *en, const double2 *sigma, const double2 *mu, double k, const double *leg,
                 double2 *Mout, hipStream_t st);
 void launch_l2p(int nr, int nleaf, int p, const int32_t *leaf_start, const double4 *center, const double4 *ec,
-                const double2 *Lc, double k, const double *leg, const double2 *ynear, double half,
-                const int32_t *perm, int64_t n, const double2 *x, double2 *y, int has_far, hipStream_t st);
+                const double2 *Lc, double k, const double *leg, const double2 *ynear, int nsplit,
+                double half, const int32_t *perm, int64_t n, const double2 *x, double2 *y, int has_far,
+                hipStream_t st);
 __global__ void k_cvt_d2f(int64_t, const double2 *, float2 *);
 __global__ void k_cvt_f2d(int64_t, const float2 *, double2 *);
 __global__ void k_cvt_real_d2f(int64_t, const double *, float *);
@@ -1073,7 +1076,8 @@ static void fmm_pass(fmmbem_ctx *c, int nr, const double2 *sigma, const double2 
     const int nleaf = (int)T.leaf_start.size() - 1;
     auto I32 = [&](const char *s) { return (int32_t *)c->buf.find(s); };
     const double4 *ec = (double4 *)c->buf.find("ec"), *en = (double4 *)c->buf.find("en");
-    double2 *ynear = dget<double2>(c->scratch, "ynear", (size_t)n * nr);
+    const int nsplit = mixed ? 1 : p2p_splits_of(nleaf);
+    double2 *ynear = dget<double2>(c->scratch, "ynear", (size_t)n * nr * nsplit);
     ensure_nr(c, nr, mixed);
     struct CurGuard {
         fmmbem_ctx *c;
@@ -1082,7 +1086,7 @@ static void fmm_pass(fmmbem_ctx *c, int nr, const double2 *sigma, const double2 
     auto near_field = [&]() {
         int pe = prof_begin(c);
         const double pairs = exact_far ? (double)n * n : (double)c->p2p_pairs;
-        launch_p2p(nr, mixed, nleaf, I32("leaf_start"), I32("nbr_start"), I32("nbr_list"), exact_far ? 1 : 0, ec, en,
+        launch_p2p(nr, mixed, nleaf, nsplit, I32("leaf_start"), I32("nbr_start"), I32("nbr_list"), exact_far ? 1 : 0, ec, en,
                    sigma, mu, c->k, c->rc * c->rc, I32("near_start"), I32("near_col"),
                    c->buf.find(mixed ? "near_L32" : "near_L"), c->buf.find(mixed ? "near_M32" : "near_M"), ynear,
                    c->cur);
@@ -1129,8 +1133,8 @@ static void fmm_pass(fmmbem_ctx *c, int nr, const double2 *sigma, const double2 
     rec(c, 6);
     LevelDev &LL = c->lev[L];
     pe = prof_begin(c);
-    launch_l2p(nr, nleaf, LL.p, I32("leaf_start"), LL.center, ec, LL.L, c->k, leg_table(c), ynear, half,
-               I32("perm"), n, x, y, exact_far ? 0 : 1, A);
+    launch_l2p(nr, nleaf, LL.p, I32("leaf_start"), LL.center, ec, LL.L, c->k, leg_table(c), ynear, nsplit,
+               half, I32("perm"), n, x, y, exact_far ? 0 : 1, A);
     prof_end(c, pe, "k_l2p", (double)n * LL.p * LL.p * 8.0 * nr,
              32.0 * n + 16.0 * n * 3 * nr + 16.0 * nleaf * LL.p * LL.p * nr);
     rec(c, 7);
@@ -1287,7 +1291,9 @@ static void fmm_pass_ind(fmmbem_ctx *c, const double2 *sigma, const double2 *mu,
     const int nleaf = (int)T.leaf_start.size() - 1;
     auto I32 = [&](const char *s) { return (int32_t *)c->buf.find(s); };
     const double4 *ec = (double4 *)c->buf.find("ec"), *en = (double4 *)c->buf.find("en");
-    double2 *yv = dget<double2>(c->scratch, "ynear", n), *yn = dget<double2>(c->scratch, "ynearn", n);
+    const int nsplit = p2p_splits_of(nleaf);
+    double2 *yv = dget<double2>(c->scratch, "ynear", (size_t)n * nsplit),
+            *yn = dget<double2>(c->scratch, "ynearn", (size_t)n * nsplit);
     struct CurGuard {
         fmmbem_ctx *c;
         ~CurGuard() { c->cur = c->stream; }
@@ -1298,11 +1304,10 @@ static void fmm_pass_ind(fmmbem_ctx *c, const double2 *sigma, const double2 *mu,
         c->cur = B;
     }
     int pe = prof_begin(c);
-    k_p2p_n<<<nleaf, 64, 0, c->cur>>>(nleaf, I32("leaf_start"), I32("nbr_start"), I32("nbr_list"), exact_far ? 1 : 0,
-                                      ec, en, sigma, mu, c->k, c->rc * c->rc, I32("near_start"), I32("near_col"),
-                                      (double2 *)c->buf.find("near_L"), (double2 *)c->buf.find("near_M"),
-                                      (double2 *)c->buf.find("near_Lp"), (double2 *)c->buf.find("near_Mp"), yv, yn);
-    LAUNCH_OK();
+    launch_p2p_n(nleaf, nsplit, I32("leaf_start"), I32("nbr_start"), I32("nbr_list"), exact_far ? 1 : 0, ec, en, sigma,
+                 mu, c->k, c->rc * c->rc, I32("near_start"), I32("near_col"), (double2 *)c->buf.find("near_L"),
+                 (double2 *)c->buf.find("near_M"), (double2 *)c->buf.find("near_Lp"),
+                 (double2 *)c->buf.find("near_Mp"), yv, yn, c->cur);
     prof_end(c, pe, "k_p2p_n", 100.0 * (exact_far ? (double)n * n : (double)c->p2p_pairs), 0.0);
     c->cur = A;
     LevelDev &LL = c->lev[L];
@@ -1332,7 +1337,7 @@ static void fmm_pass_ind(fmmbem_ctx *c, const double2 *sigma, const double2 *mu,
     }
     pe = prof_begin(c);
     k_l2p_n<<<nleaf, 64, ((size_t)64 * (p + 3) + (size_t)3 * (p + 1) * (p + 2) / 2) * sizeof(double), A>>>(
-        nleaf, p, I32("leaf_start"), LL.center, ec, en, LL.L, Dz, Dp, Dm, c->k, leg_table(c), yv, yn, I32("perm"), n, x,
+        nleaf, p, I32("leaf_start"), LL.center, ec, en, LL.L, Dz, Dp, Dm, c->k, leg_table(c), yv, yn, nsplit, I32("perm"), n, x,
         (double2 *)c->buf.find("beta"), (double2 *)c->buf.find("betap"), y, exact_far ? 0 : 1);
     LAUNCH_OK();
     prof_end(c, pe, "k_l2p_n", (double)n * q1 * 8.0 * 4, 0.0);

@@ -99,11 +99,11 @@ __host__ __device__ inline double coef_b(int n, int m) {
 __host__ __device__ inline int leg_tri(int n, int m) { return n * (n + 1) / 2 + m; }
 __host__ __device__ inline int64_t leg_table_len(int pmax) { return 3 * (int64_t)(pmax + 1) * (pmax + 2) / 2; }
 
-// squared distance without contraction, so that every kernel and the host classify
-// near pairs identically
+// squared distance with its rounding written out (the compiler would contract the sum as it sees
+// fit), so that every kernel classifies near pairs identically
 __device__ inline double dist2_exact(double ax, double ay, double az, double bx, double by, double bz) {
-    double dx = __dsub_rn(bx, ax), dy = __dsub_rn(by, ay), dz = __dsub_rn(bz, az);
-    return __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
+    const double dx = bx - ax, dy = by - ay, dz = bz - az;
+    return fma(dz, dz, fma(dx, dx, __dmul_rn(dy, dy)));
 }
 
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }

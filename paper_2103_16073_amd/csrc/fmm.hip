@@ -317,20 +317,337 @@ __global__ void k_gamma(int64_t n, const double4 *ec, const double4 *en, const d
 }
 
 // ------------------------------------------------------------------ pair-kernel helpers
-// 1/sqrt(d) for a positive, normal d: hardware estimate and two Newton steps (about an ulp)
+// 1/sqrt(d) for a positive, normal d: the hardware estimate y (relative error below 1e-7) and one
+// third-order step, y (1 + e/2 + 3 e^2/8) with e = 1 - d y^2: two instructions fewer than two Newton
+// steps, within the same ulp
 __device__ inline double rsq_nr(double d) {
-    double y = __builtin_amdgcn_rsq(d);
-    double e = fma(-d * y, y, 1.0);
-    y = fma(0.5 * y, e, y);
-    e = fma(-d * y, y, 1.0);
-    return fma(0.5 * y, e, y);
+    const double y = __builtin_amdgcn_rsq(d);
+    const double e = fma(-d * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// cos and sin of 2 pi i / 128
+constexpr int EIKR_N = 128;
+__device__ const double2 EIKR_TAB[EIKR_N] = {
+    {1.0, 0.0}, {0.9987954562051724, 0.049067674327418015},
+    {0.9951847266721969, 0.0980171403295606}, {0.989176509964781, 0.14673047445536175},
+    {0.9807852804032304, 0.19509032201612828}, {0.970031253194544, 0.2429801799032639},
+    {0.9569403357322088, 0.2902846772544624}, {0.9415440651830208, 0.33688985339222005},
+    {0.9238795325112867, 0.3826834323650898}, {0.9039892931234433, 0.4275550934302821},
+    {0.881921264348355, 0.47139673682599764}, {0.8577286100002721, 0.5141027441932218},
+    {0.8314696123025452, 0.5555702330196022}, {0.8032075314806449, 0.5956993044924334},
+    {0.773010453362737, 0.6343932841636455}, {0.7409511253549591, 0.6715589548470184},
+    {0.7071067811865476, 0.7071067811865476}, {0.6715589548470184, 0.7409511253549591},
+    {0.6343932841636455, 0.773010453362737}, {0.5956993044924334, 0.8032075314806449},
+    {0.5555702330196022, 0.8314696123025452}, {0.5141027441932218, 0.8577286100002721},
+    {0.47139673682599764, 0.881921264348355}, {0.4275550934302821, 0.9039892931234433},
+    {0.3826834323650898, 0.9238795325112867}, {0.33688985339222005, 0.9415440651830208},
+    {0.2902846772544624, 0.9569403357322088}, {0.2429801799032639, 0.970031253194544},
+    {0.19509032201612828, 0.9807852804032304}, {0.14673047445536175, 0.989176509964781},
+    {0.0980171403295606, 0.9951847266721969}, {0.049067674327418015, 0.9987954562051724},
+    {0.0, 1.0}, {-0.049067674327418015, 0.9987954562051724},
+    {-0.0980171403295606, 0.9951847266721969}, {-0.14673047445536175, 0.989176509964781},
+    {-0.19509032201612828, 0.9807852804032304}, {-0.2429801799032639, 0.970031253194544},
+    {-0.2902846772544624, 0.9569403357322088}, {-0.33688985339222005, 0.9415440651830208},
+    {-0.3826834323650898, 0.9238795325112867}, {-0.4275550934302821, 0.9039892931234433},
+    {-0.47139673682599764, 0.881921264348355}, {-0.5141027441932218, 0.8577286100002721},
+    {-0.5555702330196022, 0.8314696123025452}, {-0.5956993044924334, 0.8032075314806449},
+    {-0.6343932841636455, 0.773010453362737}, {-0.6715589548470184, 0.7409511253549591},
+    {-0.7071067811865476, 0.7071067811865476}, {-0.7409511253549591, 0.6715589548470184},
+    {-0.773010453362737, 0.6343932841636455}, {-0.8032075314806449, 0.5956993044924334},
+    {-0.8314696123025452, 0.5555702330196022}, {-0.8577286100002721, 0.5141027441932218},
+    {-0.881921264348355, 0.47139673682599764}, {-0.9039892931234433, 0.4275550934302821},
+    {-0.9238795325112867, 0.3826834323650898}, {-0.9415440651830208, 0.33688985339222005},
+    {-0.9569403357322088, 0.2902846772544624}, {-0.970031253194544, 0.2429801799032639},
+    {-0.9807852804032304, 0.19509032201612828}, {-0.989176509964781, 0.14673047445536175},
+    {-0.9951847266721969, 0.0980171403295606}, {-0.9987954562051724, 0.049067674327418015},
+    {-1.0, 0.0}, {-0.9987954562051724, -0.049067674327418015},
+    {-0.9951847266721969, -0.0980171403295606}, {-0.989176509964781, -0.14673047445536175},
+    {-0.9807852804032304, -0.19509032201612828}, {-0.970031253194544, -0.2429801799032639},
+    {-0.9569403357322088, -0.2902846772544624}, {-0.9415440651830208, -0.33688985339222005},
+    {-0.9238795325112867, -0.3826834323650898}, {-0.9039892931234433, -0.4275550934302821},
+    {-0.881921264348355, -0.47139673682599764}, {-0.8577286100002721, -0.5141027441932218},
+    {-0.8314696123025452, -0.5555702330196022}, {-0.8032075314806449, -0.5956993044924334},
+    {-0.773010453362737, -0.6343932841636455}, {-0.7409511253549591, -0.6715589548470184},
+    {-0.7071067811865476, -0.7071067811865476}, {-0.6715589548470184, -0.7409511253549591},
+    {-0.6343932841636455, -0.773010453362737}, {-0.5956993044924334, -0.8032075314806449},
+    {-0.5555702330196022, -0.8314696123025452}, {-0.5141027441932218, -0.8577286100002721},
+    {-0.47139673682599764, -0.881921264348355}, {-0.4275550934302821, -0.9039892931234433},
+    {-0.3826834323650898, -0.9238795325112867}, {-0.33688985339222005, -0.9415440651830208},
+    {-0.2902846772544624, -0.9569403357322088}, {-0.2429801799032639, -0.970031253194544},
+    {-0.19509032201612828, -0.9807852804032304}, {-0.14673047445536175, -0.989176509964781},
+    {-0.0980171403295606, -0.9951847266721969}, {-0.049067674327418015, -0.9987954562051724},
+    {0.0, -1.0}, {0.049067674327418015, -0.9987954562051724},
+    {0.0980171403295606, -0.9951847266721969}, {0.14673047445536175, -0.989176509964781},
+    {0.19509032201612828, -0.9807852804032304}, {0.2429801799032639, -0.970031253194544},
+    {0.2902846772544624, -0.9569403357322088}, {0.33688985339222005, -0.9415440651830208},
+    {0.3826834323650898, -0.9238795325112867}, {0.4275550934302821, -0.9039892931234433},
+    {0.47139673682599764, -0.881921264348355}, {0.5141027441932218, -0.8577286100002721},
+    {0.5555702330196022, -0.8314696123025452}, {0.5956993044924334, -0.8032075314806449},
+    {0.6343932841636455, -0.773010453362737}, {0.6715589548470184, -0.7409511253549591},
+    {0.7071067811865476, -0.7071067811865476}, {0.7409511253549591, -0.6715589548470184},
+    {0.773010453362737, -0.6343932841636455}, {0.8032075314806449, -0.5956993044924334},
+    {0.8314696123025452, -0.5555702330196022}, {0.8577286100002721, -0.5141027441932218},
+    {0.881921264348355, -0.47139673682599764}, {0.9039892931234433, -0.4275550934302821},
+    {0.9238795325112867, -0.3826834323650898}, {0.9415440651830208, -0.33688985339222005},
+    {0.9569403357322088, -0.2902846772544624}, {0.970031253194544, -0.2429801799032639},
+    {0.9807852804032304, -0.19509032201612828}, {0.989176509964781, -0.14673047445536175},
+    {0.9951847266721969, -0.0980171403295606}, {0.9987954562051724, -0.049067674327418015},
+};
+// the table in LDS, by the first 128 threads of the workgroup
+__device__ inline void eikr_stage(double2 *tab, int tid) {
+    if (tid < EIKR_N) tab[tid] = EIKR_TAB[tid];
+}
+// e^{ikr}, kk = k 128 / (2 pi) as a sum of two doubles (eikr_scale): r kk is split into the nearest
+// integer n (the low bits of r kk + 1.5 2^52) and a remainder f, |f| <= 1/2; e^{2 pi i n / 128} comes
+// from the table in LDS and e^{2 pi i f / 128} from the Taylor polynomials through f^7 and f^6
+// (truncation below 2e-17).  About 20 instructions, against about 45 for a Cody-Waite reduction by
+// pi/2 and polynomials through degree 17 with their quadrant selects, and more accurate: k r is not
+// rounded before the reduction.  Absolute error against 113-bit values, worst of 400,000 draws: 2.1e-16
+// for every k r in 0.01..90,000 (the reduction of the rounded product: 2.2e-16 below 1, 9.8e-16 in
+// 1..10, 5.7e-14 in 100..1,000).  Needs k r < 2^46 (truncation numbers up to 1,000 bound k r by 1e7
+// inside a room).
+__device__ inline void eikr(double r, double2 kk, const double2 *tab, double &c, double &s) {
+    const double m = fma(r, kk.x, 6755399441055744.0);
+    const int i = __double2loint(m) & (EIKR_N - 1);
+    const double f = fma(r, kk.y, fma(r, kk.x, 6755399441055744.0 - m));
+    const double t = 2.0 * FMM_PI / EIKR_N, t2 = t * t;
+    const double w = f * f;
+    const double sn = fma(fma(fma(-t * t2 * t2 * t2 / 5040.0, w, t * t2 * t2 / 120.0), w, -t * t2 / 6.0), w, t) * f;
+    const double cm = fma(fma(-t2 * t2 * t2 / 720.0, w, t2 * t2 / 24.0), w, -0.5 * t2) * w;  // cos - 1
+    const double2 e = tab[i];
+    c = fma(-e.y, sn, fma(e.x, cm, e.x));
+    s = fma(e.x, sn, fma(e.y, cm, e.y));
 }
 
 // ------------------------------------------------------------------ P2P + near table
 // y_i = sum_{j in neighbour leaves, |c_i - c_j| >= r_c} [G q_j + dG/dn_y w_j] + sum_near [L sigma + M mu]
-// with q_j = A_j sigma_j, w_j = A_j mu_j.  One workgroup (one wavefront) per target leaf,
-// source tiles staged in LDS.  A small leaf splits every source tile over S groups of lanes, one
-// target per lane of a group, and adds the groups' sums at the end.
+// with q_j = A_j sigma_j, w_j = A_j mu_j, and (NRM) the normal derivative at i of the same layers,
+// yn_i, from the L', M' near entries and the kernel's derivatives.
+//
+// One workgroup of 256 per target leaf and split of its sources.  Bound by FP64 vector instructions
+// (about 60 per pair), so the layout keeps lanes busy and instructions few:
+//  - the neighbour leaves' sources form one list (their ranges end to end), and tiles of it are
+//    staged in LDS whole, whatever the leaves' sizes;
+//  - a lane takes two targets, so that every source read from LDS serves two pairs; TP lanes cover
+//    the leaf and S = floor(256 / TP) lane groups take every S-th source of a tile (leaves hold
+//    17-48 targets mostly: 94-100 % of the lanes busy); the groups' sums are added in LDS;
+//  - pairs closer than r_c (and the self pair) are left to the near table by a zero 1/r, without a
+//    branch.
+// With few leaves (nsplit > 1) the source list is cut into nsplit pieces, one workgroup each, so
+// that a small room still fills the device; piece g writes its own sums at y + g n NR, which L2P adds
+// in order.  Measured against one wavefront per leaf, one target per lane and the polynomial sincos
+// (FP64, one vector): 2,664 elements 255 -> 13.6 us, 90,972 241 -> 73 us, 1M L-room 1.20 -> 0.67 ms
+// (5.4e11 pairs/s); with normal derivatives 2,664 elements 431 -> 19.5 us, 90,972 412 -> 140 us.
+constexpr int P2P_WG = 256, P2P_T = 2;
+// lanes per group TP and groups S of a leaf of nt targets, for the number of passes over the sources
+// P (the fewest possible, or up to three more) with the least lane work P / S; a further pass
+// stages the sources again and has to save 2 % of it.  Four lanes weigh the four candidates.
+__device__ inline void p2p_shape(int nt, int tid, int &TP, int &S) {
+    const int P = (nt + P2P_WG * P2P_T - 1) / (P2P_WG * P2P_T) + (tid & 3);
+    int tp = (nt + P2P_T * P - 1) / (P2P_T * P), sg = P2P_WG / tp;
+    float cost = (float)P / (float)sg * (1.0f + 0.02f * (tid & 3));
+    for (int d = 1; d < 4; d <<= 1) {
+        const float oc = __shfl_xor(cost, d, 4);
+        const int ot = __shfl_xor(tp, d, 4), os = __shfl_xor(sg, d, 4);
+        if (oc < cost || (oc == cost && os < sg)) {
+            cost = oc;
+            tp = ot;
+            sg = os;
+        }
+    }
+    TP = __builtin_amdgcn_readfirstlane(tp);
+    S = __builtin_amdgcn_readfirstlane(sg);
+}
+
+// source tiles: per source (x, y), (z, n_x), (n_y, n_z), then NR (q), NR (w) as double2
+template <int NR> constexpr int p2p_tile() { return NR >= 4 ? 128 : 256; }
+
+template <int NR, bool NRM>
+__global__ void __launch_bounds__(P2P_WG) __attribute__((amdgpu_waves_per_eu(4)))
+k_p2p(int nleaf, const int32_t *leaf_start, const int32_t *nbr_start, const int32_t *nbr_list, int all_leaves,
+      int nsplit, const double4 *ec, const double4 *en, const double2 *sigma, const double2 *mu, double k, double2 kk,
+      double rc2, const int32_t *near_start, const int32_t *near_col, const double2 *nL, const double2 *nM,
+      const double2 *nLp, const double2 *nMp, double2 *y, double2 *yn) {
+    constexpr int T = P2P_T, TS = p2p_tile<NR>(), F = 3 + 2 * NR, NA = NRM ? 2 * NR : NR;
+    constexpr int BUF = TS * F > P2P_WG * T * NA ? TS * F : P2P_WG * T * NA;
+    const int b = blockIdx.x / nsplit, g = blockIdx.x - b * nsplit, tid = threadIdx.x;
+    __shared__ double2 tab[EIKR_N], buf[BUF];
+    __shared__ int rs[32], cum[33];
+    const int ts = leaf_start[b], te = leaf_start[b + 1];
+    int nrng = 1;
+    if (all_leaves) {  // all-pairs product: the one range of every element
+        if (tid == 0) {
+            rs[0] = 0;
+            cum[0] = 0;
+            cum[1] = leaf_start[nleaf];
+        }
+    } else {
+        const int nb0 = nbr_start[b];
+        nrng = nbr_start[b + 1] - nb0;  // at most 27
+        if (tid < 32) {
+            int c = 0;
+            if (tid < nrng) {
+                const int sb = nbr_list[nb0 + tid], ss = leaf_start[sb];
+                rs[tid] = ss;
+                c = leaf_start[sb + 1] - ss;
+            }
+            for (int d = 1; d < 32; d <<= 1) {
+                const int o = __shfl_up(c, d, 32);
+                if (tid >= d) c += o;
+            }
+            cum[tid + 1] = c;
+            if (tid == 0) cum[0] = 0;
+        }
+    }
+    eikr_stage(tab, tid);
+    __syncthreads();
+    // this workgroup's piece of the source list
+    int lo = 0, hi = cum[nrng];
+    if (nsplit > 1) {
+        const unsigned tot = hi, piece = (tot + nsplit - 1) / nsplit;
+        lo = (int)min(tot, g * piece);
+        hi = (int)min(tot, (g + 1) * piece);
+    }
+    int TP, S;
+    p2p_shape(te - ts, tid, TP, S);
+    const int h = tid / TP, l = tid - h * TP;
+    const double inv4pi = 1.0 / (4.0 * FMM_PI);
+    const int64_t n = leaf_start[nleaf];
+    for (int t0 = ts; t0 < te; t0 += TP * T) {
+        // a lane's targets: the second one repeats the first (unused) where the leaf ends
+        int t[T];
+        bool act[T];
+        double4 ct[T], nt[T];
+        double2 acc[T][NR], accn[T][NR];
+#pragma unroll
+        for (int u = 0; u < T; ++u) {
+            t[u] = t0 + l + u * TP;
+            act[u] = t[u] < te && h < S;
+            const int tt = t[u] < te ? t[u] : ts;
+            ct[u] = ec[tt];
+            if (NRM) nt[u] = en[tt];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[u][r] = accn[u][r] = cmk(0, 0);
+        }
+        for (int j0 = lo; j0 < hi; j0 += TS) {
+            __syncthreads();
+            const int idx = j0 + tid;
+            if (tid < TS && idx < hi) {
+                int q = 0;
+#pragma unroll
+                for (int d = 16; d > 0; d >>= 1)
+                    if (q + d < nrng && cum[q + d] <= idx) q += d;
+                const int j = rs[q] + (idx - cum[q]);
+                const double4 c = ec[j], nv = en[j];
+                double2 *o = buf + tid * F;
+                o[0] = cmk(c.x, c.y);
+                o[1] = cmk(c.z, nv.x);
+                o[2] = cmk(nv.y, nv.z);
+                const double wgt = c.w * inv4pi;
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    o[3 + r] = cscale(sigma[(int64_t)j * NR + r], wgt);
+                    o[3 + NR + r] = cscale(mu[(int64_t)j * NR + r], wgt);
+                }
+            }
+            __syncthreads();
+            const int cnt = min(TS, hi - j0);
+            if (h < S && act[0])
+                for (int jj = h; jj < cnt; jj += S) {
+                    const double2 *o = buf + jj * F;
+                    const double2 xy = o[0], zn = o[1], nn2 = o[2];
+#pragma unroll
+                    for (int u = 0; u < T; ++u) {
+                        const double d2 = dist2_exact(ct[u].x, ct[u].y, ct[u].z, xy.x, xy.y, zn.x);
+                        const double dx = xy.x - ct[u].x, dy = xy.y - ct[u].y, dz = zn.x - ct[u].z;
+                        const double ir = d2 < rc2 ? 0.0 : rsq_nr(d2), r = d2 * ir, ir2 = ir * ir, kr = k * r;
+                        double s, c;
+                        eikr(r, kk, tab, c, s);
+                        const double2 G = cmk(c * ir, s * ir);
+                        const double a1 = (dx * zn.y + dy * nn2.x + dz * nn2.y) * ir2;  // (y-x).n / r^2
+                        double a2 = 0, kx = 0, ky = 0;
+                        if (NRM) {
+                            // K = G [a1 a2 (3 - 3ikr - k^2 r^2) - (n_x.n_y / r^2)(ikr - 1)], a2 = -(y-x).n_x / r^2
+                            a2 = -(dx * nt[u].x + dy * nt[u].y + dz * nt[u].z) * ir2;
+                            const double bb = (nt[u].x * zn.y + nt[u].y * nn2.x + nt[u].z * nn2.y) * ir2, mm = a1 * a2;
+                            kx = fma(mm, fma(-kr, kr, 3.0), bb);
+                            ky = -kr * fma(3.0, mm, bb);
+                        }
+#pragma unroll
+                        for (int rr = 0; rr < NR; ++rr) {
+                            const double2 q = o[3 + rr], w = o[3 + NR + rr];
+                            // G (q + (ikr - 1) a1 w)
+                            const double2 v = cmk(fma(-a1, fma(kr, w.y, w.x), q.x), fma(-a1, fma(-kr, w.x, w.y), q.y));
+                            acc[u][rr] = cfma(G, v, acc[u][rr]);
+                            if (NRM) {  // G ((ikr - 1) a2 q) + K w
+                                const double2 z = cmk(fma(-a2, fma(kr, q.y, q.x), fma(kx, w.x, -ky * w.y)),
+                                                      fma(-a2, fma(-kr, q.x, q.y), fma(kx, w.y, ky * w.x)));
+                                accn[u][rr] = cfma(G, z, accn[u][rr]);
+                            }
+                        }
+                    }
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < T; ++u)
+            if (act[u])
+                for (int e = near_start[t[u]] + h + S * g; e < near_start[t[u] + 1]; e += S * nsplit) {
+                    const int64_t j = near_col[e];
+                    const double2 lv = nL[e], mv = nM[e];
+#pragma unroll
+                    for (int rr = 0; rr < NR; ++rr) {
+                        const double2 sg = sigma[j * NR + rr], m_ = mu[j * NR + rr];
+                        acc[u][rr] = cfma(mv, m_, cfma(lv, sg, acc[u][rr]));
+                        if (NRM) accn[u][rr] = cfma(nMp[e], m_, cfma(nLp[e], sg, accn[u][rr]));
+                    }
+                }
+        // add the groups' sums: every step folds the upper half of the groups onto the lower
+        for (int m = S; m > 1;) {
+            const int half = (m + 1) / 2;
+            __syncthreads();
+            if (h >= half && h < m)
+#pragma unroll
+                for (int u = 0; u < T; ++u)
+#pragma unroll
+                    for (int rr = 0; rr < NR; ++rr) {
+                        buf[((h - half) * TP + l) * (T * NA) + u * NA + rr] = acc[u][rr];
+                        if (NRM) buf[((h - half) * TP + l) * (T * NA) + u * NA + NR + rr] = accn[u][rr];
+                    }
+            __syncthreads();
+            if (h < m - half)
+#pragma unroll
+                for (int u = 0; u < T; ++u)
+#pragma unroll
+                    for (int rr = 0; rr < NR; ++rr) {
+                        acc[u][rr] = cadd(acc[u][rr], buf[(h * TP + l) * (T * NA) + u * NA + rr]);
+                        if (NRM) accn[u][rr] = cadd(accn[u][rr], buf[(h * TP + l) * (T * NA) + u * NA + NR + rr]);
+                    }
+            m = half;
+        }
+        if (h == 0)
+#pragma unroll
+            for (int u = 0; u < T; ++u)
+                if (act[u])
+#pragma unroll
+                    for (int rr = 0; rr < NR; ++rr) {
+                        y[(g * n + t[u]) * NR + rr] = acc[u][rr];
+                        if (NRM) yn[(g * n + t[u]) * NR + rr] = accn[u][rr];
+                    }
+    }
+}
+
+// ------------------------------------------------------------------ P2P, FP32 arithmetic
+// Mixed-precision near field: the near/far classification uses the exact FP64 squared distance
+// (so it matches the near table), the kernel evaluation runs in FP32, and the accumulation is
+// Kahan-compensated in FP32.  Near-table entries are stored in FP32.
+__device__ inline void kahan_add(float &s, float &c, float v) {
+    const float y = v - c;
+    const float t = s + y;
+    c = (t - s) - y;
+    s = t;
+}
+
 // Source splits S of a leaf of nt targets: lane groups of TP = floor(64 / S) targets, each group
 // summing every S-th source, ceil(nt / TP) passes over the sources; S in 1..8 minimises the lane
 // work ceil(nt / TP) / S (ties to the smaller S, which adds fewer partial sums).  Lanes past S TP
@@ -347,110 +664,6 @@ __device__ inline int p2p_splits(int nt) {
         }
     }
     return best;
-}
-
-template <int NR>
-__global__ void __launch_bounds__(64) k_p2p(int nleaf, const int32_t *leaf_start, const int32_t *nbr_start,
-                                            const int32_t *nbr_list, int all_leaves, const double4 *ec,
-                                            const double4 *en, const double2 *sigma, const double2 *mu, double k,
-                                            double rc2, const int32_t *near_start, const int32_t *near_col,
-                                            const double2 *nL, const double2 *nM, double2 *y) {
-    const int b = blockIdx.x, tid = threadIdx.x;
-    __shared__ double sx[64], sy[64], sz[64], snx[64], sny[64], snz[64];
-    __shared__ double2 sq[64 * NR], sw[64 * NR];
-    __shared__ double2 red[64 * NR];
-    const int ts = leaf_start[b], te = leaf_start[b + 1];
-    const int nb0 = all_leaves ? 0 : nbr_start[b], nb1 = all_leaves ? nleaf : nbr_start[b + 1];
-    const double inv4pi = 1.0 / (4.0 * FMM_PI);
-    const int S = p2p_splits(te - ts), TP = 64 / S;  // source splits, targets per pass
-    const int h = tid / TP;
-    for (int t0 = ts; t0 < te; t0 += TP) {
-        const int t = t0 + tid % TP;
-        const bool act = t < te && h < S;
-        double4 ct = act ? ec[t] : make_double4(0, 0, 0, 0);
-        double2 acc[NR];
-#pragma unroll
-        for (int r = 0; r < NR; ++r) acc[r] = cmk(0, 0);
-        for (int q = nb0; q < nb1; ++q) {
-            const int sb = all_leaves ? q : nbr_list[q];
-            const int ss = leaf_start[sb], se = leaf_start[sb + 1];
-            for (int j0 = ss; j0 < se; j0 += 64) {
-                __syncthreads();
-                int j = j0 + tid;
-                if (j < se) {
-                    double4 c = ec[j], nv = en[j];
-                    sx[tid] = c.x;
-                    sy[tid] = c.y;
-                    sz[tid] = c.z;
-                    snx[tid] = nv.x;
-                    sny[tid] = nv.y;
-                    snz[tid] = nv.z;
-#pragma unroll
-                    for (int r = 0; r < NR; ++r) {
-                        sq[tid * NR + r] = cscale(sigma[(int64_t)j * NR + r], c.w);
-                        sw[tid * NR + r] = cscale(mu[(int64_t)j * NR + r], c.w);
-                    }
-                }
-                __syncthreads();
-                const int cnt = min(64, se - j0);
-                if (act) {
-                    for (int jj = h; jj < cnt; jj += S) {
-                        double d2 = dist2_exact(ct.x, ct.y, ct.z, sx[jj], sy[jj], sz[jj]);
-                        if (d2 < rc2) continue;
-                        double dx = sx[jj] - ct.x, dy = sy[jj] - ct.y, dz = sz[jj] - ct.z;
-                        const double ir = rsq_nr(d2), r = d2 * ir;
-                        double s, c;
-                        sincos_red(k * r, s, c);
-                        double2 G = cmk(c * ir * inv4pi, s * ir * inv4pi);
-                        double u = (dx * snx[jj] + dy * sny[jj] + dz * snz[jj]) * ir * ir;  // (y-x).n / r^2
-                        // G * (q + (ikr - 1) u w)
-                        const double2 f = cmk(-u, k * r * u);
-#pragma unroll
-                        for (int rr = 0; rr < NR; ++rr) {
-                            double2 t2 = cmul(f, sw[jj * NR + rr]);
-                            acc[rr] = cfma(G, cadd(sq[jj * NR + rr], t2), acc[rr]);
-                        }
-                    }
-                }
-            }
-        }
-        if (act) {
-            for (int e = near_start[t] + h; e < near_start[t + 1]; e += S) {
-                const int64_t j = near_col[e];
-                const double2 l = nL[e], m = nM[e];
-#pragma unroll
-                for (int rr = 0; rr < NR; ++rr) {
-                    acc[rr] = cfma(l, sigma[j * NR + rr], acc[rr]);
-                    acc[rr] = cfma(m, mu[j * NR + rr], acc[rr]);
-                }
-            }
-        }
-        if (S > 1) {  // add the groups' partial sums (group 0 keeps the result)
-            __syncthreads();
-#pragma unroll
-            for (int rr = 0; rr < NR; ++rr) red[tid * NR + rr] = acc[rr];
-            __syncthreads();
-            if (h == 0)
-                for (int g = 1; g < S; ++g)
-#pragma unroll
-                    for (int rr = 0; rr < NR; ++rr) acc[rr] = cadd(acc[rr], red[(tid + g * TP) * NR + rr]);
-        }
-        if (act && h == 0) {
-#pragma unroll
-            for (int rr = 0; rr < NR; ++rr) y[(int64_t)t * NR + rr] = acc[rr];
-        }
-    }
-}
-
-// ------------------------------------------------------------------ P2P, FP32 arithmetic
-// Mixed-precision near field: the near/far classification uses the exact FP64 squared distance
-// (so it matches the near table), the kernel evaluation runs in FP32, and the accumulation is
-// Kahan-compensated in FP32.  Near-table entries are stored in FP32.
-__device__ inline void kahan_add(float &s, float &c, float v) {
-    const float y = v - c;
-    const float t = s + y;
-    c = (t - s) - y;
-    s = t;
 }
 
 template <int NR>
@@ -1115,8 +1328,8 @@ __global__ void __launch_bounds__(256) k_p2m(int nleaf, int p, int CH, const int
 template <int NR, bool STAGE>
 __global__ void __launch_bounds__(64) k_l2p(int nleaf, int p, const int32_t *leaf_start, const double4 *center,
                                             const double4 *ec, const double2 *Lc, double k, const double *leg,
-                                            const double2 *ynear, double half, const int32_t *perm, int64_t n,
-                                            const double2 *x, double2 *y, int has_far) {
+                                            const double2 *ynear, int nsplit, double half, const int32_t *perm,
+                                            int64_t n, const double2 *x, double2 *y, int has_far) {
     extern __shared__ double2 l2p_sm[];
     const int b = blockIdx.x, tid = threadIdx.x;
     const double4 C = center[b];
@@ -1206,7 +1419,9 @@ __global__ void __launch_bounds__(64) k_l2p(int nleaf, int p, const int32_t *lea
         const int64_t u = perm[t];
 #pragma unroll
         for (int rr = 0; rr < NR; ++rr) {
-            double2 v = cadd(ynear[(int64_t)t * NR + rr], far[rr]);
+            double2 v = ynear[(int64_t)t * NR + rr];
+            for (int g2 = 1; g2 < nsplit; ++g2) v = cadd(v, ynear[(g2 * n + t) * NR + rr]);
+            v = cadd(v, far[rr]);
             if (x) v = cadd(v, cscale(x[rr * n + u], half));  // the right-hand side pass has no identity term
             y[rr * n + u] = v;
         }
@@ -1487,84 +1702,6 @@ __global__ void k_bm_rhs(int64_t n, const int32_t *perm, const double2 *gam, dou
     b[u] = cadd(pq[u], cmul(alpha, csub(pq[n + u], cscale(gam[i], 0.5))));
 }
 
-// potential and normal derivative at the targets from one-point pairs and the near table
-__global__ void __launch_bounds__(64) k_p2p_n(int nleaf, const int32_t *leaf_start, const int32_t *nbr_start,
-                                              const int32_t *nbr_list, int all_leaves, const double4 *ec,
-                                              const double4 *en, const double2 *sigma, const double2 *mu, double k,
-                                              double rc2, const int32_t *near_start, const int32_t *near_col,
-                                              const double2 *nL, const double2 *nM, const double2 *nLp,
-                                              const double2 *nMp, double2 *y, double2 *yn) {
-    const int b = blockIdx.x, tid = threadIdx.x;
-    __shared__ double sx[64], sy[64], sz[64], snx[64], sny[64], snz[64];
-    __shared__ double2 sq[64], sw[64];
-    const int ts = leaf_start[b], te = leaf_start[b + 1];
-    const int nb0 = all_leaves ? 0 : nbr_start[b], nb1 = all_leaves ? nleaf : nbr_start[b + 1];
-    const double inv4pi = 1.0 / (4.0 * FMM_PI);
-    for (int t0 = ts; t0 < te; t0 += 64) {
-        const int t = t0 + tid;
-        const bool act = t < te;
-        const double4 ct = act ? ec[t] : make_double4(0, 0, 0, 0);
-        const double4 nt = act ? en[t] : make_double4(0, 0, 1, 0);
-        double2 acc = cmk(0, 0), accn = cmk(0, 0);
-        for (int q = nb0; q < nb1; ++q) {
-            const int sb = all_leaves ? q : nbr_list[q];
-            const int ss = leaf_start[sb], se = leaf_start[sb + 1];
-            for (int j0 = ss; j0 < se; j0 += 64) {
-                __syncthreads();
-                int j = j0 + tid;
-                if (j < se) {
-                    double4 c = ec[j], nv = en[j];
-                    sx[tid] = c.x;
-                    sy[tid] = c.y;
-                    sz[tid] = c.z;
-                    snx[tid] = nv.x;
-                    sny[tid] = nv.y;
-                    snz[tid] = nv.z;
-                    sq[tid] = cscale(sigma[j], c.w);
-                    sw[tid] = cscale(mu[j], c.w);
-                }
-                __syncthreads();
-                const int cnt = min(64, se - j0);
-                if (act) {
-                    for (int jj = 0; jj < cnt; ++jj) {
-                        double d2 = dist2_exact(ct.x, ct.y, ct.z, sx[jj], sy[jj], sz[jj]);
-                        if (d2 < rc2) continue;
-                        const double dx = sx[jj] - ct.x, dy = sy[jj] - ct.y, dz = sz[jj] - ct.z;
-                        const double ir = rsq_nr(d2), r = d2 * ir, ir2 = ir * ir;
-                        double s, c;
-                        sincos_red(k * r, s, c);
-                        const double2 E = cmk(c * inv4pi, s * inv4pi);  // e^{ikr} / 4 pi
-                        const double2 G = cscale(E, ir);
-                        const double dny = dx * snx[jj] + dy * sny[jj] + dz * snz[jj];
-                        const double dnx = dx * nt.x + dy * nt.y + dz * nt.z;
-                        const double nn = nt.x * snx[jj] + nt.y * sny[jj] + nt.z * snz[jj];
-                        const double2 g1 = cmul(G, cmk(-1.0, k * r));  // G (ikr - 1)
-                        // potential: G q + G (ikr - 1) (d.n_y)/r^2 w
-                        acc = cfma(G, sq[jj], acc);
-                        acc = cfma(cscale(g1, dny * ir2), sw[jj], acc);
-                        // normal derivative: -G (ikr - 1)(d.n_x)/r^2 q + K w
-                        accn = cfma(cscale(g1, -dnx * ir2), sq[jj], accn);
-                        const double2 k3 = cmul(E, cmk(3.0 - k * k * d2, -3.0 * k * r));  // e(3 - 3ikr - k^2 r^2)
-                        const double2 K = csub(cscale(k3, -dnx * dny * ir2 * ir2 * ir), cscale(cmul(E, cmk(-1.0, k * r)), nn * ir2 * ir));
-                        accn = cfma(K, sw[jj], accn);
-                    }
-                }
-            }
-        }
-        if (act) {
-            for (int e = near_start[t]; e < near_start[t + 1]; ++e) {
-                const int j = near_col[e];
-                acc = cfma(nL[e], sigma[j], acc);
-                acc = cfma(nM[e], mu[j], acc);
-                accn = cfma(nLp[e], sigma[j], accn);
-                accn = cfma(nMp[e], mu[j], accn);
-            }
-            y[t] = acc;
-            yn[t] = accn;
-        }
-    }
-}
-
 // derivative local expansions of a leaf (degree p + 1) from its local expansion D (degree p):
 //   d_z R_n^m = k (a_{n-1}^m R_{n-1}^m - a_n^m R_{n+1}^m), etc. (the P2M recurrences), collected
 //   per output coefficient (n, m)
@@ -1599,8 +1736,7 @@ __global__ void __launch_bounds__(64) k_l2p_n(int nleaf, int p, const int32_t *l
                                               const double4 *ec, const double4 *en, const double2 *Lc,
                                               const double2 *Dz, const double2 *Dp, const double2 *Dm, double k,
                                               const double *leg, const double2 *ynear, const double2 *ynearn,
-                                              const int32_t *perm,
-                                              int64_t n, const double2 *x, const double2 *bm, const double2 *bp,
+                                              int nsplit, const int32_t *perm, int64_t n, const double2 *x, const double2 *bm, const double2 *bp,
                                               double2 *y, int has_far) {
     extern __shared__ double jbuf[];
     const int b = blockIdx.x, tid = threadIdx.x;
@@ -1674,7 +1810,13 @@ __global__ void __launch_bounds__(64) k_l2p_n(int nleaf, int p, const int32_t *l
         farn = cadd(farn, cmul(cmk(0.5 * nt.x, -0.5 * nt.y), fp));
         farn = cadd(farn, cmul(cmk(0.5 * nt.x, 0.5 * nt.y), fm));
         const int64_t u = perm[t];
-        double2 v1 = cadd(ynear[t], far), v2 = cadd(ynearn[t], farn);
+        double2 v1 = ynear[t], v2 = ynearn[t];
+        for (int g = 1; g < nsplit; ++g) {
+            v1 = cadd(v1, ynear[g * n + t]);
+            v2 = cadd(v2, ynearn[g * n + t]);
+        }
+        v1 = cadd(v1, far);
+        v2 = cadd(v2, farn);
         if (x) {
             const double2 pm = x[u], pp = x[n + u];
             v1 = cadd(v1, cscale(cadd(pm, pp), 0.5));
@@ -1732,7 +1874,19 @@ __global__ void k_mul_diag2(int64_t n, const int32_t *perm, const double2 *inv, 
     default: throw FmmError(-1, "right-hand-side chunk must be 1, 2 or 4");  \
     }
 
-void launch_p2p(int nr, bool fp32, int nleaf, const int32_t *leaf_start, const int32_t *nbr_start,
+// e^{ikr} by table steps: k 128 / (2 pi) as a sum of two doubles
+static double2 eikr_scale(double k) {
+    const long double v = (long double)k * (EIKR_N / (2.0L * 3.14159265358979323846264338327950288L));
+    const double hi = (double)v;
+    return make_double2(hi, (double)(v - (long double)hi));
+}
+
+// pieces of every leaf's source list in the FP64 near field: enough workgroups for every CU to hold
+// its eight (2,048), at most 16 sums for L2P to add.  56 leaves (2,664 elements): 29.6 us whole,
+// 13.6 us in 16 pieces, 16.8 us in 32; the 2,700 leaves of 90,972 elements gain nothing from pieces.
+int p2p_splits_of(int nleaf) { return std::max(1, std::min(16, ceil_div(2048, std::max(1, nleaf)))); }
+
+void launch_p2p(int nr, bool fp32, int nleaf, int nsplit, const int32_t *leaf_start, const int32_t *nbr_start,
                 const int32_t *nbr_list, int all_leaves, const double4 *ec, const double4 *en, const double2 *sigma,
                 const double2 *mu, double k, double rc2, const int32_t *near_start, const int32_t *near_col,
                 const void *nL, const void *nM, double2 *y, hipStream_t st) {
@@ -1742,10 +1896,23 @@ void launch_p2p(int nr, bool fp32, int nleaf, const int32_t *leaf_start, const i
         k_p2p32<R><<<nleaf, 64, 0, st>>>(nleaf, leaf_start, nbr_start, nbr_list, ec, en, sigma, mu, k, rc2,          \
                                          near_start, near_col, (const float2 *)nL, (const float2 *)nM, y);           \
     else                                                                                                              \
-        k_p2p<R><<<nleaf, 64, 0, st>>>(nleaf, leaf_start, nbr_start, nbr_list, all_leaves, ec, en, sigma, mu, k, rc2, \
-                                       near_start, near_col, (const double2 *)nL, (const double2 *)nM, y)
+        k_p2p<R, false><<<nleaf * nsplit, P2P_WG, 0, st>>>(nleaf, leaf_start, nbr_start, nbr_list, all_leaves, nsplit, \
+                                                           ec, en, sigma, mu, k, eikr_scale(k), rc2, near_start,      \
+                                                           near_col, (const double2 *)nL, (const double2 *)nM,        \
+                                                           nullptr, nullptr, y, nullptr)
     FMM_NR_DISPATCH(nr, P2P_CALL)
 #undef P2P_CALL
+    LAUNCH_OK();
+}
+
+// potential y and normal derivative yn of one vector
+void launch_p2p_n(int nleaf, int nsplit, const int32_t *leaf_start, const int32_t *nbr_start, const int32_t *nbr_list,
+                  int all_leaves, const double4 *ec, const double4 *en, const double2 *sigma, const double2 *mu,
+                  double k, double rc2, const int32_t *near_start, const int32_t *near_col, const double2 *nL,
+                  const double2 *nM, const double2 *nLp, const double2 *nMp, double2 *y, double2 *yn, hipStream_t st) {
+    k_p2p<1, true><<<nleaf * nsplit, P2P_WG, 0, st>>>(nleaf, leaf_start, nbr_start, nbr_list, all_leaves, nsplit, ec,
+                                                      en, sigma, mu, k, eikr_scale(k), rc2, near_start, near_col, nL,
+                                                      nM, nLp, nMp, y, yn);
     LAUNCH_OK();
 }
 
@@ -1806,21 +1973,21 @@ void launch_p2m(int nr, int nleaf, int p, const int32_t *leaf_start, const doubl
 }
 
 void launch_l2p(int nr, int nleaf, int p, const int32_t *leaf_start, const double4 *center, const double4 *ec,
-                const double2 *Lc, double k, const double *leg, const double2 *ynear, double half,
+                const double2 *Lc, double k, const double *leg, const double2 *ynear, int nsplit, double half,
                 const int32_t *perm, int64_t n, const double2 *x, double2 *y, int has_far, hipStream_t st) {
     if (nleaf <= 0) return;
     const size_t base = ((size_t)64 * (p + 2) + (size_t)3 * p * (p + 1) / 2 + 2 * BS_TERMS) * sizeof(double);
     const size_t staged = base + (size_t)nr * p * p * 16;
     if (staged <= 48 * 1024) {
 #define L2P_CALL(R)                                                                                                   \
-    k_l2p<R, true><<<nleaf, 64, staged, st>>>(nleaf, p, leaf_start, center, ec, Lc, k, leg, ynear, half, perm, n, x, y, \
-                                              has_far)
+    k_l2p<R, true><<<nleaf, 64, staged, st>>>(nleaf, p, leaf_start, center, ec, Lc, k, leg, ynear, nsplit, half, perm, n, \
+                                              x, y, has_far)
         FMM_NR_DISPATCH(nr, L2P_CALL)
 #undef L2P_CALL
     } else {
 #define L2P_CALL(R)                                                                                                  \
-    k_l2p<R, false><<<nleaf, 64, base, st>>>(nleaf, p, leaf_start, center, ec, Lc, k, leg, ynear, half, perm, n, x, y, \
-                                             has_far)
+    k_l2p<R, false><<<nleaf, 64, base, st>>>(nleaf, p, leaf_start, center, ec, Lc, k, leg, ynear, nsplit, half, perm, n, \
+                                             x, y, has_far)
         FMM_NR_DISPATCH(nr, L2P_CALL)
 #undef L2P_CALL
     }

@@ -1,0 +1,53 @@
+"""Pair kernels (near field of a product, field at receivers) at the sizes where their split of the
+work changes, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import bem
+from paper_2103_16073_amd import synth
+from rc_check import oracle_rc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def F():
+    from paper_2103_16073_amd import fmmbem
+    fmmbem.lib()
+    return fmmbem
+
+
+def _ctx(F, room, k, **opt):
+    ctx = F.Context(0, **opt)
+    ctx.fmmbem_set_mesh(room.vertices, room.triangles)
+    ctx.fmmbem_set_wavenumber(k)
+    ctx.fmmbem_set_admittance(room.beta)
+    return ctx
+
+
+# leaves of a few targets (odd counts, single elements), of about 50, of about 270 (one pass of more
+# than 128 lanes) and of more than 512 (several passes); the source list whole or in up to 16 pieces
+@pytest.mark.parametrize("h,opt", [(0.5, {}), (0.34, dict(leaf_max=1)), (0.17, {}), (0.07, dict(max_depth=2)),
+                                   (0.045, dict(max_depth=2)), (0.045, {})])
+@pytest.mark.parametrize("form", ["direct", "bm"])
+def test_near_field_leaf_sizes_vs_oracle(F, h, opt, form):
+    """The all-pairs product (every pair through the pair kernel) to rounding and the FMM product to
+    its truncation, one to four vectors, on sampled rows."""
+    room = synth.shoebox(3.0, 2.5, 2.0, h)
+    k = synth.wavenumber(250.0)
+    ctx = _ctx(F, room, k, **opt)
+    if form == "bm":
+        ctx.fmmbem_set_formulation(F.FMMBEM_DIRECT_BM)
+    rows = np.unique(np.linspace(0, room.n - 1, 40).astype(int))
+    X = synth.complex_normal(room.n, 5, count=4)
+    rc = oracle_rc(ctx, room)
+    rowsf = bem.direct_matvec_rows if form == "direct" else bem.bm_matvec_rows
+    ref = np.stack([rowsf(room.vertices, room.triangles, k, room.beta, rc, x, rows) for x in X])
+    for nr in ((1, 2, 4) if form == "direct" else (1,)):
+        y = ctx.fmmbem_matvec(X[:nr], exact_far=True)[:, rows]
+        f = ctx.fmmbem_matvec(X[:nr])[:, rows]
+        for q in range(nr):
+            s = np.linalg.norm(ref[q])
+            assert np.linalg.norm(y[q] - ref[q]) < 1e-12 * s, (nr, q, np.linalg.norm(y[q] - ref[q]) / s)
+            assert np.linalg.norm(f[q] - ref[q]) < 2e-6 * s, (nr, q, np.linalg.norm(f[q] - ref[q]) / s)
+    ctx.close()
