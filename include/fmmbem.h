@@ -383,8 +383,8 @@ int fmmbem_eval_field_dev(fmmbem_ctx *ctx, int32_t isrc, int64_t nr, const void 
                           void *psi_dev, void *stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc): fmmbem_eval_field_dev with its two density arrays in a
- * fixed device array of the library (32 MiB, held by every device the library runs on until the
+ * loops, harnesses that forbid hipMalloc): fmmbem_eval_field_dev with its work arrays in a
+ * fixed device array of the library (34 MiB, held by every device the library runs on until the
  * process ends) instead of the context's workspace.  It calls no hipMalloc, hipFree or other
  * allocating routine and builds nothing: the context must be set up already (fmmbem_setup, or any
  * earlier product, solve or field call, after the last setter), else FMMBEM_ENOTREADY.  At most

@@ -77,11 +77,9 @@ void launch_l2p(int nr, int nleaf, int p, const int32_t *leaf_start, const doubl
 __global__ void k_cvt_d2f(int64_t, const double2 *, float2 *);
 __global__ void k_cvt_f2d(int64_t, const float2 *, double2 *);
 __global__ void k_cvt_real_d2f(int64_t, const double *, float *);
-__global__ void k_field(int64_t, const double *, const double4 *, const double4 *, const double *, const double2 *,
-                        const double2 *, double, double, double, double, double, double2, double2 *);
-__global__ void k_field_tile(int64_t, int64_t, const double *, const double4 *, const double4 *, const double *,
-                             const double2 *, const double2 *, double, double, double, double, double, double2,
-                             double2 *);
+void launch_field(int64_t nt, int64_t nr, const FieldTree &tree, const double *pts, const double4 *ec,
+                  const double4 *en, const double *ev, const double2 *sigma, const double2 *mu, double k, double rc2,
+                  const double *rs, double2 amp, double2 *part, double2 *out, hipStream_t st);
 __global__ void k_diag_inv(int64_t, const int32_t *, const int32_t *, const int32_t *, const double2 *,
                            const double2 *, const double2 *, double, double, double2 *);
 __global__ void k_mul_diag(int64_t, const double2 *, const double2 *, double2 *);
@@ -191,6 +189,7 @@ static void setup_mesh(fmmbem_ctx *c) {
     upload(c->buf, "perm", T.perm, st);
     upload(c->buf, "leaf_of", leaf_of, st);
     upload(c->buf, "leaf_start", T.leaf_start, st);
+    upload(c->buf, "leaf_code", T.lv[L].code, st);
     upload(c->buf, "nbr_start", T.nbr_start, st);
     upload(c->buf, "nbr_list", T.nbr_list, st);
     // P2P pairs (one-point rule candidates) for reporting
@@ -1474,12 +1473,12 @@ using namespace fmm;
 
 // ------------------------------------------------------------------ fixed field workspace
 // Device workspace of fmmbem_eval_field_noalloc: the receiver formula's two density arrays
-// (sigma, mu) for at most NOALLOC_MAX_N elements, 32 MiB.  Every device the library runs on holds
+// (sigma, mu) for at most NOALLOC_MAX_N elements and its partial sums, 34 MiB.  Every device the library runs on holds
 // its own copy until the process ends.  Host code never uses the array's name as an address: the
 // address on each device comes from hipGetSymbolAddress, taken once per device at context creation
 // with that device current.
 static constexpr int64_t NOALLOC_MAX_N = (int64_t)1 << 20;
-static __device__ __align__(256) double2 scratch[2 * NOALLOC_MAX_N];
+static __device__ __align__(256) double2 scratch[2 * NOALLOC_MAX_N + FIELD_PART];
 static std::mutex g_noalloc_mu;
 static std::map<int, double2 *> g_noalloc_ptr;  // device -> address of `scratch` there
 
@@ -2656,10 +2655,11 @@ int fmmbem_learned_train(fmmbem_ctx *ctx, int32_t isrc, const fmmbem_train_opts 
 }
 
 // Field at nr receivers (device points pts, nr x 3) from the surface unknown x (device, caller
-// order) into psi (device), on stream st, with the two density arrays sigma, mu (n each) supplied
-// by the caller of this helper (the context's workspace or a fixed device array).
+// order) into psi (device), on stream st, with the two density arrays sigma, mu (n each) and the
+// FIELD_PART partial sums supplied by the caller of this helper (the context's workspace
+// or a fixed device array).
 static void eval_field_run(fmmbem_ctx *ctx, int isrc, int64_t nr, const double *pts, const double2 *x, double2 *psi,
-                           double2 *sigma, double2 *mu, hipStream_t st) {
+                           double2 *sigma, double2 *mu, double2 *part, hipStream_t st) {
     const int64_t n = ctx->nt;
     const double *rs = &ctx->src[3 * isrc];
     const int form = indirect(ctx) ? 3 : dpsi(ctx) ? 1 : 0;
@@ -2669,18 +2669,15 @@ static void eval_field_run(fmmbem_ctx *ctx, int isrc, int64_t nr, const double *
                                                    (double4 *)ctx->buf.find("ec"), (double4 *)ctx->buf.find("en"), bm,
                                                    bp, ctx->k, rs[0], rs[1], rs[2], ctx->src_amp[isrc], sigma, mu);
     LAUNCH_OK();
-    const double4 *ec = (double4 *)ctx->buf.find("ec"), *en = (double4 *)ctx->buf.find("en");
-    const double *ev = (double *)ctx->buf.find("ev");
-    // many points: FIELD_FQ per workgroup sharing element tiles in LDS, once there are about three
-    // such workgroups per CU; fewer points: one workgroup per point
-    if (nr >= (int64_t)FIELD_FQ * 768)
-        k_field_tile<<<(unsigned)ceil_div(nr, FIELD_FQ), 256, 0, st>>>(n, nr, pts, ec, en, ev, sigma, mu, ctx->k,
-                                                                      ctx->rc * ctx->rc, rs[0], rs[1], rs[2],
-                                                                      ctx->src_amp[isrc], psi);
-    else
-        k_field<<<(unsigned)nr, 256, 0, st>>>(n, pts, ec, en, ev, sigma, mu, ctx->k, ctx->rc * ctx->rc, rs[0], rs[1],
-                                              rs[2], ctx->src_amp[isrc], psi);
-    LAUNCH_OK();
+    const TreeHost &T = ctx->tree;
+    FieldTree tree{(uint64_t *)ctx->buf.find("leaf_code"), (int32_t *)ctx->buf.find("leaf_start"),
+                   (int)T.leaf_start.size() - 1, T.depth, 0, {T.lo[0], T.lo[1], T.lo[2]},
+                   (double)(1u << T.depth) / T.side};
+    // cells an element closer than r_c may lie away (one, unless a depth-2 leaf is smaller than r_c)
+    tree.reach = (int)std::min(std::floor(ctx->rc * tree.scale + 1e-9), (double)(1u << T.depth)) + 1;
+    launch_field(n, nr, tree, pts, (double4 *)ctx->buf.find("ec"), (double4 *)ctx->buf.find("en"),
+                 (double *)ctx->buf.find("ev"), sigma, mu, ctx->k, ctx->rc * ctx->rc, rs, ctx->src_amp[isrc], part, psi,
+                 st);
 }
 
 // checks shared by the host and device variants; 0 or an error status
@@ -2706,9 +2703,10 @@ int fmmbem_eval_field(fmmbem_ctx *ctx, int32_t isrc, int64_t nr, const double *r
     double *dp = dget<double>(ctx->scratch, "fe_pts", 3 * nr);
     double2 *dout = dget<double2>(ctx->scratch, "fe_out", nr);
     double2 *dsg = dget<double2>(ctx->scratch, "fe_sg", n), *dmu = dget<double2>(ctx->scratch, "fe_mu", n);
+    double2 *dpart = dget<double2>(ctx->scratch, "fe_part", FIELD_PART);
     h2d_now(dx, x, sizeof(double2) * nu, st);
     h2d_now(dp, r, sizeof(double) * 3 * nr, st);
-    eval_field_run(ctx, isrc, nr, dp, dx, dout, dsg, dmu, st);
+    eval_field_run(ctx, isrc, nr, dp, dx, dout, dsg, dmu, dpart, st);
     HIP_OK(hipMemcpyAsync(psi, dout, sizeof(double2) * nr, hipMemcpyDeviceToHost, st));
     HIP_OK(hipStreamSynchronize(st));
     return FMMBEM_OK;
@@ -2738,7 +2736,7 @@ int fmmbem_eval_field_noalloc(fmmbem_ctx *ctx, int32_t isrc, int64_t nr, const v
     ev_record(ctx, EV_CALLER_IN, caller);
     ev_wait(ctx, EV_CALLER_IN, ctx->stream);
     eval_field_run(ctx, isrc, nr, (const double *)r_dev, (const double2 *)x_dev, (double2 *)psi_dev, ws,
-                   ws + NOALLOC_MAX_N, ctx->stream);
+                   ws + NOALLOC_MAX_N, ws + 2 * NOALLOC_MAX_N, ctx->stream);
     ev_record(ctx, EV_CALLER_DONE, ctx->stream);
     ev_wait(ctx, EV_CALLER_DONE, caller);
     return FMMBEM_OK;
@@ -2755,11 +2753,12 @@ int fmmbem_eval_field_dev(fmmbem_ctx *ctx, int32_t isrc, int64_t nr, const void 
     if (nr == 0) return FMMBEM_OK;
     const int64_t n = ctx->nt;
     double2 *dsg = dget<double2>(ctx->scratch, "fe_sg", n), *dmu = dget<double2>(ctx->scratch, "fe_mu", n);
+    double2 *dpart = dget<double2>(ctx->scratch, "fe_part", FIELD_PART);
     hipStream_t caller = (hipStream_t)stream;
     ev_record(ctx, EV_CALLER_IN, caller);
     ev_wait(ctx, EV_CALLER_IN, ctx->stream);
     eval_field_run(ctx, isrc, nr, (const double *)r_dev, (const double2 *)x_dev, (double2 *)psi_dev, dsg, dmu,
-                   ctx->stream);
+                   dpart, ctx->stream);
     ev_record(ctx, EV_CALLER_DONE, ctx->stream);
     ev_wait(ctx, EV_CALLER_DONE, caller);
     return FMMBEM_OK;

@@ -1430,114 +1430,174 @@ __global__ void __launch_bounds__(64) k_l2p(int nleaf, int p, const int32_t *lea
 
 // ------------------------------------------------------------------ field at points
 // out[q] = amp * G(r_q, rs) + sum_j [L_j(r_q) sigma_j + M_j(r_q) mu_j], accurate integrals for
-// elements with |r_q - c_j| < r_c, one-point rule otherwise.  One workgroup per point (few points:
-// below about three workgroups of k_field_tile per CU).
-__global__ void __launch_bounds__(256) k_field(int64_t nt, const double *pts, const double4 *ec, const double4 *en,
-                                               const double *ev, const double2 *sigma, const double2 *mu, double k,
-                                               double rc2, double sx, double sy, double sz, double2 amp,
-                                               double2 *out) {
-    const int q = blockIdx.x, tid = threadIdx.x;
-    const double x[3] = {pts[3 * q], pts[3 * q + 1], pts[3 * q + 2]};
-    double2 acc = cmk(0, 0);
-    const double inv4pi = 1.0 / (4.0 * FMM_PI);
-    for (int64_t j = tid; j < nt; j += blockDim.x) {
-        double4 c = ec[j];
-        double d2 = dist2_exact(x[0], x[1], x[2], c.x, c.y, c.z);
-        double2 L, M;
-        if (d2 < rc2) {
-            double v[9];
-            for (int e = 0; e < 9; ++e) v[e] = ev[9 * j + e];
-            tri_integrals(x, v, k, 0, L, M);
-        } else {
-            double4 nv = en[j];
-            double dx = c.x - x[0], dy = c.y - x[1], dz = c.z - x[2];
-            double r = sqrt(d2), s, co;
-            sincos(k * r, &s, &co);
-            double2 G = cmk(co / r * inv4pi, s / r * inv4pi);
-            double u = (dx * nv.x + dy * nv.y + dz * nv.z) / d2;
-            L = cscale(G, c.w);
-            M = cscale(cmul(G, cmk(-u, k * r * u)), c.w);
-        }
-        acc = cfma(L, sigma[j], acc);
-        acc = cfma(M, mu[j], acc);
-    }
-    __shared__ double2 red[256];
-    red[tid] = acc;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (tid < s) red[tid] = cadd(red[tid], red[tid + s]);
-        __syncthreads();
-    }
-    if (tid == 0) {
-        double dx = x[0] - sx, dy = x[1] - sy, dz = x[2] - sz;
-        double r = sqrt(dx * dx + dy * dy + dz * dz), s, co;
-        sincos(k * r, &s, &co);
-        out[q] = cadd(red[0], cmul(amp, cmk(co / r * inv4pi, s / r * inv4pi)));
-    }
+// elements with |r_q - c_j| < r_c, one-point rule otherwise.
+//
+// A workgroup takes R points (8; fewer when fewer are asked for) and one piece of the elements: every
+// thread reads its own elements straight into registers (consecutive, no staging), and the points'
+// coordinates are the same for all threads (scalar registers), so an element read serves R pairs.
+// Bound by FP64 vector instructions (about 60 per pair; e^{ikr} from the table, as in k_p2p).  The
+// elements are cut into pieces until there are a few thousand workgroups (field_pieces): with few
+// points they are the only parallelism, with many they even out the last round of workgroups.
+// Every piece writes its partial sums; k_field_sum adds them in order with the incident field.  The
+// pairs closer than r_c take a zero 1/r in that loop; the first workgroups of the launch (one
+// wavefront per point) find them through the octree's leaves and write their accurate integrals as
+// one more partial sum, beside the other workgroups.
+// Measured against one workgroup per point, or 8 points sharing element tiles in LDS from 6,144 points
+// on, both with the polynomial sincos: 16 points of 90,972 elements 384 -> 15.4 us (both kernels),
+// 19,200 points of 906,812 elements 80.8 -> 30.7 ms (2.2e11 -> 5.7e11 pairs/s).
+
+// spreads the bits of a cell coordinate (below 2^21) three apart
+__device__ inline uint64_t spread3_dev(uint64_t v) {
+    v = (v | v << 32) & 0x1f00000000ffffULL;
+    v = (v | v << 16) & 0x1f0000ff0000ffULL;
+    v = (v | v << 8) & 0x100f00f00f00f00fULL;
+    v = (v | v << 4) & 0x10c30c30c30c30c3ULL;
+    return (v | v << 2) & 0x1249249249249249ULL;
 }
 
-// The same for many points: a workgroup takes FIELD_FQ points, tiles of
-// 256 elements pass through LDS once for all of them (one workgroup per point read every element
-// from the caches once per point), 32 threads per point take every 32nd element of a tile, and
-// each point's 32 partial sums are added in a fixed order.  1/r and sin/cos(kr) as in the pair
-// kernel of the product.  Three waves per SIMD (168 registers; four waves spill): 19,200 points
-// on the 1M L-room at 2.0e11 pairs/s, against 1.25-1.47e11 with one workgroup per point.
-static_assert(FIELD_FQ * 32 == 256, "32 threads per receiver in a workgroup of 256");
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
-k_field_tile(int64_t nt, int64_t nq, const double *pts, const double4 *ec, const double4 *en, const double *ev,
-             const double2 *sigma, const double2 *mu, double k, double rc2, double sx, double sy, double sz,
-             double2 amp, double2 *out) {
-    __shared__ double4 sc[256], sn[256];
-    __shared__ double2 ssg[256], smu[256], red[256];
-    const int tid = threadIdx.x, l = tid & 31;
-    const int64_t q = (int64_t)blockIdx.x * FIELD_FQ + (tid >> 5), qc = q < nq ? q : nq - 1;
-    const double x[3] = {pts[3 * qc], pts[3 * qc + 1], pts[3 * qc + 2]};
-    const double inv4pi = 1.0 / (4.0 * FMM_PI);
+// accurate contribution of the elements closer than r_c to the point x, summed over the wavefront:
+// lanes look up the leaves of the cells within `reach` of the point's cell by their Morton codes,
+// then take the elements of every leaf found
+__device__ double2 field_near(const double *x, const FieldTree &T, const double4 *ec, const double *ev,
+                              const double2 *sigma, const double2 *mu, double k, double rc2) {
+    const int lane = threadIdx.x & 63, w = 2 * T.reach + 1, ncell = w * w * w, nc = 1 << T.depth;
+    int base[3];
+    for (int d = 0; d < 3; ++d) {  // cells far outside stay outside; a NaN ends up in no cell
+        const double q = floor((x[d] - T.lo[d]) * T.scale);
+        base[d] = q >= -1e6 && q <= 4e6 ? (int)q : -1000000;
+    }
     double2 acc = cmk(0, 0);
-    for (int64_t j0 = 0; j0 < nt; j0 += 256) {
-        __syncthreads();
-        if (j0 + tid < nt) {
-            sc[tid] = ec[j0 + tid];
-            sn[tid] = en[j0 + tid];
-            ssg[tid] = sigma[j0 + tid];
-            smu[tid] = mu[j0 + tid];
-        }
-        __syncthreads();
-        const int cnt = (int)(nt - j0 < 256 ? nt - j0 : 256);
-        for (int jj = l; jj < cnt; jj += 32) {
-            const double4 c = sc[jj];
-            const double d2 = dist2_exact(x[0], x[1], x[2], c.x, c.y, c.z);
-            double2 L, M;
-            if (d2 < rc2) {
-                double v[9];
-                for (int e = 0; e < 9; ++e) v[e] = ev[9 * (j0 + jj) + e];
-                tri_integrals(x, v, k, 0, L, M);
-            } else {
-                const double4 nv = sn[jj];
-                const double dx = c.x - x[0], dy = c.y - x[1], dz = c.z - x[2];
-                const double ir = rsq_nr(d2), r = d2 * ir;
-                double s, co;
-                sincos_red(k * r, s, co);
-                const double2 G = cmk(co * ir * inv4pi, s * ir * inv4pi);
-                const double u = (dx * nv.x + dy * nv.y + dz * nv.z) * ir * ir;
-                L = cscale(G, c.w);
-                M = cscale(cmul(G, cmk(-u, k * r * u)), c.w);
+    for (int c0 = 0; c0 < ncell; c0 += 64) {
+        int ss = 0, cnt = 0;
+        const int c = c0 + lane;
+        if (c < ncell) {
+            const int ix = base[0] + c % w - T.reach, iy = base[1] + c / w % w - T.reach, iz = base[2] + c / (w * w) - T.reach;
+            if (ix >= 0 && iy >= 0 && iz >= 0 && ix < nc && iy < nc && iz < nc) {
+                const uint64_t code = spread3_dev(ix) | spread3_dev(iy) << 1 | spread3_dev(iz) << 2;
+                int a = 0, b = T.nleaf;  // first leaf whose code is not below
+                while (a < b) {
+                    const int m = (a + b) >> 1;
+                    if (T.code[m] < code) a = m + 1;
+                    else b = m;
+                }
+                if (a < T.nleaf && T.code[a] == code) {
+                    ss = T.leaf_start[a];
+                    cnt = T.leaf_start[a + 1] - ss;
+                }
             }
-            acc = cfma(L, ssg[jj], acc);
-            acc = cfma(M, smu[jj], acc);
+        }
+        for (uint64_t m = __ballot(cnt > 0); m; m &= m - 1) {
+            const int src = __builtin_ctzll(m), s0 = __shfl(ss, src), n0 = __shfl(cnt, src);
+            for (int e = lane; e < n0; e += 64) {
+                const int64_t j = s0 + e;
+                const double4 cj = ec[j];
+                if (dist2_exact(x[0], x[1], x[2], cj.x, cj.y, cj.z) < rc2) {
+                    double v[9];
+                    for (int q = 0; q < 9; ++q) v[q] = ev[9 * j + q];
+                    double2 L, M;
+                    tri_integrals(x, v, k, 0, L, M);
+                    acc = cfma(M, mu[j], cfma(L, sigma[j], acc));
+                }
+            }
         }
     }
-    red[tid] = acc;
-    __syncthreads();
-    for (int h = 16; h > 0; h >>= 1) {
-        if (l < h) red[tid] = cadd(red[tid], red[tid + h]);
-        __syncthreads();
+    for (int d = 32; d > 0; d >>= 1) acc = cmk(acc.x + __shfl_xor(acc.x, d), acc.y + __shfl_xor(acc.y, d));
+    return acc;
+}
+
+template <int R>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+k_field(int64_t nt, int64_t nq, int64_t piece, int npiece, unsigned ngroup, FieldTree tree,
+        const double *__restrict__ pts, const double4 *__restrict__ ec, const double4 *__restrict__ en,
+        const double *__restrict__ ev,        const double2 *__restrict__ sigma, const double2 *__restrict__ mu, double k, double2 kk, double rc2,
+        double2 *__restrict__ part) {
+    __shared__ double2 tab[EIKR_N], red[4 * R];
+    const int tid = threadIdx.x;
+    const unsigned nnear = (unsigned)((nq + 3) / 4);
+    if (blockIdx.x < nnear) {
+        const int64_t q = (int64_t)blockIdx.x * 4 + (tid >> 6);
+        if (q >= nq) return;
+        const double y[3] = {pts[3 * q], pts[3 * q + 1], pts[3 * q + 2]};
+        const double2 f = field_near(y, tree, ec, ev, sigma, mu, k, rc2);
+        if ((tid & 63) == 0) part[npiece * nq + q] = f;
+        return;
     }
-    if (l == 0 && q < nq) {
-        double dx = x[0] - sx, dy = x[1] - sy, dz = x[2] - sz;
-        double r = sqrt(dx * dx + dy * dy + dz * dz), s, co;
+    const unsigned bid = blockIdx.x - nnear;
+    const unsigned pc = bid / ngroup, grp = bid - pc * ngroup;  // pieces outermost: neighbours share one
+    eikr_stage(tab, tid);
+    double x[R][3];
+    double2 acc[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const int64_t q = (int64_t)grp * R + u, qc = q < nq ? q : nq - 1;
+        for (int d = 0; d < 3; ++d) x[u][d] = pts[3 * qc + d];
+        acc[u] = cmk(0, 0);
+    }
+    __syncthreads();
+    const double inv4pi = 1.0 / (4.0 * FMM_PI);
+    // a table phase needs r kk < 2^51; a point so far away that k r itself is not known to 1 % keeps
+    // the phase of that distance
+    const double rmax = 1.0e15 / kk.x;
+    const int64_t lo = pc * piece, hi = lo + piece < nt ? lo + piece : nt;
+    for (int64_t j = lo + tid; j < hi; j += 256) {
+        const double4 c = ec[j], nv = en[j];
+        const double2 sg = sigma[j], um = mu[j];
+        const double wgt = c.w * inv4pi;
+        const double2 q = cscale(sg, wgt), w = cscale(um, wgt);
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const double d2 = dist2_exact(x[u][0], x[u][1], x[u][2], c.x, c.y, c.z);
+            const double dx = c.x - x[u][0], dy = c.y - x[u][1], dz = c.z - x[u][2];
+            const double ir = d2 < rc2 ? 0.0 : rsq_nr(d2), r = d2 * ir, kr = k * r;
+            double s, co;
+            eikr(fmin(r, rmax), kk, tab, co, s);
+            const double2 G = cmk(co * ir, s * ir);
+            const double a1 = (dx * nv.x + dy * nv.y + dz * nv.z) * ir * ir;  // (y-x).n / r^2
+            // G (q + (ikr - 1) a1 w)
+            acc[u] = cfma(G, cmk(fma(-a1, fma(kr, w.y, w.x), q.x), fma(-a1, fma(-kr, w.x, w.y), q.y)), acc[u]);
+        }
+    }
+    // sums over the wavefront: R/2, R/4, ... points exchanged per step until a lane holds one, then
+    // plain folding; the four wavefronts' sums through LDS
+    const int lane = tid & 63;
+    int who = 0;
+#pragma unroll
+    for (int d = 32, h = R / 2; d > 0; d >>= 1, h >>= 1) {
+        if (h > 0) {
+            const bool up = (lane & d) != 0;
+#pragma unroll
+            for (int u = 0; u < h; ++u) {
+                const double2 give = up ? acc[u] : acc[u + h], keep = up ? acc[u + h] : acc[u];
+                acc[u] = cmk(keep.x + __shfl_xor(give.x, d), keep.y + __shfl_xor(give.y, d));
+            }
+            who += up ? h : 0;
+        } else {
+            acc[0] = cmk(acc[0].x + __shfl_xor(acc[0].x, d), acc[0].y + __shfl_xor(acc[0].y, d));
+        }
+    }
+    if ((lane & (64 / R - 1)) == 0) red[(tid >> 6) * R + who] = acc[0];
+    __syncthreads();
+    const int64_t q = (int64_t)grp * R + tid;
+    if (tid < R && q < nq)
+        part[pc * nq + q] = cadd(cadd(red[tid], red[R + tid]), cadd(red[2 * R + tid], red[3 * R + tid]));
+}
+
+// one wavefront per point: the pieces' sums and the incident field
+__global__ void __launch_bounds__(256) k_field_sum(int64_t nq, int npiece, const double *pts, double k, double sx,
+                                                   double sy, double sz, double2 amp, const double2 *part,
+                                                   double2 *out) {
+    const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (q >= nq) return;
+    double2 a = cmk(0, 0);
+    for (int g = lane; g <= npiece; g += 64) a = cadd(a, part[g * nq + q]);  // the last: the near pairs
+    for (int d = 32; d > 0; d >>= 1) a = cmk(a.x + __shfl_xor(a.x, d), a.y + __shfl_xor(a.y, d));
+    if (lane == 0) {
+        const double dx = pts[3 * q] - sx, dy = pts[3 * q + 1] - sy, dz = pts[3 * q + 2] - sz;
+        const double r = sqrt(dx * dx + dy * dy + dz * dz), inv4pi = 1.0 / (4.0 * FMM_PI);
+        double s, co;
         sincos(k * r, &s, &co);
-        out[q] = cadd(red[tid], cmul(amp, cmk(co / r * inv4pi, s / r * inv4pi)));
+        out[q] = cadd(a, cmul(amp, cmk(co / r * inv4pi, s / r * inv4pi)));
     }
 }
 
@@ -1914,6 +1974,44 @@ void launch_p2p_n(int nleaf, int nsplit, const int32_t *leaf_start, const int32_
                                                       en, sigma, mu, k, eikr_scale(k), rc2, near_start, near_col, nL,
                                                       nM, nLp, nMp, y, yn);
     LAUNCH_OK();
+}
+
+// Points per workgroup and pieces of the elements for nq points: enough pieces for FIELD_WGS
+// workgroups, none below 256 elements, and no more partial sums than FIELD_PART (the near pairs'
+// among them).
+static void field_shape(int64_t nt, int64_t nq, int &R, int64_t &piece, int &npiece) {
+    R = nq >= 5 ? 8 : nq >= 3 ? 4 : (int)nq;
+    const int64_t groups = (nq + R - 1) / R;
+    int64_t np = std::min<int64_t>((nt + 255) / 256, (FIELD_WGS + groups - 1) / groups);
+    np = std::max<int64_t>(1, std::min(np, FIELD_PART / nq - 1));
+    piece = (((nt + np - 1) / np + 255) / 256) * 256;
+    npiece = (int)((nt + piece - 1) / piece);
+}
+
+// part: FIELD_PART partial sums
+void launch_field(int64_t nt, int64_t nr, const FieldTree &tree, const double *pts, const double4 *ec,
+                  const double4 *en, const double *ev, const double2 *sigma, const double2 *mu, double k, double rc2,
+                  const double *rs, double2 amp, double2 *part, double2 *out, hipStream_t st) {
+    for (int64_t q0 = 0; q0 < nr; q0 += FIELD_PART / 2) {
+        const int64_t nq = std::min<int64_t>(nr - q0, FIELD_PART / 2);
+        int R, np;
+        int64_t piece;
+        field_shape(nt, nq, R, piece, np);
+        const unsigned ng = (unsigned)ceil_div(nq, R);
+#define FIELD_CALL(RR)                                                                                                \
+    k_field<RR><<<ceil_div(nq, 4) + ng * np, 256, 0, st>>>(nt, nq, piece, np, ng, tree, pts + 3 * q0, ec, en, ev, sigma, \
+                                                           mu, k, eikr_scale(k), rc2, part)
+        switch (R) {
+        case 1: FIELD_CALL(1); break;
+        case 2: FIELD_CALL(2); break;
+        case 4: FIELD_CALL(4); break;
+        default: FIELD_CALL(8);
+        }
+#undef FIELD_CALL
+        LAUNCH_OK();
+        k_field_sum<<<ceil_div(nq, 4), 256, 0, st>>>(nq, np, pts + 3 * q0, k, rs[0], rs[1], rs[2], amp, part, out + q0);
+        LAUNCH_OK();
+    }
 }
 
 size_t p2m_stage_bytes(int nr, int p) {

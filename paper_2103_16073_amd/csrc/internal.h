@@ -153,8 +153,17 @@ struct TransBatch {
 // runs of the back-rotation output never cross a multiple of this many (real) jobs, so that a
 // run lies in one 32-lane half tile (the fused kernel's block) for 1, 2 or 4 right-hand sides
 constexpr int SEG_ALIGN = 8;
-// receivers per workgroup of the tiled field kernel (k_field_tile)
-constexpr int FIELD_FQ = 8;
+// field at points: workgroups wanted before the elements are left in one piece, and the most partial
+// sums a call writes (2 MiB)
+constexpr int64_t FIELD_WGS = 8192, FIELD_PART = (int64_t)1 << 17;
+// the octree's leaves, for the elements near a point: sorted Morton codes, ranges of elements, the
+// cube's corner and cells per metre, and how many cells r_c may reach
+struct FieldTree {
+    const uint64_t *code;
+    const int32_t *leaf_start;
+    int nleaf, depth, reach;
+    double lo[3], scale;
+};
 // one translation job before tiling
 struct JobH {
     int32_t src, tgt;
