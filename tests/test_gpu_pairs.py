@@ -51,3 +51,33 @@ def test_near_field_leaf_sizes_vs_oracle(F, h, opt, form):
             assert np.linalg.norm(y[q] - ref[q]) < 1e-12 * s, (nr, q, np.linalg.norm(y[q] - ref[q]) / s)
             assert np.linalg.norm(f[q] - ref[q]) < 2e-6 * s, (nr, q, np.linalg.norm(f[q] - ref[q]) / s)
     ctx.close()
+
+
+# one to nine points (every points-per-workgroup shape and its remainders), several hundred, and more
+# than one launch's worth; the near integrals reaching one cell, or (r_c above the leaf side) several
+@pytest.mark.parametrize("h,opt", [(0.34, {}), (0.34, dict(rc=1.7)), (0.1, {})])
+def test_field_point_counts_vs_oracle(F, h, opt):
+    room = synth.shoebox(3.0, 2.5, 2.0, h)
+    k = synth.wavenumber(250.0)
+    ctx = _ctx(F, room, k, **opt)
+    rs, rec = synth.source_and_receivers(room, 700)
+    ctx.fmmbem_set_sources(rs)
+    V, T = room.vertices, room.triangles
+    c = V[T].mean(axis=1)
+    nrm = np.cross(V[T[:, 1]] - V[T[:, 0]], V[T[:, 2]] - V[T[:, 0]])
+    nrm /= np.linalg.norm(nrm, axis=1)[:, None]
+    sel = np.linspace(0, room.n - 1, 40).astype(int)
+    # points in the room, just inside and just outside the walls, and far outside the octree's cube
+    pts = np.vstack([rec, c[sel] - 0.03 * nrm[sel], c[sel] + 0.03 * nrm[sel], [[30.0, -4.0, 2.0], [3.5, 2.6, 2.2]]])
+    pts = pts[np.random.default_rng(4).permutation(len(pts))]
+    x = synth.complex_normal(room.n, 77)
+    rc = opt.get("rc") or oracle_rc(ctx, room)
+    ref = bem.direct_receivers(V, T, k, room.beta, rs[0], rc, x, pts)
+    for nr in (1, 2, 3, 4, 5, 8, 9, len(pts)):
+        psi = ctx.fmmbem_eval_field(0, pts[:nr], x)
+        assert np.max(np.abs(psi - ref[:nr])) < 1e-10 * np.linalg.norm(ref) / np.sqrt(len(ref)), nr
+    if h == 0.34:
+        many = np.tile(pts, (66000 // len(pts) + 1, 1))
+        psi = ctx.fmmbem_eval_field(0, many, x)
+        assert np.max(np.abs(psi - np.tile(ref, len(many) // len(pts)))) < 1e-10 * np.linalg.norm(ref) / np.sqrt(len(ref))
+    ctx.close()
