@@ -442,7 +442,8 @@ static void make_batch(fmmbem_ctx *c, const std::string &name, std::vector<JobH>
         HIP_OK(hipMemsetAsync(b.H + nt_, 0, sizeof(double) * TABLE_PAD, st));
         HIP_OK(hipMemsetAsync(b.HT + nt_, 0, sizeof(double) * TABLE_PAD, st));
     }
-    build_rot_tables(betas, b.P, (double *)c->buf.find("delta"), b.H, b.HT, c->scratch, st);
+    build_rot_tables(betas, b.P, (double *)c->buf.find("delta"), (double *)c->buf.find("deltaT"), b.H, b.HT, c->scratch,
+                     st);
 }
 
 // the batch's tables in the fused tiles' fragment order (coax: its ncoax coaxial tables)

@@ -47,81 +47,160 @@ int64_t coax_ws_size(int p) {
 }
 
 // kernel 1: one workgroup per table.  seq, sectorial, zonal and diagonal coefficients.
+// A serial chain of recursions (in m, n and along the diagonals), so it is bound by the latency of a
+// step: the rows that a step reads are kept in LDS (two rows, each step overwriting the older one)
+// and only written to the workspace; j_n and y_n run on different wavefronts; and the diagonals, whose entry (M, n) needs (M - 1, n) and
+// (M, n - 1), run one thread per M, all entries with the same M + n at once.  The
+// tables of one wavenumber (79 tables, p up to 63): 2.5 ms with the rows in global memory and the
+// diagonals on one thread, 0.29 ms now, bitwise the same tables.
+constexpr int COAX_STRIP = 128;  // diagonal rows in flight
+size_t coax_lds_bytes(int p) {
+    const size_t rows = (size_t)2 * (2 * p + 4) * sizeof(double2);
+    const size_t diag = ((size_t)3 * (p + 4) + 2 * 3 * (COAX_STRIP + 1)) * sizeof(double2);
+    return std::max(rows, diag);
+}
 __global__ void __launch_bounds__(256) k_coax_prepare(const CoaxJob *jobs, double2 *ws_base, int64_t ws_stride) {
     const CoaxJob J = jobs[blockIdx.x];
-    const int p = J.p;
+    const int p = J.p, tid = threadIdx.x;
     CoaxWS ws{p, 2 * p + 4, ws_base + ws_stride * blockIdx.x};
     const int N = 2 * p;  // orders 0..2p-1
-    __shared__ double jb[2 * 1024 + 8];
-    __shared__ double yb[2 * 1024 + 8];
-    if (threadIdx.x == 0) {
-        sph_jn_seq(J.ktau, N, jb);
-        if (J.kind == 0) sph_yn_seq(J.ktau, N, yb);
-    }
+    extern __shared__ double2 coax_sm[];
+    double2 *ra = coax_sm, *rb = coax_sm + 2 * p + 4;
+    double *jb = (double *)rb, *yb = jb + N + 2;
+    if (tid == 0) sph_jn_seq(J.ktau, N, jb);
+    else if (tid == 64 && J.kind == 0) sph_yn_seq(J.ktau, N, yb);
     __syncthreads();
     // step 1, Eq. (shft1): (E|F)^0_{n'0} = (-1)^n' sqrt(2n'+1) f_n'(k tau)
-    for (int nn = threadIdx.x; nn <= 2 * p - 2; nn += blockDim.x) {
+    for (int nn = tid; nn <= 2 * p - 2; nn += blockDim.x) {
         double sg = (nn & 1) ? -1.0 : 1.0;
         double r = sg * sqrt(2.0 * nn + 1.0);
-        ws.S(0, nn) = cmk(r * jb[nn], J.kind == 0 ? r * yb[nn] : 0.0);
+        ra[nn] = cmk(r * jb[nn], J.kind == 0 ? r * yb[nn] : 0.0);
+        ws.S(0, nn) = ra[nn];
     }
     __syncthreads();
     // step 2, Eq. (shft2): sectorial, propagation in m
     for (int m = 0; m <= p - 2; ++m) {
         double bden = coef_b(m + 1, -m - 1);
-        for (int nn = m + 1 + threadIdx.x; nn <= 2 * p - 3 - m; nn += blockDim.x) {
-            double2 v = csub(cscale(ws.S(m, nn - 1), coef_b(nn, -m - 1)), cscale(ws.S(m, nn + 1), coef_b(nn + 1, m)));
-            ws.S(m + 1, nn) = cscale(v, 1.0 / bden);
+        for (int nn = m + 1 + tid; nn <= 2 * p - 3 - m; nn += blockDim.x) {
+            double2 v = csub(cscale(ra[nn - 1], coef_b(nn, -m - 1)), cscale(ra[nn + 1], coef_b(nn + 1, m)));
+            rb[nn] = cscale(v, 1.0 / bden);
+            ws.S(m + 1, nn) = rb[nn];
         }
+        double2 *t = ra;
+        ra = rb;
+        rb = t;
         __syncthreads();
     }
     if (J.method == 0) return;
-    // step 3.1, Eq. (shft7): zonal block by propagation in n
-    for (int nn = threadIdx.x; nn <= 2 * p - 2; nn += blockDim.x) ws.Z(nn, 0) = ws.S(0, nn);
+    // step 3.1, Eq. (shft7): zonal block by propagation in n; column n - 1 is overwritten by n + 1
+    for (int nn = tid; nn <= 2 * p - 2; nn += blockDim.x) {
+        ra[nn] = ws.S(0, nn);
+        ws.Z(nn, 0) = ra[nn];
+    }
     __syncthreads();
     for (int n = 0; n <= p - 2; ++n) {
         double an = coef_a(n, 0), an1 = (n >= 1) ? coef_a(n - 1, 0) : 0.0;
-        for (int nn = n + 1 + threadIdx.x; nn <= 2 * p - n - 3; nn += blockDim.x) {
-            double2 v = cscale(ws.Z(nn + 1, n), -coef_a(nn, 0));
-            v = cadd(v, cscale(ws.Z(nn - 1, n), coef_a(nn - 1, 0)));
-            if (n >= 1) v = cadd(v, cscale(ws.Z(nn, n - 1), an1));
-            ws.Z(nn, n + 1) = cscale(v, 1.0 / an);
+        for (int nn = n + 1 + tid; nn <= 2 * p - n - 3; nn += blockDim.x) {
+            double2 v = cscale(ra[nn + 1], -coef_a(nn, 0));
+            v = cadd(v, cscale(ra[nn - 1], coef_a(nn - 1, 0)));
+            if (n >= 1) v = cadd(v, cscale(rb[nn], an1));
+            rb[nn] = cscale(v, 1.0 / an);
+            ws.Z(nn, n + 1) = rb[nn];
         }
+        double2 *t = ra;
+        ra = rb;
+        rb = t;
         __syncthreads();
     }
-    // step 3.2, Eq. (shft8): diagonals by propagation in m (sequential chain)
-    if (threadIdx.x == 0) {
-        for (int n = 0; n <= p - 1; ++n) {
-            ws.D(0, 0, n) = ws.Z(n, n);
-            ws.D(1, 0, n) = ws.Z(n + 1, n);
-            ws.D(2, 0, n) = ws.Z(n + 2, n);
+    // step 3.2, Eq. (shft8): diagonals by propagation in m.  Strips of COAX_STRIP rows M, one thread
+    // each; base holds the row before the strip, pub (two buffers) every row's newest entries
+    // D0(M, n+1), D1(M, n), D2(M, n) for the thread of row M + 1 in the next step.
+    double2 *base = coax_sm, *pub = coax_sm + 3 * (p + 4);
+    const int PW = 3 * (COAX_STRIP + 1);
+    for (int n = tid; n <= p - 1; n += blockDim.x) {
+        base[n] = ws.Z(n, n);
+        base[(p + 4) + n] = ws.Z(n + 1, n);
+        base[2 * (p + 4) + n] = ws.Z(n + 2, n);
+        for (int q = 0; q < 3; ++q) ws.D(q, 0, n) = base[q * (p + 4) + n];
+    }
+    __syncthreads();
+    for (int m0 = 0; m0 <= p - 3; m0 += COAX_STRIP) {
+        const int rows = min(COAX_STRIP, p - 2 - m0), m = m0 + tid, M = m + 1;
+        const bool mine = tid < rows;
+        // D0(m, n), D1(m, n - 1), D2(m, n - 1) of the row above; D0(M, n), D1(M, n - 1), D2(M, n - 1) of this one
+        double2 u0 = cmk(0, 0), u1 = u0, u2 = u0, o0 = u0, o1 = u0, o2 = u0, s1 = u0, s2 = u0;
+        if (mine) {
+            o0 = ws.S(M, M);
+            s1 = ws.S(M, M + 1);
+            s2 = ws.S(M, M + 2);
+            ws.D(0, M, M) = o0;
+            ws.D(1, M, M) = s1;
+            ws.D(2, M, M) = s2;
         }
-        for (int m = 0; m <= p - 3; ++m) {
-            const int M = m + 1;
-            ws.D(0, M, M) = ws.S(M, M);
-            ws.D(1, M, M) = ws.S(M, M + 1);
-            ws.D(2, M, M) = ws.S(M, M + 2);
-            for (int n = m + 1; n <= p - 2; ++n) {
-                const double bnp1 = coef_b(n + 1, -m - 1);
-                // (E|F)^{m+1}_{n+1,n+1}
-                double2 v = cscale(ws.D(0, m, n), bnp1);
-                v = csub(v, cscale(ws.D(2, m, n), coef_b(n + 2, m)));
-                if (n - 1 >= M) v = cadd(v, cscale(ws.D(2, M, n - 1), coef_b(n, m)));
-                ws.D(0, M, n + 1) = cscale(v, 1.0 / bnp1);
-                if (n >= m + 2) {
-                    // (E|F)^{m+1}_{n+1,n}
-                    double2 w = cscale(ws.D(1, m, n), coef_b(n + 1, m));
-                    w = cadd(w, cscale(ws.D(1, m, n - 1), coef_b(n, -m - 1)));
-                    w = csub(w, cscale(ws.D(1, M, n - 1), coef_b(n, m)));
-                    ws.D(1, M, n) = cscale(w, 1.0 / bnp1);
-                    // (E|F)^{m+1}_{n+2,n}  (coefficient of (E|F)^m_{n+1,n-1} read as b_n^{-m-1})
-                    double2 u = cscale(ws.D(0, M, n), coef_b(n + 1, m));
-                    u = csub(u, cscale(ws.D(0, m, n + 1), coef_b(n + 1, m)));
-                    u = cadd(u, cscale(ws.D(2, m, n - 1), coef_b(n, -m - 1)));
-                    ws.D(2, M, n) = cscale(u, 1.0 / coef_b(n + 2, -m - 1));
+        // step t: row M takes n = t - tid, from n = M on (row m has taken n one step before)
+        const int t1 = p - 2 + rows - 1;
+        for (int t = m0 + 1; t <= t1; ++t) {
+            const int n = t - tid, cur = t & 1;
+            if (mine && n >= m && n <= p - 2) {
+                // the row above at n: D0(m, n + 1), D1(m, n), D2(m, n)
+                double2 a0, a1, a2;
+                if (tid == 0) {
+                    a0 = base[n + 1];
+                    a1 = base[(p + 4) + n];
+                    a2 = base[2 * (p + 4) + n];
+                    if (n == M) {
+                        u0 = base[n];
+                        u1 = base[(p + 4) + n - 1];
+                        u2 = base[2 * (p + 4) + n - 1];
+                    }
+                } else {
+                    const double2 *pb = pub + (1 - cur) * PW + 3 * (tid - 1);
+                    a0 = pb[0];
+                    a1 = pb[1];
+                    a2 = pb[2];
                 }
+                if (n >= M) {
+                    const double bnp1 = coef_b(n + 1, -m - 1);
+                    // (E|F)^{m+1}_{n+1,n+1}
+                    double2 v = cscale(u0, bnp1);
+                    v = csub(v, cscale(a2, coef_b(n + 2, m)));
+                    if (n - 1 >= M) v = cadd(v, cscale(o2, coef_b(n, m)));
+                    const double2 d0 = cscale(v, 1.0 / bnp1);
+                    double2 d1 = s1, d2 = s2;
+                    if (n >= m + 2) {
+                        // (E|F)^{m+1}_{n+1,n}
+                        double2 w = cscale(a1, coef_b(n + 1, m));
+                        w = cadd(w, cscale(u1, coef_b(n, -m - 1)));
+                        w = csub(w, cscale(o1, coef_b(n, m)));
+                        d1 = cscale(w, 1.0 / bnp1);
+                        // (E|F)^{m+1}_{n+2,n}  (coefficient of (E|F)^m_{n+1,n-1} read as b_n^{-m-1})
+                        double2 z = cscale(o0, coef_b(n + 1, m));
+                        z = csub(z, cscale(a0, coef_b(n + 1, m)));
+                        z = cadd(z, cscale(u2, coef_b(n, -m - 1)));
+                        d2 = cscale(z, 1.0 / coef_b(n + 2, -m - 1));
+                        ws.D(1, M, n) = d1;
+                        ws.D(2, M, n) = d2;
+                    }
+                    ws.D(0, M, n + 1) = d0;
+                    o0 = d0;
+                    o1 = d1;
+                    o2 = d2;
+                    double2 *pb = pub + cur * PW + 3 * tid;
+                    pb[0] = d0;
+                    pb[1] = d1;
+                    pb[2] = d2;
+                }
+                u0 = a0;
+                u1 = a1;
+                u2 = a2;
             }
+            __syncthreads();
         }
+        // the strip's last row is the next one's base
+        const int Ml = m0 + rows;
+        for (int n = Ml + tid; n <= p - 1; n += blockDim.x)
+            for (int q = 0; q < 3; ++q) base[q * (p + 4) + n] = ws.D(q, Ml, n);
+        __syncthreads();
     }
 }
 
@@ -235,7 +314,7 @@ void build_coax_tables(const std::vector<CoaxJob> &jobs, DeviceBuffers &scratch,
     for (size_t s = 0; s < jobs.size(); s += per) {
         int cnt = (int)std::min<int64_t>(per, jobs.size() - s);
         double2 *ws = (double2 *)scratch.get("coax_ws", sizeof(double2) * wsz * cnt);
-        k_coax_prepare<<<cnt, 256, 0, st>>>(djobs + s, ws, wsz);
+        k_coax_prepare<<<cnt, 256, coax_lds_bytes(pmax), st>>>(djobs + s, ws, wsz);
         LAUNCH_OK();
         k_coax_fill<<<dim3(pmax, cnt), 256, 0, st>>>(djobs + s, ws, wsz);
         LAUNCH_OK();
@@ -284,48 +363,60 @@ __global__ void k_delta(int p, double *D, double *DT) {
 
 // Rotation matrices for polar angle b from the quarter-turn matrices (Fourier-series form of the
 // Wigner matrices): H_n(b)[m'][m] = sum_k Delta_{m'k} Delta_{mk} cos(k b + (m'-m) pi/2), which is
-// the real matrix i^{m'-m} sum_k Delta_{m'k} Delta_{mk} e^{i k b}.  One thread per (b, n, m'),
-// writing row m' of H and column m' of H^T.
-__global__ void k_rot_tables(int nb, const double *betas, int P, const double *D, double *H, double *HT) {
-    int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t per = (int64_t)P * P;  // rows over all degrees < P
-    if (gid >= per * nb) return;
-    const int ib = (int)(gid / per);
-    const int64_t r = gid - (int64_t)ib * per;
-    int n = (int)floor(sqrt((double)r));
-    while ((int64_t)n * n > r) --n;
-    while ((int64_t)(n + 1) * (n + 1) <= r) ++n;
-    const int w = 2 * n + 1;
-    const int mpi = (int)(r - (int64_t)n * n);  // row index m' + n
+// the real matrix i^{m'-m} sum_k Delta_{m'k} Delta_{mk} e^{i k b}, and its transpose.
+// For m' - m even the sum takes +-cos(k b), for odd +-sin(k b), so a degree is a product
+// Delta diag(cos or sin) Delta^T: a workgroup takes 16 rows m' and 64 columns m of one (b, n), a
+// wavefront 4 rows, whose entries are the same for all lanes (scalar loads), and a lane one column
+// (Delta^T: consecutive lanes read consecutive values); cos and sin come from LDS.  18 instructions
+// for 4 products.  Three levels' tables (p up to 63, 49 angles): 8.6 ms with one thread per row (its
+// whole matrix product serial, strided reads), 0.19 ms.
+__global__ void __launch_bounds__(256) k_rot_tables(int nct, const double *__restrict__ betas, int P,
+                                                    const double *__restrict__ D, const double *__restrict__ DT,
+                                                    double *__restrict__ H, double *__restrict__ HT) {
+    extern __shared__ double2 rot_cs[];
+    const int n = blockIdx.y, w = 2 * n + 1, ib = blockIdx.z / nct, c0 = (blockIdx.z - ib * nct) * 64;
+    if ((int)blockIdx.x * 16 >= w || c0 >= w) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int row0 = blockIdx.x * 16 + 4 * __builtin_amdgcn_readfirstlane(tid >> 6), mi = c0 + lane;
     const double b = betas[ib];
-    const double *Dn = D + rot_block_off(n);
-    double *Hn = H + (int64_t)ib * rot_table_size(P) + rot_block_off(n);
-    double *HTn = HT + (int64_t)ib * rot_table_size(P) + rot_block_off(n);
-    double sb, cb, s0, c0;
-    sincos(b, &sb, &cb);
-    sincos(-n * b, &s0, &c0);
-    for (int mi = 0; mi < w; ++mi) {
-        const int d = (((mpi - mi) % 4) + 4) % 4;
-        double s = 0.0, cs = c0, sn = s0;  // e^{i k b}, advanced by angle addition
-        for (int ki = 0; ki < w; ++ki) {
-            const double f = d == 0 ? cs : d == 1 ? -sn : d == 2 ? -cs : sn;
-            s = fma(Dn[(int64_t)mpi * w + ki] * Dn[(int64_t)mi * w + ki], f, s);
-            const double nc = cs * cb - sn * sb;
-            sn = cs * sb + sn * cb;
-            cs = nc;
-        }
-        Hn[(int64_t)mpi * w + mi] = s;
-        HTn[(int64_t)mi * w + mpi] = s;
+    for (int ki = tid; ki < w; ki += 256) sincos((ki - n) * b, &rot_cs[ki].y, &rot_cs[ki].x);
+    __syncthreads();
+    const double *Dn = D + rot_block_off(n), *Dc = DT + rot_block_off(n) + min(mi, w - 1);
+    const double *Dr[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) Dr[r] = Dn + (int64_t)min(row0 + r, w - 1) * w;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const bool odd = mi & 1;  // rows r = 0, 2 are even (row0 is a multiple of 4)
+#pragma unroll 4
+    for (int ki = 0; ki < w; ++ki) {
+        const double2 cs = rot_cs[ki];
+        const double dc = Dc[(int64_t)ki * w], fe = dc * (odd ? cs.y : cs.x), fo = dc * (odd ? cs.x : cs.y);
+        acc[0] = fma(Dr[0][ki], fe, acc[0]);
+        acc[1] = fma(Dr[1][ki], fo, acc[1]);
+        acc[2] = fma(Dr[2][ki], fe, acc[2]);
+        acc[3] = fma(Dr[3][ki], fo, acc[3]);
+    }
+    if (mi >= w) return;
+    const int64_t off = (int64_t)ib * rot_table_size(P) + rot_block_off(n);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int mpi = row0 + r;
+        if (mpi >= w) break;
+        const int d = (mpi - mi) & 3;  // cos, -sin, -cos, sin
+        const double v = d == 1 || d == 2 ? -acc[r] : acc[r];
+        H[off + (int64_t)mpi * w + mi] = v;
+        HT[off + (int64_t)mi * w + mpi] = v;
     }
 }
 
-void build_rot_tables(const std::vector<double> &betas, int P, const double *D, double *H, double *HT,
+void build_rot_tables(const std::vector<double> &betas, int P, const double *D, const double *DT, double *H, double *HT,
                       DeviceBuffers &scratch, hipStream_t st) {
     if (betas.empty()) return;
     double *db = (double *)scratch.get("rot_betas", sizeof(double) * betas.size());
     HIP_OK(hipMemcpyAsync(db, betas.data(), sizeof(double) * betas.size(), hipMemcpyHostToDevice, st));
-    const int64_t nthr = (int64_t)P * P * betas.size();
-    k_rot_tables<<<ceil_div(nthr, 128), 128, 0, st>>>((int)betas.size(), db, P, D, H, HT);
+    const int w = 2 * P - 1, nct = ceil_div(w, 64);
+    k_rot_tables<<<dim3(ceil_div(w, 16), P, nct * (unsigned)betas.size()), 256, sizeof(double2) * w, st>>>(nct, db, P, D,
+                                                                                                          DT, H, HT);
     LAUNCH_OK();
     HIP_OK(hipStreamSynchronize(st));  // betas buffer reuse
 }
