@@ -9,6 +9,13 @@
 // per distinct b, see k_rot_tables in tables.hip).  Jobs are sorted so that every tile of JT jobs
 // shares |t| and b: each table value read from memory then feeds the whole tile.
 //
+// The rotation commutes with c^m <-> c^{-m} (H_n[-m'][-m] = H_n[m'][m]: a rotation about y keeps the
+// expansion of a real field real), so the sums u_m = c^m + c^{-m} and the differences v_m = c^m -
+// c^{-m} of the orders m >= 0 rotate separately, by the (n+1)^2 matrices H[m'][m] +- H[m'][-m]:
+// half the multiplications of the (2n+1)^2 matrix.  The coaxial step has one block for +-m, so it
+// takes u and v as they are.  The matrix-core tiles (k_tm_*, k_tq_lds) work on u (in the places of
+// m >= 0) and v (in those of m < 0) from the forward rotation's output to the back rotation's input.
+//
 // Three launches per batch, each parallel over (tile, degree) or (tile, order):
 //   k_tr_rot_fwd  gathers the sources, applies the phase and H      -> W1 (P^2 per job)
 //   k_tr_coax     applies the coaxial block of each order m         -> W2
@@ -818,47 +825,52 @@ template <> struct TmOp<float> {
     static __device__ inline v4 mma(float a, float b, v4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
     static __device__ inline int row(int kq, int i) { return 4 * kq + i; }
 };
-constexpr int TM_KC = 8;    // K rows per LDS chunk (double-buffered) of the rotations
-constexpr int TM_LD = 130;  // LDS row stride (doubles) of the staged A and B chunks
+constexpr int TM_LD = 130;  // LDS row stride of the staged B chunks
 
 // Rotation of degree n for one tile of TMJ jobs (64 or 32: 2 TMJ columns, the four wavefronts owning
-// TMJ / 2 columns each, in NCB = TMJ / 32 blocks of 16), as a GEMM over K chunks staged in LDS
-// (double-buffered: the global loads of chunk c+1 are issued before the matrix-core work on chunk
-// c).  RBG row blocks of 16 rows per pass; a workgroup takes the passes pass, pass + npass, ... of
-// its degree.
-//   FWD:  Y = H X, X = e^{i m a} c_n of the sources, A[r][k] = H[r][k] = HT[k][r]; rows -> W1.
-//   !FWD: Y = H^T X, X = W2 rows, A[r][k] = H[k][r]; the pass's outputs go through LDS, are
-//         phased (e^{-i m a}), summed over the runs of one target and stored job-major in W1.
-template <class R, bool FWD, int RBG, int TMJ>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) k_tm_rot(TransArgsT<R> a, int npass) {
+// TMJ / 2 columns each, in NCB = TMJ / 32 blocks of 16), as two GEMMs (sums u, differences v; n + 1
+// rows m' >= 0 and K = n + 1 values m >= 0 each) over K chunks staged in LDS (double-buffered: the
+// global loads of chunk c+1 are issued before the matrix-core work on chunk c).  RBG row blocks of 16
+// rows of both per pass; a workgroup takes the passes pass, pass + npass, ... of its degree.
+//   FWD:  u' = Hs u, v' = Ha v, u_m, v_m = x_m +- x_{-m}, x = e^{i m a} c_n of the sources, Hs, Ha =
+//         H[m'][m] +- H[m'][-m] (row 0 of Hs halved: u'_0 = c'^0; u_0 = x_0); rows -> W1.
+//   !FWD: the same with H^T, halved, on the W2 rows, so that the outputs c^{+-m'} are u +- v; they go
+//         through LDS, are phased (e^{-i m a}), summed over the runs of one target and stored
+//         job-major in W1.
+// Half the matrix instructions of the (2n+1)^2 product; bound by the work rows' memory traffic and
+// staging all the same: levels 2-5 of the 1M L-room, ms per product against the full matrices,
+// FP64 forward 1.30 -> 1.15, back 1.60 -> 1.58; FP32, four vectors at 2 kHz, 1.32 -> 1.03 and 1.65 -> 1.39.
+// K chunks of 4 (FP64; 22 KB of LDS) or 8 rows (FP32, and 32-job tiles).  Held to four wavefronts per
+// SIMD the FP64 kernels spill 12-23 registers and lose 25-40 %, so three are allowed.
+template <class R, bool FWD, int RBG, int TMJ, int KC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 4))) k_tm_rot(TransArgsT<R> a, int npass) {
     using C = typename Cx<R>::T;
     using Op = TmOp<R>;
     using v4 = typename Op::v4;
     constexpr int RG = 16 * RBG;            // rows per pass
     constexpr int NCOL = 2 * TMJ;           // real columns of a tile
     constexpr int NCB = TMJ / 32;           // 16-column blocks per wavefront
-    // K chunks of 8 and passes of 64 rows: 33 KB of LDS, four workgroups per CU (measured at levels
-    // 2-5 of the 1M L-room against chunks of 16 and passes of 128 / 64 rows: back rotation 1.51 ->
-    // 1.15 ms, forward rotation 1.90 -> 1.66 ms per product).  The back rotation's outputs leave
-    // through the same LDS block 32 rows at a time (64-row passes instead of 32: FP64 product
-    // 10.97 -> 10.88 ms, mixed 9.00 -> 8.86 ms).
-    constexpr int KC = TM_KC;
-    constexpr int EQ = RBG < 2 ? RBG : 2;  // back: row blocks per epilogue step (32 rows through LDS)
-    constexpr int LDSN = FWD ? 4 * KC * TM_LD : (4 * KC > 16 * EQ ? 4 * KC : 16 * EQ) * TM_LD;
-    static_assert(RG <= 128 && RBG % EQ == 0, "pass too large for the LDS block");
+    constexpr int LA = RG + 2;              // LDS row stride of the staged A chunks
+    // two buffers of KC rows of B (u, v) and A (Hs, Ha); the back rotation's outputs leave through the
+    // same LDS, RG rows at a time
+    constexpr int LDSB = 4 * KC * TM_LD, LDSA = 4 * KC * LA, LDSE = FWD ? 0 : RG * TM_LD;
+    constexpr int LDSN = LDSB + LDSA > LDSE ? LDSB + LDSA : LDSE;
     static_assert(TMJ == 64 || TMJ == 32, "tiles of 64 or 32 jobs");
+    static_assert(KC % 4 == 0 && (KC * RG) % 64 == 0, "whole K steps and wavefronts per staged chunk");
     __shared__ R lds[LDSN];
     __shared__ int64_t soff[TMJ];
     __shared__ int32_t sdir[TMJ];
     __shared__ int segl[TMJ];
-    auto As = [&](int buf, int k, int r) -> R & { return lds[(buf * KC + k) * TM_LD + r]; };
-    auto Bs = [&](int buf, int k, int c) -> R & { return lds[((2 + buf) * KC + k) * TM_LD + c]; };
+    auto Bs = [&](int buf, int p, int k, int c) -> R & { return lds[((2 * buf + p) * KC + k) * TM_LD + c]; };
+    auto As = [&](int buf, int p, int k, int r) -> R & { return lds[LDSB + ((2 * buf + p) * KC + k) * LA + r]; };
     int tile, nq;
     xcd_block(tile, nq);
     const int n = nq / npass, pass = nq - n * npass;  // degree, and the pass's share of its row groups
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t J0 = (int64_t)tile * TMJ;
     const int P2 = a.P * a.P, phs = 2 * a.PH + 1, ps2 = a.psrc * a.psrc;
+    const int w = 2 * n + 1, K = n + 1, RB = (K + 15) / 16;
+    if (pass * RBG >= RB) return;  // the whole workgroup
     if (tid < TMJ) {
         const int64_t J = J0 + tid, Jc = J < a.njob ? J : a.njob - 1;
         soff[tid] = FWD ? src_row(a, Jc) * ps2 : 0;
@@ -866,96 +878,108 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
         segl[tid] = (!FWD && J < a.njob) ? a.jseg[J / a.nr] : 0;
     }
     __syncthreads();
-    const int w = 2 * n + 1, RB = (w + 15) / 16;
     const int tr = a.tile_rot[tile / a.nr];
-    const R *Mn = (FWD ? a.HT : a.H) + (int64_t)tr * rot_table_size(a.P) + rot_block_off(n);
+    // M[k][r] = H[r][k] (FWD, from HT) or H[k][r], centred at (m, m') = (0, 0)
+    const R *Mn = (FWD ? a.HT : a.H) + (int64_t)tr * rot_table_size(a.P) + rot_block_off(n) + n * w + n;
     const R *Xin = (const R *)a.W2;
-    const int colw = (NCOL / 4) * wv + (lane & 15), kq = lane >> 4;
-    const int nch = (w + KC - 1) / KC;
-    constexpr int NA = KC * RG / 256;   // A values staged per thread
-    constexpr int NB = KC * NCOL / 256;  // B values staged per thread
+    const int colw = (NCOL / 4) * wv + (lane & 15), kq = lane >> 4, nc = n * n + n;
+    const int nch = (K + KC - 1) / KC;
+    constexpr int NA = (KC * RG + 255) / 256;  // (Hs, Ha) pairs staged per thread
+    constexpr int NB = KC * TMJ / 256;         // (u, v) pairs of a job staged per thread
+    static_assert(NB >= 1, "chunk too small");
     for (int rb0 = pass * RBG; rb0 < RB; rb0 += npass * RBG) {
         const int r0 = rb0 * 16;
-        // the forward rotation keeps the loaded phases and source coefficients until the LDS store,
-        // so that the next chunk's loads stay in flight through the matrix-core work (1.66 -> 1.35 ms
-        // per product at levels 2-5 of the 1M L-room, against multiplying them as they arrive)
-        R ra[NA], rbv[FWD ? 1 : NB];
-        C rph[FWD ? NB / 2 : 1], rsr[FWD ? NB / 2 : 1];
+        // the loaded values are kept until the LDS store, so that the next chunk's loads stay in
+        // flight through the matrix-core work
+        R ra[NA][2];
+        C rph[FWD ? NB : 1], rsr[NB][2];
         auto gload = [&](int kc) {
 #pragma unroll
             for (int i = 0; i < NA; ++i) {
                 const int e = tid + 256 * i, kk = e / RG, rr = e % RG, k = kc + kk, r = r0 + rr;
-                ra[i] = (k < w && r < w) ? Mn[(int64_t)k * w + r] : R(0);
+                const bool in = (KC * RG % 256 == 0 || e < KC * RG) && k < K && r < K;
+                ra[i][0] = in ? Mn[(int64_t)k * w + r] : R(0);
+                ra[i][1] = in ? Mn[-(int64_t)k * w + r] : R(0);
             }
-            if (FWD) {
 #pragma unroll
-                for (int i = 0; i < NB / 2; ++i) {
-                    const int e = tid + 256 * i, kk = e % KC, j = e / KC, k = kc + kk;  // a job's KC rows: one segment
-                    rph[i] = k < w ? a.ph[sdir[j] + k - n] : mkc<C>(0, 0);
-                    rsr[i] = k < w ? a.src[soff[j] + n * n + k] : mkc<C>(0, 0);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    const int e = tid + 256 * i, kk = e / NCOL, col = e % NCOL, k = kc + kk;
-                    rbv[i] = k < w ? Xin[((int64_t)tile * P2 + n * n + k) * NCOL + col] : R(0);
+            for (int i = 0; i < NB; ++i) {
+                const int e = tid + 256 * i;
+                if (FWD) {
+                    const int kk = e % KC, j = e / KC, k = kc + kk;  // a job's KC rows: two segments
+                    rph[i] = k < K ? a.ph[sdir[j] + k] : mkc<C>(0, 0);
+                    rsr[i][0] = k < K ? a.src[soff[j] + nc + k] : mkc<C>(0, 0);
+                    rsr[i][1] = k < K ? a.src[soff[j] + nc - k] : mkc<C>(0, 0);
+                } else {
+                    const int kk = e / TMJ, j = e % TMJ, k = kc + kk;
+                    const C *X = (const C *)Xin + ((int64_t)tile * P2 + nc) * TMJ + j;
+                    rsr[i][0] = k < K ? X[(int64_t)k * TMJ] : mkc<C>(0, 0);
+                    rsr[i][1] = k < K ? X[-(int64_t)k * TMJ] : mkc<C>(0, 0);
                 }
             }
         };
-        auto lstore = [&](int buf) {
+        auto lstore = [&](int buf, int kc) {
 #pragma unroll
             for (int i = 0; i < NA; ++i) {
-                const int e = tid + 256 * i;
-                As(buf, e / RG, e % RG) = ra[i];
+                const int e = tid + 256 * i, kk = e / RG, rr = e % RG;
+                if (KC * RG % 256 == 0 || e < KC * RG) {
+                    const R f = FWD && r0 + rr > 0 ? R(1) : R(0.5);
+                    As(buf, 0, kk, rr) = f * (ra[i][0] + ra[i][1]);
+                    As(buf, 1, kk, rr) = (FWD ? R(1) : R(0.5)) * (ra[i][0] - ra[i][1]);
+                }
             }
-            if (FWD) {
 #pragma unroll
-                for (int i = 0; i < NB / 2; ++i) {
-                    const int e = tid + 256 * i, kk = e % KC, j = e / KC;
-                    const C x = mulc(rph[i], rsr[i]);  // e^{i m a} c_n^m
-                    Bs(buf, kk, 2 * j) = x.x;
-                    Bs(buf, kk, 2 * j + 1) = x.y;
+            for (int i = 0; i < NB; ++i) {
+                const int e = tid + 256 * i, kk = FWD ? e % KC : e / TMJ, j = FWD ? e / KC : e % TMJ;
+                C u = rsr[i][0], v = rsr[i][1];
+                if (FWD) {
+                    const C x = mulc(rph[i], u), y = mulcc(v, rph[i]);  // e^{i m a} c^m, e^{-i m a} c^{-m}
+                    const bool zero = kc + kk == 0;
+                    u = zero ? x : addc(x, y);
+                    v = zero ? mkc<C>(0, 0) : mkc<C>(x.x - y.x, x.y - y.y);
                 }
-            } else {
-#pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    const int e = tid + 256 * i;
-                    Bs(buf, e / NCOL, e % NCOL) = rbv[i];
-                }
+                Bs(buf, 0, kk, 2 * j) = u.x;
+                Bs(buf, 0, kk, 2 * j + 1) = u.y;
+                Bs(buf, 1, kk, 2 * j) = v.x;
+                Bs(buf, 1, kk, 2 * j + 1) = v.y;
             }
         };
-        v4 acc[RBG][NCB];
+        v4 acc[2][RBG][NCB];
 #pragma unroll
-        for (int q = 0; q < RBG; ++q)
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) acc[q][cb] = v4{0, 0, 0, 0};
+            for (int q = 0; q < RBG; ++q)
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb) acc[p][q][cb] = v4{0, 0, 0, 0};
         gload(0);
         __syncthreads();  // the previous pass's readers of the LDS block are done
-        lstore(0);
+        lstore(0, 0);
         __syncthreads();
         for (int c = 0; c < nch; ++c) {
             const int buf = c & 1;
             if (c + 1 < nch) gload((c + 1) * KC);
-            const int kn = min(KC, w - c * KC);
+            const int kn = min(KC, K - c * KC);
             for (int ks = 0; ks < kn; ks += 4) {
-                R bv[NCB];
 #pragma unroll
-                for (int cb = 0; cb < NCB; ++cb) bv[cb] = Bs(buf, ks + kq, colw + 16 * cb);
+                for (int p = 0; p < 2; ++p) {
+                    R bv[NCB];
 #pragma unroll
-                for (int q = 0; q < RBG; ++q) {
-                    if (rb0 + q >= RB) break;
-                    const R av = As(buf, ks + kq, q * 16 + (lane & 15));
+                    for (int cb = 0; cb < NCB; ++cb) bv[cb] = Bs(buf, p, ks + kq, colw + 16 * cb);
 #pragma unroll
-                    for (int cb = 0; cb < NCB; ++cb) acc[q][cb] = Op::mma(av, bv[cb], acc[q][cb]);
+                    for (int q = 0; q < RBG; ++q) {
+                        if (rb0 + q >= RB) break;
+                        const R av = As(buf, p, ks + kq, q * 16 + (lane & 15));
+#pragma unroll
+                        for (int cb = 0; cb < NCB; ++cb) acc[p][q][cb] = Op::mma(av, bv[cb], acc[p][q][cb]);
+                    }
                 }
             }
             if (c + 1 < nch) {
-                lstore(buf ^ 1);
+                lstore(buf ^ 1, (c + 1) * KC);
                 __syncthreads();
             }
         }
         if (FWD) {
-            R *Wout = (R *)a.W1;
+            R *Wout = (R *)a.W1 + ((int64_t)tile * P2 + nc) * NCOL + colw;
 #pragma unroll
             for (int q = 0; q < RBG; ++q) {
                 if (rb0 + q >= RB) break;
@@ -964,27 +988,30 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const int r = (rb0 + q) * 16 + Op::row(kq, i);
-                        if (r < w) Wout[((int64_t)tile * P2 + n * n + r) * NCOL + colw + 16 * cb] = acc[q][cb][i];
+                        if (r < K) Wout[(int64_t)r * NCOL + 16 * cb] = acc[0][q][cb][i];
+                        if (r > 0 && r < K) Wout[-(int64_t)r * NCOL + 16 * cb] = acc[1][q][cb][i];
                     }
             }
         } else {
-            // the pass's output rows go through the LDS block EQ row blocks (ER rows x NCOL columns)
-            // at a time: phase, run sums and job-major stores (consecutive threads: consecutive rows
-            // of one job)
-            constexpr int ER = 16 * EQ, NE = ER * TMJ / 256;
+            // the pass's outputs c^{m} (sign 0) and c^{-m} (sign 1) go through the LDS block RG rows m at
+            // a time: phase, run sums and job-major stores (consecutive threads: consecutive rows of
+            // one job)
+            constexpr int NE = RG * TMJ / 256;
+            const int nrow = min(RG, K - r0);
 #pragma unroll
-            for (int q0 = 0; q0 < RBG; q0 += EQ) {
-                if (rb0 + q0 >= RB) break;
+            for (int sign = 0; sign < 2; ++sign) {
+                if (sign && K == 1) break;
                 __syncthreads();
 #pragma unroll
-                for (int q = 0; q < EQ; ++q)
+                for (int q = 0; q < RBG; ++q)
 #pragma unroll
                     for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            lds[(q * 16 + Op::row(kq, i)) * TM_LD + colw + 16 * cb] = acc[q0 + q][cb][i];
+                        for (int i = 0; i < 4; ++i) {
+                            const R u = acc[0][q][cb][i], v = acc[1][q][cb][i];
+                            lds[(q * 16 + Op::row(kq, i)) * TM_LD + colw + 16 * cb] = sign ? u - v : u + v;
+                        }
                 __syncthreads();
-                const int rs = r0 + 16 * q0, nrow = min(ER, w - rs);
                 // phase every (row, job) in place first, four phase loads in flight at a time, so
                 // that the run sums below read LDS only
                 constexpr int NG = NE < 4 ? NE : 4;
@@ -993,12 +1020,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
                     C phv[NG];
 #pragma unroll
                     for (int i = 0; i < NG; ++i) {
-                        const int e = tid + 256 * (i0 + i), j = e / ER, rr = e % ER;
-                        phv[i] = rr < nrow ? a.ph[sdir[j] + rs + rr - n] : mkc<C>(0, 0);
+                        const int e = tid + 256 * (i0 + i), j = e / RG, rr = e % RG;
+                        phv[i] = rr < nrow ? a.ph[sdir[j] + (sign ? -(r0 + rr) : r0 + rr)] : mkc<C>(0, 0);
                     }
 #pragma unroll
                     for (int i = 0; i < NG; ++i) {
-                        const int e = tid + 256 * (i0 + i), j = e / ER, rr = e % ER;
+                        const int e = tid + 256 * (i0 + i), j = e / RG, rr = e % RG;
                         R *x = &lds[rr * TM_LD + 2 * j];
                         const C v = mulcc(mkc<C>(x[0], x[1]), phv[i]);  // e^{-i m a}
                         x[0] = v.x;
@@ -1006,16 +1033,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
                     }
                 }
                 __syncthreads();
-                for (int e = tid; e < ER * TMJ; e += 256) {
-                    const int j = e / ER, rr = e % ER, r = rs + rr;
+                for (int e = tid; e < RG * TMJ; e += 256) {
+                    const int j = e / RG, rr = e % RG, m = r0 + rr;
                     const int len = segl[j];
-                    if (rr >= nrow || len == 0) continue;
+                    if (rr >= nrow || len == 0 || (sign && m == 0)) continue;
                     C v = mkc<C>(0, 0);
                     for (int t = 0; t < len; ++t) {
                         const int jj = j + t * a.nr;
                         v = addc(v, mkc<C>(lds[rr * TM_LD + 2 * jj], lds[rr * TM_LD + 2 * jj + 1]));
                     }
-                    a.W1[(J0 + j) * (int64_t)P2 + n * n + r] = v;
+                    a.W1[(J0 + j) * (int64_t)P2 + nc + (sign ? -m : m)] = v;
                 }
             }
         }
@@ -2185,12 +2212,13 @@ const char *trans_stage(const TransBatch &b, const TransTables<R> &tb, int stage
             const int np = ((rows + 15) / 16 + rbg - 1) / rbg;
             return (int64_t)ntile * nd >= 2048 ? 1 : np;
         };
+        constexpr int TM_KC = sizeof(R) == 8 ? 4 : 8;  // K rows per LDS chunk of the rotations
         int np;
         switch (stage) {
         case 0:
-            np = passes(2 * b.psrc - 1, 4, b.psrc);
-            if (b.JT == LANE_JT) k_tm_rot<R, true, 4, 64><<<dim3(ntile, b.psrc * np), 256, 0, st>>>(a, np);
-            else k_tm_rot<R, true, 4, 32><<<dim3(ntile, b.psrc * np), 256, 0, st>>>(a, np);
+            np = passes(b.psrc, 2, b.psrc);
+            if (b.JT == LANE_JT) k_tm_rot<R, true, 2, 64, TM_KC><<<dim3(ntile, b.psrc * np), 256, 0, st>>>(a, np);
+            else k_tm_rot<R, true, 2, 32, 8><<<dim3(ntile, b.psrc * np), 256, 0, st>>>(a, np);
             name = f32 ? "k_tm_rot_fwd_f32" : "k_tm_rot_fwd";
             break;
         case 1:
@@ -2201,9 +2229,9 @@ const char *trans_stage(const TransBatch &b, const TransTables<R> &tb, int stage
             name = f32 ? "k_tm_coax_f32" : "k_tm_coax";
             break;
         default:
-            np = passes(2 * b.ptgt - 1, 4, b.ptgt);
-            if (b.JT == LANE_JT) k_tm_rot<R, false, 4, 64><<<dim3(ntile, b.ptgt * np), 256, 0, st>>>(a, np);
-            else k_tm_rot<R, false, 4, 32><<<dim3(ntile, b.ptgt * np), 256, 0, st>>>(a, np);
+            np = passes(b.ptgt, 2, b.ptgt);
+            if (b.JT == LANE_JT) k_tm_rot<R, false, 2, 64, TM_KC><<<dim3(ntile, b.ptgt * np), 256, 0, st>>>(a, np);
+            else k_tm_rot<R, false, 2, 32, 8><<<dim3(ntile, b.ptgt * np), 256, 0, st>>>(a, np);
             name = f32 ? "k_tm_rot_back_f32" : "k_tm_rot_back";
         }
         LAUNCH_OK();
