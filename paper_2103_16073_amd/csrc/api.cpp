@@ -454,7 +454,9 @@ static void fused_tables(fmmbem_ctx *c, const std::string &name, TransBatch &b, 
     b.frHT = dget<double>(c->buf, name + "_frHT", nr);
     b.frC = dget<double>(c->buf, name + "_frC", nc);
     b.nfrc = std::max(1, ncoax);
-    build_fused_tables(b.P, b.PT, b.nbeta, b.H, b.HT, ncoax, coax, b.frH, b.frHT, b.frC, c->stream);
+    b.frPF = dget<double>(c->buf, name + "_frPF", (size_t)std::max(1, b.nbeta) * TQ_FR_ROT);
+    b.frPB = dget<double>(c->buf, name + "_frPB", (size_t)std::max(1, b.nbeta) * TQ_FR_ROT);
+    build_fused_tables(b.P, b.PT, b.nbeta, b.H, b.HT, ncoax, coax, b.frH, b.frHT, b.frPF, b.frPB, b.frC, c->stream);
 }
 
 // Batches of every level.  A level whose octree and truncation numbers (its own and the next
@@ -763,10 +765,10 @@ static void run_batch(fmmbem_ctx *c, int nrv, const TransBatch &b0, const typena
 }
 
 static TransTables<double> tables64(const TransBatch &b, const double2 *coax) {
-    return {coax, b.H, b.HT, b.frH, b.frHT, b.frC};
+    return {coax, b.H, b.HT, b.frH, b.frHT, b.frC, b.frPF, b.frPB};
 }
 static TransTables<float> tables32(const TransBatch &b, const float2 *coax) {
-    return {coax, b.H32, b.HT32, b.frH32, b.frHT32, b.frC32};
+    return {coax, b.H32, b.HT32, b.frH32, b.frHT32, b.frC32, b.frPF32, b.frPB32};
 }
 
 // every batch of the product with its source/target expansions and coaxial tables
@@ -938,6 +940,11 @@ static void ensure_mixed(fmmbem_ctx *c) {
                 convert(c, nr, (const double *)b.frH, b.frH32);
                 convert(c, nr, (const double *)b.frHT, b.frHT32);
                 convert(c, nc, (const double *)b.frC, b.frC32);
+                const int64_t np = (int64_t)std::max(1, b.nbeta) * TQ_FR_ROT;
+                b.frPF32 = dget<float>(c->buf, s + nm3[q] + "_frPF32", np);
+                b.frPB32 = dget<float>(c->buf, s + nm3[q] + "_frPB32", np);
+                convert(c, np, (const double *)b.frPF, b.frPF32);
+                convert(c, np, (const double *)b.frPB, b.frPB32);
             }
         }
     }

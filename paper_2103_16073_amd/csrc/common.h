@@ -122,4 +122,5 @@ template <class R> struct TransTables {
     const R *H, *HT;
     // the same tables in the fused tiles' fragment order (batches with p_src = p_tgt <= 16)
     const R *frH = nullptr, *frHT = nullptr, *frC = nullptr;
+    const R *frPF = nullptr, *frPB = nullptr;  // the rotations of sums and differences (TQ_FR_ROT)
 };

@@ -148,6 +148,9 @@ struct TransBatch {
     // lanes hold matrix-core fragments, zero past every block (built when p_src = p_tgt <= 16)
     double *frH = nullptr, *frHT = nullptr, *frC = nullptr;
     float *frH32 = nullptr, *frHT32 = nullptr, *frC32 = nullptr;
+    // the rotations of the sums and differences of orders +-m, forward and back
+    double *frPF = nullptr, *frPB = nullptr;
+    float *frPF32 = nullptr, *frPB32 = nullptr;
     int nfrc = 0;  // coaxial classes in frC
 };
 // runs of the back-rotation output never cross a multiple of this many (real) jobs, so that a
@@ -179,8 +182,10 @@ int trans_rcr_p();  // the truncation number of the register-resident fused tile
 // 8 K chunks x 2 row blocks x 64 lanes; coaxial 16 orders x 4 K chunks x (re, im) x 64 lanes
 constexpr int TF_FR_STEP = 2 * 8 * 2 * 64, TF_FR_ROT = 8 * TF_FR_STEP;
 constexpr int TF_FR_ORDER = 4 * 2 * 64, TF_FR_COAX = 16 * TF_FR_ORDER;
+// of the p = 16 tiles in LDS: 16 degrees x (sums, differences) x 4 K chunks x 64 lanes
+constexpr int TQ_FR_ROT = 16 * 2 * 4 * 64;
 void build_fused_tables(int P, int PT, int nbeta, const double *H, const double *HT, int ncoax, const double2 *coax,
-                        double *frH, double *frHT, double *frC, hipStream_t st);
+                        double *frH, double *frHT, double *frPF, double *frPB, double *frC, hipStream_t st);
 size_t trans_lds_bytes(int JT, int P, int whole);
 void trans_configure_lds(size_t lds_max);
 template <class R>

@@ -52,6 +52,7 @@ struct TransArgsT {
     C *W1, *W2;                 // work rows, P^2 per job
     const int8_t *jseg;         // lane batches: run length at the first job of a run, else 0
     const R *frH, *frHT, *frC;  // fused tiles: fragment-order tables (TF_FR_ROT, TF_FR_COAX per class)
+    const R *frPF, *frPB;       // p = 16 tiles in LDS: the rotations of sums and differences (TQ_FR_ROT per class)
 };
 
 constexpr int RJ = 4, RR = 4;
@@ -1805,7 +1806,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC, OC
 // tiles.  Measured at levels 6-7 of the 1M L-room: FP32 (mixed products) 2.77 ms with one
 // wavefront per workgroup and the partner moves of k_tq_rcr, 2.27 ms with lanes owning
 // coefficients in the first and last steps, 1.70 ms with two wavefronts, 1.71 -> 1.70 with four;
-// FP64 3.29 ms in registers (k_tq_rcr, two wavefronts per SIMD), 2.88 ms here with four.
+// FP64 3.29 ms in registers (k_tq_rcr, two wavefronts per SIMD), 2.85 ms here with four.  With the
+// rotations of sums and differences (310 matrix instructions per 8 jobs instead of 400) 2.50 ms; with
+// odd row strides, constant address offsets and spare-row writes instead of branches 2.32 ms.  FP32
+// with four vectors (2 kHz L-room): 6.50 -> 6.11 -> 5.71 ms, where matrix cores are busy 46 %, vector
+// instructions issue 45 % and the LDS works 54 % of the cycles.
 
 template <class R, int NW, int CB>
 __global__ void __launch_bounds__(64 * NW) k_tq_lds(TransArgsT<R> a) {
@@ -1816,12 +1821,15 @@ __global__ void __launch_bounds__(64 * NW) k_tq_lds(TransArgsT<R> a) {
     constexpr int P = TQ_P, P2 = P * P, NPH = 2 * P - 1, NJ = 8 * CB, JW = NJ / NW;
     static_assert(NW == 2 || NW == 4, "two or four wavefronts per workgroup");
     static_assert(CB == 1 || CB == 2, "one or two column blocks");
-    // coefficient (n, m) at row n^2 + n + m, column 2 job + part; rows P2 .. P2 + 3 (zeros) are read
-    // past the last degree.  Reads need no branch: rows past a degree or order meet zero columns of
-    // the table block (without the branches the reads of a step issue together: 2.58 -> 2.27 ms at
-    // levels 6-7 of the 1M L-room); writes past a block stay masked (writing them to spare rows
-    // nearly doubles the LDS stores and was slower)
-    __shared__ R Xs[CB][P2 + 4][16];
+    // coefficient (n, m) at row n^2 + n + m, column 2 job + part; rows LD apart, an odd number, so that
+    // lanes that own coefficients (the first and last steps) spread over the banks as well as lanes that
+    // own columns.  Reads need no branch: rows past a degree or order meet zero columns of the table
+    // block.  Writes past a block go to a spare row: a branch around each of them cost more (every lane
+    // group's last rows have one: about 40 % of the instructions).  The kernel is bound by
+    // instructions issued, so addresses are one value per lane (a base, or base + 2 x g LD for the
+    // rows of the coaxial step) plus constants.
+    constexpr int LD = 17, CS = P2 * LD + 64;  // a block's rows and its spare row (one place per lane)
+    __shared__ R Xs[CB * CS];
     __shared__ C phg[NJ][NPH];  // e^{i m a_j}
     __shared__ int64_t soff[NJ];
     __shared__ int segl[NJ];
@@ -1841,7 +1849,6 @@ __global__ void __launch_bounds__(64 * NW) k_tq_lds(TransArgsT<R> a) {
         soff[tid] = ((int64_t)a.jsrc[Jc] * nr + rv) * P2;  // sources: nr vectors per box
         segl[tid] = Jv < nj ? a.jseg[Jv] : 0;
     }
-    if (h < CB) Xs[h][P2 + g][col] = R(0);
     for (int e = tid; e < NJ * NPH; e += 64 * NW) {
         const int j = e / NPH, q = e - j * NPH;
         const int64_t Jv = J0 + j, Jc = Jv < nj ? Jv : nj - 1;
@@ -1849,8 +1856,8 @@ __global__ void __launch_bounds__(64 * NW) k_tq_lds(TransArgsT<R> a) {
     }
     __syncthreads();
     const int tr = a.tile_rot[rt], tc = a.tile_coax[rt];
-    const R *FF = a.frHT + (int64_t)tr * TF_FR_ROT + lane;  // forward: H (from HT's fragments)
-    const R *FB = a.frH + (int64_t)tr * TF_FR_ROT + lane;   // back: H^T
+    const R *FF = a.frPF + (int64_t)tr * TQ_FR_ROT + lane;
+    const R *FB = a.frPB + (int64_t)tr * TQ_FR_ROT + lane;
     const R *FC = a.frC + (int64_t)tc * TF_FR_COAX + lane;
     // lane l owns coefficients e = l + 64 u (u < 4) in the first and last steps; their orders m
     int mo[4];
@@ -1871,71 +1878,96 @@ __global__ void __launch_bounds__(64 * NW) k_tq_lds(TransArgsT<R> a) {
         for (int u = 0; u < 4; ++u) {
             const int e = lane + 64 * u;
             const C x = src[e], ph = phg[j][mo[u] + P - 1];
-            Xs[cb][e][2 * jl] = ph.x * x.x - ph.y * x.y;  // scalar accesses only (no type punning of Xs)
-            Xs[cb][e][2 * jl + 1] = ph.x * x.y + ph.y * x.x;
+            R *o = Xs + cb * CS + e * LD + 2 * jl;
+            o[0] = ph.x * x.x - ph.y * x.y;  // scalar accesses only (no type punning of Xs)
+            o[1] = ph.x * x.y + ph.y * x.x;
         }
     }
-    // rotation of degree n on the rows of Xs, in place
-    auto rotate = [&](auto nI, const R (&A)[16]) {
-        constexpr int n = decltype(nI)::value, KS = tq_dreg(n), RB = (2 * n + 16) / 16, w = 2 * n + 1;
-        R B[CB][KS];
+    // a lane's place g (operands) or 4 g (FP32 outputs) rows above and below row 0, in column col, as
+    // pointers that take constant offsets; its spare place
+    constexpr bool F64 = sizeof(R) == 8;
+    auto place = [&](int off) { return (R *)((char *)Xs + off * (int)sizeof(R)); };
+    R *const bp = place(g * LD + col), *const bm = place(col - g * LD);
+    R *const wp = F64 ? bp : place(4 * g * LD + col), *const wm = F64 ? bm : place(col - 4 * g * LD);
+    R *const spare = place(P2 * LD + lane);
+    // rotation of degree n > 0 on the rows of Xs, in place (degree 0 does not change): the sums u and
+    // the differences v of the orders +-k, one 16-row block each.  Forward: from c^{+-k} to u', v' (in
+    // the rows of +k and -k); back: from u', v' to c^{+-k} (the tables hold the factors 1/2).
+    auto rotate = [&](auto nI, auto fwdI, const R (&A)[8]) {
+        constexpr int n = decltype(nI)::value, KS = (n + 4) / 4, nc = n * n + n;
+        constexpr bool FWD = decltype(fwdI)::value != 0;
+        R Bu[CB][KS], Bv[CB][KS];
         tq_for<CB>([&](auto cI) {
             tq_for<KS>([&](auto iI) {
                 constexpr int c = decltype(cI)::value, i = decltype(iI)::value;
-                B[c][i] = Xs[c][n * n + 4 * i + g][col];  // past the degree: the next one's rows, zero columns of A
+                // k = 4 i + g; past the degree: other degrees' rows, zero columns of A
+                const R x = bp[c * CS + (nc + 4 * i) * LD];
+                const R y = n == 1 ? (g < 3 ? bm : Xs)[c * CS + nc * LD] : bm[c * CS + (nc - 4 * i) * LD];
+                Bu[c][i] = FWD ? x + y : x;
+                Bv[c][i] = FWD ? x - y : y;
             });
         });
-        v4 acc[CB][RB];
-        tq_for<CB>([&](auto cI) {
-            tq_for<RB>([&](auto bI) { acc[decltype(cI)::value][decltype(bI)::value] = v4{0, 0, 0, 0}; });
-        });
+        v4 au[CB], av[CB];
+        tq_for<CB>([&](auto cI) { au[decltype(cI)::value] = av[decltype(cI)::value] = v4{0, 0, 0, 0}; });
         tq_for<KS>([&](auto iI) {
-            tq_for<RB>([&](auto bI) {
-                tq_for<CB>([&](auto cI) {
-                    constexpr int b = decltype(bI)::value, i = decltype(iI)::value, c = decltype(cI)::value;
-                    acc[c][b] = Op::mma(A[b * 8 + i], B[c][i], acc[c][b]);
-                });
+            tq_for<CB>([&](auto cI) {
+                constexpr int i = decltype(iI)::value, c = decltype(cI)::value;
+                au[c] = Op::mma(A[i], Bu[c][i], au[c]);
+                av[c] = Op::mma(A[4 + i], Bv[c][i], av[c]);
             });
         });
-        tq_for<CB>([&](auto cI) {
-            tq_for<RB>([&](auto bI) {
-                constexpr int c = decltype(cI)::value, b = decltype(bI)::value;
-                tq_for<4>([&](auto iI) {
-                    constexpr int i = decltype(iI)::value;
-                    const int r = 16 * b + Op::row(g, i);
-                    if (r < w) Xs[c][n * n + r][col] = acc[c][b][i];
+        // rows r = Op::row(g, i); row 0 is written by both parts, the sums last (back: the same value)
+        tq_for<4>([&](auto iI) {
+            constexpr int i = decltype(iI)::value;
+            constexpr int rmin = F64 ? 4 * i : i, rmax = F64 ? 4 * i + 3 : 12 + i;
+            if constexpr (rmin <= n) {
+                const bool in = rmax <= n || (F64 ? g <= n - 4 * i : 4 * g <= n - i);
+                R *const qp = in ? wp + (nc + rmin) * LD : spare, *const qm = in ? wm + (nc - rmin) * LD : spare;
+                tq_for<CB>([&](auto cI) {
+                    constexpr int c = decltype(cI)::value;
+                    const R u = au[c][i], v = av[c][i];
+                    qm[c * CS] = FWD ? v : u - v;
+                    qp[c * CS] = FWD ? u : u + v;
                 });
-            });
+            }
+        });
+    };
+    auto load_rot = [&](auto nI, R (&A)[8], const R *F) {
+        constexpr int n = decltype(nI)::value;
+        tq_for<(n + 4) / 4>([&](auto iI) {
+            constexpr int i = decltype(iI)::value;
+            A[i] = F[((n * 2) * 4 + i) * 64];
+            A[4 + i] = F[((n * 2 + 1) * 4 + i) * 64];
         });
     };
     // the steps of one residue H (mod NW): forward rotation of its degrees, coaxial step of its
     // orders, back rotation of its degrees; table fragments one step (of the same residue) ahead
-    R AF[P][16];  // rotation fragments per degree (only the live ones take registers)
-    R TF[P][8];   // coaxial fragments per order |m|: 4 K chunks x (re, im)
+    R AF[P][8];  // rotation fragments per degree (only the live ones take registers)
+    R TF[P][8];  // coaxial fragments per order |m|: 4 K chunks x (re, im)
     auto forward = [&](auto HI) {
-        constexpr int H = decltype(HI)::value;
-        tq_for<4 / NW>([&](auto qI) {
-            constexpr int n = H + NW * decltype(qI)::value;
-            tq_load_rot<n>(AF[n], FF);
-        });
+        constexpr int H = decltype(HI)::value, N0 = H == 0 ? NW : H;  // first degree (0 stays)
+        load_rot(std::integral_constant<int, N0>{}, AF[N0], FF);
         tq_for<P / NW>([&](auto kI) {
             constexpr int n = NW * decltype(kI)::value + H;
-            if constexpr (n + 4 < P) tq_load_rot<n + 4>(AF[n + 4], FF);
-            if constexpr (n + NW >= P) {  // this residue's first order of the coaxial step
-                tq_for<tq_oreg(H)>([&](auto iI) {
-                    constexpr int i = decltype(iI)::value;
-                    TF[H][2 * i] = FC[((H * 4 + i) * 2) * 64];
-                    TF[H][2 * i + 1] = FC[((H * 4 + i) * 2 + 1) * 64];
-                });
+            if constexpr (n > 0) {
+                if constexpr (n + NW < P) load_rot(std::integral_constant<int, n + NW>{}, AF[n + NW], FF);
+                if constexpr (n + NW >= P) {  // this residue's first order of the coaxial step
+                    tq_for<tq_oreg(H)>([&](auto iI) {
+                        constexpr int i = decltype(iI)::value;
+                        TF[H][2 * i] = FC[((H * 4 + i) * 2) * 64];
+                        TF[H][2 * i + 1] = FC[((H * 4 + i) * 2 + 1) * 64];
+                    });
+                }
+                rotate(std::integral_constant<int, n>{}, std::integral_constant<int, 1>{}, AF[n]);
             }
-            rotate(std::integral_constant<int, n>{}, AF[n]);
         });
     };
     auto coax = [&](auto HI) {
         constexpr int H = decltype(HI)::value;
         const R swp = im ? R(1) : R(-1);
+        const int gl = g * LD, c1 = (g * g + g) * LD + col, c4 = (16 * g * g + 4 * g) * LD + col, pc = im ? -1 : 1;
         tq_for<P / NW>([&](auto kI) {
-            constexpr int am = NW * decltype(kI)::value + H, KS = tq_oreg(am), rows = P - am;
+            constexpr int am = NW * decltype(kI)::value + H, KS = tq_oreg(am);
             if constexpr (am + NW < P) {
                 tq_for<tq_oreg(am + NW)>([&](auto iI) {
                     constexpr int i = decltype(iI)::value;
@@ -1943,17 +1975,28 @@ __global__ void __launch_bounds__(64 * NW) k_tq_lds(TransArgsT<R> a) {
                     TF[am + NW][2 * i + 1] = FC[(((am + NW) * 4 + i) * 2 + 1) * 64];
                 });
             }
+            // degree x + g of order 0: row (x + g)^2 + x + g = x^2 + x + g (2 x + g + 1); degrees past 15
+            // read degree 15's row (zero columns of the table block)
+            R *ir[KS], *iw[4];
+            tq_for<KS>([&](auto iI) {
+                constexpr int i = decltype(iI)::value, x = am + 4 * i;
+                const int gg = min(g, P - 1 - x);
+                ir[i] = place(x + 3 < P ? c1 + 2 * x * gl : gg * (2 * x + gg + 1) * LD + col) + (x * x + x) * LD;
+            });
+            // outputs: rows r = g + 4 i (FP64: the operands' degrees) or 4 g + i
+            tq_for<4>([&](auto iI) {
+                constexpr int i = decltype(iI)::value, y = F64 ? am + 4 * i : am + i;
+                iw[i] = place(F64 ? c1 + 2 * y * gl : c4 + 8 * y * gl) + (y * y + y) * LD;
+            });
             tq_for<(am > 0 ? 2 : 1)>([&](auto sgI) {
                 constexpr int m = decltype(sgI)::value == 0 ? am : -am;
                 R B[CB][KS], Bw[CB][KS];
                 tq_for<CB>([&](auto cI) {
                     tq_for<KS>([&](auto iI) {
                         constexpr int c = decltype(cI)::value, i = decltype(iI)::value;
-                        // degrees past 15 read degree 15's row: zero columns of the table block
-                        const int nn = min(am + 4 * i + g, P - 1), row = nn * nn + nn + m;
                         // X': column 2j holds -Im x_j, column 2j+1 holds Re x_j (the partner column)
-                        B[c][i] = Xs[c][row][col];
-                        Bw[c][i] = swp * Xs[c][row][col ^ 1];
+                        B[c][i] = ir[i][c * CS + m * LD];
+                        Bw[c][i] = swp * (ir[i] + pc)[c * CS + m * LD];
                     });
                 });
                 v4 acc[CB];
@@ -1968,28 +2011,29 @@ __global__ void __launch_bounds__(64 * NW) k_tq_lds(TransArgsT<R> a) {
                         acc[c] = Op::mma(TF[am][2 * i + 1], Bw[c][i], acc[c]);
                     });
                 });
-                tq_for<CB>([&](auto cI) {
-                    tq_for<4>([&](auto iI) {
-                        constexpr int c = decltype(cI)::value, i = decltype(iI)::value;
-                        const int r = Op::row(g, i), nn = am + r;
-                        if (r < rows) Xs[c][nn * nn + nn + m][col] = acc[c][i];
-                    });
+                tq_for<4>([&](auto iI) {
+                    constexpr int i = decltype(iI)::value, y = F64 ? am + 4 * i : am + i;
+                    if constexpr (y < P) {
+                        const bool in = (F64 ? y + 3 : y + 12) < P || (F64 ? g : 4 * g) < P - y;
+                        R *const q = in ? iw[i] + m * LD : spare;
+                        tq_for<CB>([&](auto cI) {
+                            constexpr int c = decltype(cI)::value;
+                            q[c * CS] = acc[c][i];
+                        });
+                    }
                 });
             });
         });
     };
     auto back = [&](auto HI) {
         constexpr int H = decltype(HI)::value, N0 = P - NW + H;  // this residue's largest degree
-        tq_load_rot<N0>(AF[N0], FB);
+        load_rot(std::integral_constant<int, N0>{}, AF[N0], FB);
         tq_for<P / NW>([&](auto kI) {
             constexpr int n = N0 - NW * decltype(kI)::value;
-            if constexpr (n - NW >= 8) tq_load_rot<n - NW>(AF[n - NW], FB);
-            if constexpr (n >= 8 && n - NW < 8)  // the rest of this residue's degrees
-                tq_for<8 / NW>([&](auto qI) {
-                    constexpr int k = NW * decltype(qI)::value + H;
-                    tq_load_rot<k>(AF[k], FB);
-                });
-            rotate(std::integral_constant<int, n>{}, AF[n]);
+            if constexpr (n > 0) {
+                if constexpr (n - NW > 0) load_rot(std::integral_constant<int, n - NW>{}, AF[n - NW], FB);
+                rotate(std::integral_constant<int, n>{}, std::integral_constant<int, 0>{}, AF[n]);
+            }
         });
     };
     // each stage's residues under separate tests of h (compiled as one if / else chain, the back
@@ -2018,7 +2062,8 @@ __global__ void __launch_bounds__(64 * NW) k_tq_lds(TransArgsT<R> a) {
             const int e = lane + 64 * u;
             R sx = R(0), sy = R(0);
             for (int t = 0; t < len; ++t) {
-                const R xr = Xs[cb][e][2 * (jl + t)], xi = Xs[cb][e][2 * (jl + t) + 1];
+                const R *x = Xs + cb * CS + e * LD + 2 * (jl + t);
+                const R xr = x[0], xi = x[1];
                 const C ph = phg[j + t][mo[u] + P - 1];
                 sx += ph.x * xr + ph.y * xi;  // conj(e) x
                 sy += ph.x * xi - ph.y * xr;
@@ -2044,6 +2089,31 @@ __global__ void __launch_bounds__(256) k_fr_rot(int64_t ntot, int P, const doubl
     double v = 0.0;
     if (n < P && r < 2 * n + 1 && q < 2 * n + 1)
         v = M[cl * rot_table_size(P) + rot_block_off(n) + (int64_t)q * (2 * n + 1) + r];
+    out[e] = v;
+}
+
+// Fragment-order rotation tables of the sums and differences of the orders +-k (k_tq_lds), from a class's
+// table M (H^T for the forward rotation, H for the back one): element (class, n, part, i, lane) =
+// entry (r, k) = (lane % 16, 4 i + lane / 16) of degree n, M[k][r] +- M[-k][r] (orders counted from
+// 0, sign by part), zero past the degree.  Forward: row 0 of the sums is halved (u'_0 = c'^0), and so is
+// column 0, which meets 2 c^0.  Back: everything is halved (c^{+-r} = (u_r +- v_r) / 2) except row 0's
+// outcome c^0 = u_0, which the halved sum of two equal entries already is.
+__global__ void __launch_bounds__(256) k_fr_par(int64_t ntot, int P, int fwd, const double *M, double *out) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= ntot) return;
+    const int64_t cl = e / TQ_FR_ROT;
+    const int rem = (int)(e - cl * TQ_FR_ROT);
+    const int lane = rem & 63, i = (rem >> 6) & 3, part = (rem >> 8) & 1, n = rem >> 9;
+    const int r = lane & 15, k = 4 * i + (lane >> 4), w = 2 * n + 1;
+    double v = 0.0;
+    if (n < P && r <= n && k <= n) {
+        const double *Mn = M + cl * rot_table_size(P) + rot_block_off(n) + n * w + n + r;
+        const double x = Mn[k * w], y = Mn[-k * w];
+        v = part ? x - y : x + y;
+        if (!fwd || r == 0) v *= 0.5;
+        if (fwd && k == 0) v *= 0.5;
+        if (part && (r == 0 || k == 0)) v = 0.0;
+    }
     out[e] = v;
 }
 
@@ -2104,14 +2174,19 @@ int trans_fused_pmax() { return TF_PMAX; }
 int trans_rcr_p() { return TQ_P; }
 
 // H, HT: nbeta rotation tables of degree < P; coax: ncoax coaxial tables of size PT; outputs hold
-// max(1, nbeta) TF_FR_ROT and max(1, ncoax) TF_FR_COAX values
+// max(1, nbeta) TF_FR_ROT (frPF, frPB: TQ_FR_ROT) and max(1, ncoax) TF_FR_COAX values
 void build_fused_tables(int P, int PT, int nbeta, const double *H, const double *HT, int ncoax, const double2 *coax,
-                        double *frH, double *frHT, double *frC, hipStream_t st) {
+                        double *frH, double *frHT, double *frPF, double *frPB, double *frC, hipStream_t st) {
     if (P > TF_PMAX || PT < P) throw FmmError(-1, "fragment-order tables need p <= 16 and PT >= p");
     const int64_t nr = (int64_t)std::max(1, nbeta) * TF_FR_ROT, nc = (int64_t)std::max(1, ncoax) * TF_FR_COAX;
     k_fr_rot<<<(unsigned)((nr + 255) / 256), 256, 0, st>>>(nr, P, H, frH);
     LAUNCH_OK();
     k_fr_rot<<<(unsigned)((nr + 255) / 256), 256, 0, st>>>(nr, P, HT, frHT);
+    LAUNCH_OK();
+    const int64_t np = (int64_t)std::max(1, nbeta) * TQ_FR_ROT;
+    k_fr_par<<<(unsigned)((np + 255) / 256), 256, 0, st>>>(np, P, 1, HT, frPF);
+    LAUNCH_OK();
+    k_fr_par<<<(unsigned)((np + 255) / 256), 256, 0, st>>>(np, P, 0, H, frPB);
     LAUNCH_OK();
     k_fr_coax<<<(unsigned)((nc + 255) / 256), 256, 0, st>>>(nc, P, PT, coax, frC);
     LAUNCH_OK();
@@ -2146,7 +2221,8 @@ const char *trans_stage(const TransBatch &b, const TransTables<R> &tb, int stage
                         typename Cx<R>::T *W2, hipStream_t st, bool accumulate) {
     if (nr < 1 || b.JT % nr) throw FmmError(-1, "right-hand-side count must divide the tile size");
     TransArgsT<R> a{b.njob * nr, b.JT, b.psrc, b.ptgt, b.P, b.PT, PH, nr, src, dst, b.src, b.tgt, b.dir,
-                    b.tile_coax, b.tile_rot, tb.coax, tb.H, tb.HT, ph, W1, W2, b.seg, tb.frH, tb.frHT, tb.frC};
+                    b.tile_coax, b.tile_rot, tb.coax, tb.H, tb.HT, ph, W1, W2, b.seg, tb.frH, tb.frHT, tb.frC,
+                    tb.frPF, tb.frPB};
     // classes are padded to whole tiles of JT real jobs, so a tile of JT virtual jobs never
     // mixes tables: virtual tile t uses the tables of real tile t / nr
     const unsigned ntile = (unsigned)((b.njob * nr + b.JT - 1) / b.JT);
