@@ -23,8 +23,8 @@ __global__ void k_near_quad(int64_t, const int32_t *, const int32_t *, const dou
                             double2 *, double2 *);
 __global__ void k_densities(int64_t, int, const int32_t *, const double2 *, const double2 *, double, double2 *,
                             double2 *);
-__global__ void k_gamma(int64_t, const double4 *, const double4 *, const double2 *, double, double, double, double,
-                        double2, double2 *, double2 *);
+__global__ void k_gamma(int64_t, int, const double4 *, const double4 *, const double2 *, double, Monopoles, double2 *,
+                        double2 *);
 __global__ void k_zero8(int64_t, uint64_t *);
 __global__ void k_near_quad_n(int64_t, const int32_t *, const int32_t *, const double4 *, const double4 *,
                               const double *, double, double2 *, double2 *);
@@ -1249,18 +1249,41 @@ static void read_timings(fmmbem_ctx *c) {
     c->last.ms[7] = el(0, 8);
 }
 
-static void rhs_dev(fmmbem_ctx *c, int isrc, double2 *b) {
+static void launch_gamma(fmmbem_ctx *c, int nr, const int32_t *isrc, double2 *sigma, double2 *mu) {
+    const int64_t n = c->nt;
+    Monopoles m{};
+    for (int q = 0; q < nr; ++q) {
+        for (int d = 0; d < 3; ++d) m.rs[q][d] = c->src[3 * isrc[q] + d];
+        m.amp[q] = c->src_amp[isrc[q]];
+    }
+    k_gamma<<<ceil_div(n, 256), 256, 0, c->stream>>>(n, nr, (double4 *)c->buf.find("ec"), (double4 *)c->buf.find("en"),
+                                                     (double2 *)c->buf.find("beta"), c->k, m, sigma, mu);
+    LAUNCH_OK();
+}
+
+// Right-hand sides of cnt sources (b: cnt x N), in passes of 4, 2 and 1 vectors where the work rows
+// of one vector stay below 1 GiB (N up to about 280,000): there the passes share kernel evaluations,
+// tables and launches (N = 37,272, four sources: 3.70 -> 2.38 ms).  Larger rooms keep one vector per pass:
+// their passes fill the device alone (a 4-vector product of the 1M L-room costs 3.6 single ones),
+// and four vectors' work rows would be tens of GB.
+static void rhs_dev(fmmbem_ctx *c, int cnt, const int32_t *isrc, double2 *b) {
     hipStream_t st = c->stream;
     const int64_t n = c->nt;
-    double2 *sigma = dget<double2>(c->scratch, "sigma", n), *mu = dget<double2>(c->scratch, "mu", n);
-    const double *rs = &c->src[3 * isrc];
-    k_gamma<<<ceil_div(n, 256), 256, 0, st>>>(n, (double4 *)c->buf.find("ec"), (double4 *)c->buf.find("en"),
-                                              (double2 *)c->buf.find("beta"), c->k, rs[0], rs[1], rs[2],
-                                              c->src_amp[isrc], sigma, mu);
-    LAUNCH_OK();
-    HIP_OK(hipEventRecord(c->ev[0], st));
-    fmm_pass(c, 1, sigma, mu, nullptr, 0.0, b, false);
-    HIP_OK(hipEventRecord(c->ev[8], st));
+    double rows = 0.0;
+    for (const LevelDev &D : c->lev)
+        for (const TransBatch *t : {&D.m2l, &D.up, &D.down})
+            rows = std::max(rows, (double)t->njob * t->P * t->P * sizeof(double2));
+    const int most = rows <= (double)(1 << 30) ? 4 : 1;
+    for (int s = 0; s < cnt;) {
+        const int left = std::min(most, cnt - s), nr = left >= 4 ? 4 : left >= 2 ? 2 : 1;
+        double2 *sigma = dget<double2>(c->scratch, "sigma", (size_t)n * nr),
+                *mu = dget<double2>(c->scratch, "mu", (size_t)n * nr);
+        launch_gamma(c, nr, isrc + s, sigma, mu);
+        HIP_OK(hipEventRecord(c->ev[0], st));
+        fmm_pass(c, nr, sigma, mu, nullptr, 0.0, b + (int64_t)s * n, false);
+        HIP_OK(hipEventRecord(c->ev[8], st));
+        s += nr;
+    }
 }
 
 // ------------------------------------------------------------------ indirect formulation (Eq. ibem5)
@@ -1403,17 +1426,12 @@ static void matvec_bm(fmmbem_ctx *c, const double2 *x, double2 *y, bool exact_fa
     rec(c, 8);
 }
 
-static void rhs_bm(fmmbem_ctx *c, int isrc, double2 *b) {
+static void rhs_bm(fmmbem_ctx *c, int32_t isrc, double2 *b) {
     hipStream_t st = c->stream;
     const int64_t n = c->nt;
     double2 *sigma = dget<double2>(c->scratch, "sigma", n), *mu = dget<double2>(c->scratch, "mu", n);
     double2 *pq = dget<double2>(c->scratch, "bm_pq", 2 * n);
-    const double *rs = &c->src[3 * isrc];
-    // sigma = gamma (tree order), mu = 0
-    k_gamma<<<ceil_div(n, 256), 256, 0, st>>>(n, (double4 *)c->buf.find("ec"), (double4 *)c->buf.find("en"),
-                                              (double2 *)c->buf.find("beta"), c->k, rs[0], rs[1], rs[2],
-                                              c->src_amp[isrc], sigma, mu);
-    LAUNCH_OK();
+    launch_gamma(c, 1, &isrc, sigma, mu);  // sigma = gamma (tree order), mu = 0
     fmm_pass_ind(c, sigma, mu, nullptr, pq, false);
     k_bm_rhs<<<ceil_div(n, 256), 256, 0, st>>>(n, (int32_t *)c->buf.find("perm"), sigma, bm_alpha(c), pq, b);
     LAUNCH_OK();
@@ -1446,17 +1464,14 @@ static void matvec_dpsi(fmmbem_ctx *c, const double2 *v, double2 *y, bool exact_
     rec(c, 8);
 }
 
-static void rhs_dpsi(fmmbem_ctx *c, int isrc, double2 *b) {
+static void rhs_dpsi(fmmbem_ctx *c, int32_t isrc, double2 *b) {
     hipStream_t st = c->stream;
     const int64_t n = c->nt;
     double2 *sigma = dget<double2>(c->scratch, "sigma", n), *mu = dget<double2>(c->scratch, "mu", n);
     double2 *P = dget<double2>(c->scratch, "d5_p", n), *gam = dget<double2>(c->scratch, "d5_gam", n);
     const int32_t *perm = (int32_t *)c->buf.find("perm");
     const double2 *beta = (double2 *)c->buf.find("beta");
-    const double *rs = &c->src[3 * isrc];
-    k_gamma<<<ceil_div(n, 256), 256, 0, st>>>(n, (double4 *)c->buf.find("ec"), (double4 *)c->buf.find("en"), beta,
-                                              c->k, rs[0], rs[1], rs[2], c->src_amp[isrc], sigma, mu);
-    LAUNCH_OK();
+    launch_gamma(c, 1, &isrc, sigma, mu);
     k_rhs_dpsi_dens<<<ceil_div(n, 256), 256, 0, st>>>(n, perm, beta, sigma, mu, gam);
     LAUNCH_OK();
     HIP_OK(hipEventRecord(c->ev[0], st));
@@ -1799,14 +1814,17 @@ int64_t fmmbem_num_unknowns(const fmmbem_ctx *ctx) {
     return ctx->formulation == FMMBEM_INDIRECT ? 2 * ctx->nt : ctx->nt;
 }
 
-// right-hand side of source s into the device vector b (num_unknowns values) on the library stream
-static void rhs_one(fmmbem_ctx *ctx, int s, double2 *b) {
-    if (indirect(ctx)) rhs_ind(ctx, s, b);
-    else if (burton_miller(ctx)) rhs_bm(ctx, s, b);
-    else if (dpsi(ctx)) {
-        check_dpsi_beta(ctx);
-        rhs_dpsi(ctx, s, b);
-    } else rhs_dev(ctx, s, b);
+// right-hand sides of cnt sources into the device vectors b (num_unknowns values each) on the library
+// stream
+static void rhs_many(fmmbem_ctx *ctx, int cnt, const int32_t *isrc, double2 *b) {
+    if (!indirect(ctx) && !burton_miller(ctx) && !dpsi(ctx)) return rhs_dev(ctx, cnt, isrc, b);
+    if (dpsi(ctx)) check_dpsi_beta(ctx);
+    const int64_t n = fmmbem_num_unknowns(ctx);
+    for (int s = 0; s < cnt; ++s) {
+        if (indirect(ctx)) rhs_ind(ctx, isrc[s], b + s * n);
+        else if (burton_miller(ctx)) rhs_bm(ctx, isrc[s], b + s * n);
+        else rhs_dpsi(ctx, isrc[s], b + s * n);
+    }
 }
 
 int fmmbem_rhs(fmmbem_ctx *ctx, fmmbem_c64 *b) {
@@ -1817,10 +1835,13 @@ int fmmbem_rhs(fmmbem_ctx *ctx, fmmbem_c64 *b) {
     if (ctx->src.empty()) return fail(ctx, FMMBEM_ENOTREADY, "sources not set");
     ensure_setup(ctx);
     const int64_t n = fmmbem_num_unknowns(ctx);
-    double2 *db = dget<double2>(ctx->scratch, "rhs_out", n);
-    for (size_t s = 0; s < ctx->src.size() / 3; ++s) {
-        rhs_one(ctx, (int)s, db);
-        HIP_OK(hipMemcpyAsync(b + s * n, db, sizeof(double2) * n, hipMemcpyDeviceToHost, ctx->stream));
+    const int ns = (int)(ctx->src.size() / 3);
+    double2 *db = dget<double2>(ctx->scratch, "rhs_out", n * std::min(ns, 4));
+    for (int s = 0; s < ns; s += 4) {
+        const int cnt = std::min(4, ns - s);
+        const int32_t which[4] = {s, s + 1, s + 2, s + 3};
+        rhs_many(ctx, cnt, which, db);
+        HIP_OK(hipMemcpyAsync(b + s * n, db, sizeof(double2) * n * cnt, hipMemcpyDeviceToHost, ctx->stream));
         HIP_OK(hipStreamSynchronize(ctx->stream));
     }
     return FMMBEM_OK;
@@ -1834,11 +1855,12 @@ int fmmbem_rhs_dev(fmmbem_ctx *ctx, void *b_dev, void *stream) {
     HIP_OK(hipSetDevice(ctx->device));
     if (ctx->src.empty()) return fail(ctx, FMMBEM_ENOTREADY, "sources not set");
     ensure_setup(ctx);
-    const int64_t n = fmmbem_num_unknowns(ctx);
     hipStream_t caller = (hipStream_t)stream;
     ev_record(ctx, EV_CALLER_IN, caller);
     ev_wait(ctx, EV_CALLER_IN, ctx->stream);
-    for (size_t s = 0; s < ctx->src.size() / 3; ++s) rhs_one(ctx, (int)s, (double2 *)b_dev + s * n);
+    std::vector<int32_t> all(ctx->src.size() / 3);
+    std::iota(all.begin(), all.end(), 0);
+    rhs_many(ctx, (int)all.size(), all.data(), (double2 *)b_dev);
     ev_record(ctx, EV_CALLER_DONE, ctx->stream);
     ev_wait(ctx, EV_CALLER_DONE, caller);
     return FMMBEM_OK;
@@ -2249,7 +2271,7 @@ static int solve_impl(fmmbem_ctx *ctx, int32_t isrc, const fmmbem_solve_opts *op
     if (ind) rhs_ind(ctx, isrc, b);
     else if (bm) rhs_bm(ctx, isrc, b);
     else if (dp) rhs_dpsi(ctx, isrc, b);
-    else rhs_dev(ctx, isrc, b);
+    else rhs_dev(ctx, 1, &isrc, b);
     if (dev) {
         ev_record(ctx, EV_CALLER_IN, caller);
         ev_wait(ctx, EV_CALLER_IN, st);
@@ -2385,7 +2407,7 @@ int fmmbem_solve_batch(fmmbem_ctx *ctx, int32_t ns, const int32_t *isrc, const f
     auto pc = make_precond(ctx, o);
     double2 *B = dget<double2>(ctx->scratch, "sb_b", (size_t)ns * n);
     double2 *X = dget<double2>(ctx->scratch, "sb_x", (size_t)ns * n);
-    for (int s = 0; s < ns; ++s) rhs_dev(ctx, isrc[s], B + (int64_t)s * n);
+    rhs_dev(ctx, ns, isrc, B);
     if (o.use_x0) HIP_OK(hipMemcpyAsync(X, x, sizeof(double2) * n * ns, hipMemcpyHostToDevice, st));
     const bool mixed = o.precision == FMMBEM_MIXED;
     int64_t n64 = 0, nmx = 0;
@@ -2546,7 +2568,7 @@ int fmmbem_learned_train(fmmbem_ctx *ctx, int32_t isrc, const fmmbem_train_opts 
     double2 *b = dget<double2>(ctx->scratch, "tr_b", n), *x = dget<double2>(ctx->scratch, "tr_x", n);
     double2 *XS = dget<double2>(ctx->scratch, "tr_xs", (size_t)o.max_pairs * n);
     double2 *RS = dget<double2>(ctx->scratch, "tr_rs", (size_t)o.max_pairs * n);
-    rhs_dev(ctx, isrc, b);
+    rhs_dev(ctx, 1, &isrc, b);
     std::vector<double> prel;
     FgmresHooks hk;
     hk.on_restart = [&](const double2 *xk, const double2 *rk, double rel) {
@@ -2908,11 +2930,11 @@ int fmmbem_solve_many(int32_t count, fmmbem_ctx *const *ctxs, const int32_t *isr
         G.nv = nv;
         double2 *B = dget<double2>(ctx->scratch, "mb_b", (size_t)nv * n);
         double2 *X = dget<double2>(ctx->scratch, "mb_x", (size_t)nv * n);
-        if (dpsi(ctx)) check_dpsi_beta(ctx);
-        for (int s = 0; s < nv; ++s) {
-            rhs_one(ctx, isrc[mem[s]], B + (int64_t)s * n);
-            if (o.use_x0) h2d_now(X + (int64_t)s * n, x[mem[s]], sizeof(double2) * n, st);
-        }
+        std::vector<int32_t> which;
+        for (int s = 0; s < nv; ++s) which.push_back(isrc[mem[s]]);
+        rhs_many(ctx, nv, which.data(), B);
+        if (o.use_x0)
+            for (int s = 0; s < nv; ++s) h2d_now(X + (int64_t)s * n, x[mem[s]], sizeof(double2) * n, st);
         const bool mixed = o.precision == FMMBEM_MIXED;
         const bool direct = !indirect(ctx) && !burton_miller(ctx) && !dpsi(ctx);
         int64_t *c64 = &n64[q], *cmx = &nmx[q];

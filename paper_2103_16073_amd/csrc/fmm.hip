@@ -453,22 +453,25 @@ __global__ void k_densities(int64_t n, int nr, const int32_t *perm, const double
     mu[e] = xi;
 }
 
-// gamma_i = -dpsi_in/dn + i k beta psi_in at centroid i for a monopole of amplitude amp at rs (Eq. sp7)
-__global__ void k_gamma(int64_t n, const double4 *ec, const double4 *en, const double2 *beta, double k, double sx,
-                        double sy, double sz, double2 amp, double2 *sigma, double2 *mu) {
+// gamma_i = -dpsi_in/dn + i k beta psi_in at centroid i for nr monopoles of amplitude amp at rs (Eq. sp7),
+// the vectors interleaved
+__global__ void k_gamma(int64_t n, int nr, const double4 *ec, const double4 *en, const double2 *beta, double k,
+                        Monopoles src, double2 *sigma, double2 *mu) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     double4 c = ec[i], nv = en[i];
-    double dx = c.x - sx, dy = c.y - sy, dz = c.z - sz;
-    double r = sqrt(dx * dx + dy * dy + dz * dz);
-    double s, co;
-    sincos(k * r, &s, &co);
-    double2 G = cmul(amp, cmk(co / (4 * FMM_PI * r), s / (4 * FMM_PI * r)));
-    double proj = (dx * nv.x + dy * nv.y + dz * nv.z) / (r * r);
-    double2 dG = cscale(cmul(G, cmk(-1.0, k * r)), proj);      // G (ikr - 1) (x - rs).n / r^2
     double2 ikb = cmk(-k * beta[i].y, k * beta[i].x);          // i k beta
-    sigma[i] = csub(cmul(ikb, G), dG);
-    mu[i] = cmk(0, 0);
+    for (int q = 0; q < nr; ++q) {
+        double dx = c.x - src.rs[q][0], dy = c.y - src.rs[q][1], dz = c.z - src.rs[q][2];
+        double r = sqrt(dx * dx + dy * dy + dz * dz);
+        double s, co;
+        sincos(k * r, &s, &co);
+        double2 G = cmul(src.amp[q], cmk(co / (4 * FMM_PI * r), s / (4 * FMM_PI * r)));
+        double proj = (dx * nv.x + dy * nv.y + dz * nv.z) / (r * r);
+        double2 dG = cscale(cmul(G, cmk(-1.0, k * r)), proj);  // G (ikr - 1) (x - rs).n / r^2
+        sigma[i * nr + q] = csub(cmul(ikb, G), dG);
+        mu[i * nr + q] = cmk(0, 0);
+    }
 }
 
 // ------------------------------------------------------------------ pair-kernel helpers

@@ -159,6 +159,11 @@ constexpr int SEG_ALIGN = 8;
 // field at points: workgroups wanted before the elements are left in one piece, and the most partial
 // sums a call writes (2 MiB)
 constexpr int64_t FIELD_WGS = 8192, FIELD_PART = (int64_t)1 << 17;
+// up to four monopole sources of one right-hand side pass
+struct Monopoles {
+    double rs[4][3];
+    double2 amp[4];
+};
 // the octree's leaves, for the elements near a point: sorted Morton codes, ranges of elements, the
 // cube's corner and cells per metre, and how many cells r_c may reach
 struct FieldTree {

@@ -81,3 +81,24 @@ def test_field_point_counts_vs_oracle(F, h, opt):
         psi = ctx.fmmbem_eval_field(0, many, x)
         assert np.max(np.abs(psi - np.tile(ref, len(many) // len(pts)))) < 1e-10 * np.linalg.norm(ref) / np.sqrt(len(ref))
     ctx.close()
+
+
+@pytest.mark.parametrize("ns", [1, 2, 3, 4, 7])
+def test_right_hand_sides_of_many_sources_vs_oracle(F, ns):
+    """Sources taken four, two and one per pass: every right-hand side on sampled rows against the
+    oracle, amplitudes included, and a product afterwards as before."""
+    room, k = synth.config_room(1)
+    ctx = _ctx(F, room, k)
+    x = synth.complex_normal(room.n, 5)
+    before = ctx.fmmbem_matvec(x)
+    rs = synth.sample_points(room, ns, 9)
+    amp = synth.complex_normal(ns, 6)
+    ctx.fmmbem_set_sources(rs, amp)
+    b = ctx.fmmbem_rhs()
+    rows = np.unique(np.linspace(0, room.n - 1, 60).astype(int))
+    rc = oracle_rc(ctx, room)
+    for s in range(ns):
+        ref = amp[s] * bem.direct_rhs_rows(room.vertices, room.triangles, k, room.beta, rs[s], rc, rows)
+        assert np.linalg.norm(b[s, rows] - ref) < 1e-6 * np.linalg.norm(ref), s
+    assert np.array_equal(ctx.fmmbem_matvec(x), before)
+    ctx.close()
