@@ -125,7 +125,7 @@ typedef struct {
     int mfma;            /* matrix-core tiles for the stages of job-tile batches (each
                             degree/order of a 64- or 32-job tile as a real GEMM on
                             v_mfma_f64_16x16x4f64, FP32: v_mfma_f32_16x16x4f32): 1 for batches with
-                            p >= 24 under the fixed rule (32-job tiles where the classes are
+                            p >= 17 under the fixed rule (32-job tiles where the classes are
                             small), and the autotuner measures them for every job-tile batch; 2
                             for every job-tile batch; 0 never; default 1 */
     int fused;           /* lane batches with p_src = p_tgt = p <= 16 may run all three stages in

@@ -401,9 +401,11 @@ static void make_batch(fmmbem_ctx *c, const std::string &name, std::vector<JobH>
         return x.tgt < y.tgt;
     });
     // Tile shape: one job per lane (64-job tiles) when the classes are large enough that padding
-    // them to 64 wastes at most a quarter of the work, or, for matrix-core tiles (p >= 24, several
-    // times faster than the LDS tiles there), at most half of it (32-job tiles where the 64-job
-    // padding would exceed a third); otherwise whole-vector tiles while at least 8 jobs fit the
+    // them to 64 wastes at most a quarter of the work, or, for matrix-core tiles (p >= 17, several
+    // times faster than the LDS tiles there and no slower than the lane kernels: a level-3 M2L of
+    // 5,326 jobs and four vectors at p = 18, 0.78 -> 0.35 ms; 56,616 jobs at p = 21 in FP32, 1.90
+    // against 1.95 ms), at most half of it (32-job tiles where the 64-job padding would exceed a
+    // third); otherwise whole-vector tiles while at least 8 jobs fit the
     // LDS budget, per-degree slices beyond.
     int64_t pad64 = 0, pad32 = 0;
     for (size_t q = 0; q < jobs.size();) {
@@ -414,7 +416,7 @@ static void make_batch(fmmbem_ctx *c, const std::string &name, std::vector<JobH>
         q = e;
     }
     const int64_t nj = (int64_t)jobs.size();
-    const bool mf = c->opt.mfma == 2 || (c->opt.mfma == 1 && b.P >= 24);
+    const bool mf = c->opt.mfma == 2 || (c->opt.mfma == 1 && b.P >= 17);
     b.lane = !jobs.empty() && (c->opt.lane_tiles == 2 ||
                                (c->opt.lane_tiles == 1 && (pad64 * 4 <= nj * 5 || (mf && pad32 <= 2 * nj))));
     if (b.lane) {
