@@ -69,7 +69,9 @@ void launch_p2p_n(int nleaf, int nsplit, const int32_t *leaf_start, const int32_
 bool p2m_fits(int nr, int p);
 void launch_p2m(int nr, int nleaf, int p, const int32_t *leaf_start, const double4 *center, const double4 *ec,
                 const double4 *en, const double2 *sigma, const double2 *mu, double k, const double *leg,
-                double2 *Mout, hipStream_t st);
+                const double *tab, double2 *Mout, float2 *M32, hipStream_t st);
+bool p2m_writes_fp32(int p);
+void build_p2m_table(double *tab, hipStream_t st);
 void launch_l2p(int nr, int nleaf, int p, const int32_t *leaf_start, const double4 *center, const double4 *ec,
                 const double2 *Lc, double k, const double *leg, const double2 *ynear, int nsplit,
                 double half, const int32_t *perm, int64_t n, const double2 *x, double2 *y, int has_far,
@@ -545,6 +547,7 @@ static void setup_k(fmmbem_ctx *c) {
         upload(c->buf, "legtab", lt, st);
         c->delta_p = c->pmax;
     }
+    if (!c->buf.find("p2mtab")) build_p2m_table(dget<double>(c->buf, "p2mtab", P2M_TABLE), st);
     // coaxial tables
     std::vector<CoaxJob> jobs;
     for (int l = 2; l <= L; ++l) {
@@ -1119,9 +1122,10 @@ static void fmm_pass(fmmbem_ctx *c, int nr, const double2 *sigma, const double2 
         check_p2m(nr, p);
         const size_t pp = (size_t)p * p;
         pe = prof_begin(c);
-        launch_p2m(nr, nleaf, p, I32("leaf_start"), LL.center, ec, en, sigma, mu, c->k, leg_table(c), LL.M, A);
+        launch_p2m(nr, nleaf, p, I32("leaf_start"), LL.center, ec, en, sigma, mu, c->k, leg_table(c),
+                   (double *)c->buf.find("p2mtab"), LL.M, mixed && p2m_writes_fp32(p) ? LL.M32 : nullptr, A);
         prof_end(c, pe, "k_p2m", (double)n * pp * 2 * 8.0 * nr, 112.0 * n + 32.0 * n * nr + 16.0 * nleaf * pp * nr);
-        if (mixed) {
+        if (mixed && !p2m_writes_fp32(p)) {
             // FP32 translations between an FP64 P2M and an FP64 L2P
             pe = prof_begin(c);
             convert(c, (int64_t)LL.nbox * nr * pp, (const double2 *)LL.M, LL.M32);
@@ -1350,12 +1354,15 @@ static void fmm_pass_ind(fmmbem_ctx *c, const double2 *sigma, const double2 *mu,
     if (!exact_far) {
         pe = prof_begin(c);
         check_p2m(1, p);
-        launch_p2m(1, nleaf, p, I32("leaf_start"), LL.center, ec, en, sigma, mu, c->k, leg_table(c), LL.M, A);
+        launch_p2m(1, nleaf, p, I32("leaf_start"), LL.center, ec, en, sigma, mu, c->k, leg_table(c),
+                   (double *)c->buf.find("p2mtab"), LL.M, mixed && p2m_writes_fp32(p) ? LL.M32 : nullptr, A);
         prof_end(c, pe, "k_p2m", (double)n * pp * 2 * 8.0, 112.0 * n + 32.0 * n + 16.0 * nleaf * pp);
         if (mixed) {
-            pe = prof_begin(c);
-            convert(c, (int64_t)LL.nbox * pp, (const double2 *)LL.M, LL.M32);
-            prof_end(c, pe, "k_cvt", 0.0, 24.0 * LL.nbox * pp);
+            if (!p2m_writes_fp32(p)) {
+                pe = prof_begin(c);
+                convert(c, (int64_t)LL.nbox * pp, (const double2 *)LL.M, LL.M32);
+                prof_end(c, pe, "k_cvt", 0.0, 24.0 * LL.nbox * pp);
+            }
             far_field<float>(c, 1, true);
             pe = prof_begin(c);
             convert(c, (int64_t)LL.nbox * pp, (const float2 *)LL.L32, LL.L);

@@ -1324,105 +1324,204 @@ __device__ inline void bessel_j_seq_tab(double x, int N, double *j, const double
     }
 }
 
-// P2M with one thread per basis slot.  A workgroup takes one leaf; per chunk of CH sources:
-//  1. one thread per source: frame, j_0..j_p(k r), the phase powers E_m' = (sin(th) e^{i phi})^m'
-//     and the slot weights al_k of every vector;
+// Constant tables of P2M (P2M_TABLE doubles): the seven terms of every coefficient c < P2M_CAP
+// (p2m_terms without the factor k, independent of p) as factors f[7][cap] and int32 slots[7][cap] =
+// 2 slot + (conjugated entry), a missing entry with factor 0; the Bessel series, for n <= P2M_PMAX
+// ser[n][q - 1] = 1 / (q (2n + 2q + 1)) and, last in the row, 1 / (2n + 1)!!; the orders of the slots.
+__global__ void k_p2m_table(double *tab) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x, cap = P2M_CAP;
+    double *f = tab, *ser = tab + P2M_OSER;
+    int32_t *slot = (int32_t *)(tab + 7 * cap), *order = (int32_t *)(tab + P2M_OORD);
+    if (c < cap) {
+        P2mTerms T;
+        const int none = 1 << 20;
+        p2m_terms(1 << 10, none, c, 1.0, T);
+        for (int t = 0; t < 7; ++t) {
+            f[t * cap + c] = T.fx[t];
+            slot[t * cap + c] = T.i[t] == none ? 0 : 2 * T.i[t] + (T.fy[t] != T.fx[t]);
+        }
+    }
+    if (c <= P2M_PMAX) {
+        double df = 1.0;
+        for (int q = 1; q <= c; ++q) df *= 2.0 * q + 1.0;
+        for (int q = 1; q < P2M_SER; ++q) ser[c * P2M_SER + q - 1] = 1.0 / ((double)q * (2.0 * c + 2.0 * q + 1.0));
+        ser[c * P2M_SER + P2M_SER - 1] = 1.0 / df;
+        for (int m = 0; m <= c; ++m) order[leg_tri(c, m)] = m;
+        for (int t = leg_tri(P2M_PMAX + 1, 0) + c; t < P2M_SLOTS; t += P2M_PMAX + 1) order[t] = 0;
+    }
+}
+
+// x^m by squaring, m < 32
+__device__ inline double pow_small(double x, int m) {
+    double r = m & 1 ? x : 1.0;
+    for (int b = 1; b < 5; ++b) {
+        x *= x;
+        r = (m >> b) & 1 ? r * x : r;
+    }
+    return r;
+}
+
+// j_0(x) .. j_N(x), 1 <= N <= P2M_PMAX, by the method of bessel_j_seq: for 1e-2 <= x < 4 j_N and j_{N-1}
+// from their series (tables of the orders N - 1 and N, P2M_SER each, at ser) and the downward
+// recurrence; ix = 1 / x
+__device__ inline void bessel_j_seq_ser(double x, double ix, int N, double *j, const double *ser) {
+    if (x < 1e-2 || x >= 4.0) {
+        bessel_j_seq_fast(x, N, j);
+        return;
+    }
+    const double h = -0.5 * x * x;
+    double sh = 1.0, th = 1.0, sl = 1.0, tl = 1.0;  // orders N and N - 1
+#pragma unroll 1
+    for (int q = 0; q + 4 < P2M_SER; q += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            tl *= h * ser[q + u];
+            th *= h * ser[P2M_SER + q + u];
+            sl += tl;
+            sh += th;
+        }
+        if (!__any(fabs(tl) > 1e-17 * fabs(sl))) break;
+    }
+    const double xn = pow_small(x, N - 1);
+    double jl = sl * (xn * ser[P2M_SER - 1]), jh = sh * (xn * x * ser[2 * P2M_SER - 1]);
+    j[N] = jh;
+    j[N - 1] = jl;
+    double c = 2.0 * N - 1.0;  // 2n + 1
+    for (int n = N - 1; n >= 1; --n) {
+        const double jm = fma(c * ix, jl, -jh);
+        j[n - 1] = jm;
+        jh = jl;
+        jl = jm;
+        c -= 2.0;
+    }
+}
+
+// P2M by matrix cores.  A workgroup takes one leaf, its sources in equal groups of at most G; per
+// group:
+//  1. one thread per source: j_0..j_p(k r) on one wavefront, the phase powers E_m' = ((dx + i dy) /
+//     r)^m' = (sin(th) e^{i phi})^m' on another, the weights al_k of every vector on the other two;
 //  2. the real part of the basis, R~_n^m' = j_n(k r) P_n^m'(cos th) / sin^m'(th), one recurrence in
 //     n per (source, m'), the orders m' and p - m' paired so that each item is p + 2 steps long;
-//  3. one thread per slot (n, m'), m' >= 0: R_n^m' = E_m' R~_n^m' and, for every k, the four real
-//     sums of Re/Im al_k times Re/Im R, which give both sum_s al_k R (P) and sum_s conj(al_k) R (Q)
-//     (the same slot sums as the wide kernel, at half its multiplications);
-//  4. every coefficient from seven factor-weighted slot sums, through LDS.
-// Needs (p + 1)(p + 2)/2 <= 256 (p <= 20); launch_p2m takes the wide kernel beyond.
-template <int NR>
-__global__ void __launch_bounds__(256) k_p2m(int nleaf, int p, int CH, const int32_t *leaf_start,
-                                             const double4 *center, const double4 *ec, const double4 *en,
-                                             const double2 *sigma, const double2 *mu, double k, const double *leg,
-                                             double2 *Mout) {
-    extern __shared__ double2 smem[];
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const int TB = (p + 1) * (p + 2) / 2, TS = TB + 1, p1 = p + 1;
-    double2 *E = smem;                          // CH * (p+1)
-    double2 *al = E + CH * p1;                  // CH * 4 * NR
-    double *Rb = (double *)(al + CH * 4 * NR);  // CH * TB
-    double *jb = Rb + CH * TB;                  // CH * (p+2)
-    double *cth = jb + CH * (p + 2);            // CH
-    double *lt = cth + CH;                      // 3 TB: Legendre recurrence table
-    double *bc = lt + 3 * TB;                   // 2 BS_TERMS: series coefficients of j_p, j_{p-1}
-    double2 *SL = smem;                         // after the last chunk: [8][TS] slot sums of one vector
-    for (int e = tid; e < 3 * TB; e += blockDim.x) lt[e] = leg[e];
-    bessel_series_coeffs(p, bc, tid, blockDim.x);
+//  3. the sums over the sources as a product: rows the slots (n, m' >= 0) twice (Re E R~, Im E R~,
+//     formed as the A operand is read), columns Re/Im al_k of every vector, K the sources: the four
+//     real sums per weight that give both sum_s al_k R (P) and sum_s conj(al_k) R (Q).  The four
+//     wavefronts take every fourth block of 16 rows, NBW of them, in registers over all groups.
+// Then every coefficient from seven factor-weighted slot sums, through LDS.  Bound by the latency of
+// its steps: G is chosen for four workgroups per CU (three for several vectors).
+// Measured against one thread per slot (every source's weights times the basis on the vector units,
+// an FP64 result converted by another kernel for FP32 translations), leaves of 33 sources, p = 16:
+// 90,972 elements 94 -> 86 us, 906,812 elements 669 -> 625 us; four vectors of 612,000 elements in
+// mixed precision 1,975 -> 990 us.  A thread per (source, order) evaluating its own Bessel series,
+// instead of one recurrence per source: 896 us at 906,812 elements.
+// Needs (p + 1)(p + 2)/2 <= 256 (p <= 21); launch_p2m takes the wide kernel beyond.
+// CO: float2 where the translations run in FP32.
+struct P2mLayout {
+    int TB, TBP, LDR, LDD, p1, GP, NC;  // slots, padded to 16; row strides; sources padded to 4; columns
+    int oE, oJ, oC, oW, oL, oS, total;  // offsets in doubles (the basis at 0)
+    __host__ __device__ P2mLayout(int p, int G, int nr) {
+        TB = (p + 1) * (p + 2) / 2;
+        TBP = (TB + 15) & ~15;
+        LDR = TBP + (TBP % 32 ? 0 : 16);  // four sources' rows on different banks
+        LDD = nr > 1 && TBP <= 160 ? 17 : 9;  // the sums of two vectors or one (8 columns each)
+        p1 = p + 1;
+        GP = (G + 3) & ~3;
+        NC = nr > 2 ? 32 : 16;
+        oE = G * LDR;
+        oJ = oE + 2 * G * p1;
+        oC = oJ + G * (p + 2);
+        oW = (oC + G + 1) & ~1;
+        oL = oW + GP * NC;
+        oS = oL + 3 * TB;
+        total = oS + 2 * P2M_SER;
+        if (total < 2 * TBP * LDD) total = 2 * TBP * LDD;  // the sums reuse the area
+    }
+};
+template <int NR, int NBW, class CO>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NBW <= 5 ? (NR > 1 ? 3 : 4) : (NR > 2 ? 2 : 3))))
+k_p2m(int p, int G, const int32_t *leaf_start, const double4 *center, const double4 *ec, const double4 *en,
+      const double2 *sigma, const double2 *mu, double k, double ik, const double *leg, const double *tab, CO *Mout) {
+    typedef double v4 __attribute__((ext_vector_type(4)));
+    constexpr int NCB = NR > 2 ? 2 : 1, NC = 16 * NCB, VP = NR > 1 && NBW <= 5 ? 2 : 1, LDD = 8 * VP + 1, cap = P2M_CAP;
+    extern __shared__ double p2m_sm[];
+    const P2mLayout Y(p, G, NR);
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l16 = lane & 15, kq = lane >> 4;
+    const int TB = Y.TB, TBP = Y.TBP, LDR = Y.LDR, p1 = Y.p1;
+    double *Rb = p2m_sm, *E = p2m_sm + Y.oE, *jb = p2m_sm + Y.oJ, *cth = p2m_sm + Y.oC, *W = p2m_sm + Y.oW,
+           *lt = p2m_sm + Y.oL, *ser = p2m_sm + Y.oS, *Dl = p2m_sm;
     const double4 C = center[b];
-    const int ss = leaf_start[b], se = leaf_start[b + 1];
-    // a chunk's source data is loaded while the previous chunk is summed
-    double4 pc = make_double4(0, 0, 0, 0), pn = pc;
-    double2 pq[NR], pw[NR];
-    auto fetch = [&](int j0n) {
-        const int j = j0n + tid;
-        if (tid < CH && j < se) {
-            pc = ec[j];
-            pn = en[j];
+    const int ss = leaf_start[b], ns = leaf_start[b + 1] - ss;
+    const int ng = (ns + G - 1) / G, gs = (ns + ng - 1) / ng;
+    for (int e = tid; e < 3 * TB; e += 256) lt[e] = leg[e];
+    if (tid < 2 * P2M_SER) ser[tid] = tab[P2M_OSER + (p - 1) * P2M_SER + tid];
+    const int32_t *order = (const int32_t *)(tab + P2M_OORD);
+    // this lane's rows of the product: basis slot and the phase power it takes (its real or imaginary part)
+    int slot[NBW], eo[NBW];
 #pragma unroll
-            for (int rr = 0; rr < NR; ++rr) {
-                pq[rr] = sigma[(int64_t)j * NR + rr];
-                pw[rr] = mu[(int64_t)j * NR + rr];
+    for (int q = 0; q < NBW; ++q) {
+        const int row = 16 * (wv + 4 * q) + l16, part = row >= TBP ? 1 : 0, t = min(row - part * TBP, TBP - 1);
+        slot[q] = t;
+        eo[q] = t < TB ? 2 * order[t] + part : 0;
+    }
+    v4 acc[NBW][NCB];
+#pragma unroll
+    for (int q = 0; q < NBW; ++q)
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) acc[q][cb] = v4{0, 0, 0, 0};
+    const int npair = p / 2 + 1, npad = TBP - TB;
+    for (int g = 0; g < ng; ++g) {
+        const int j0 = ss + g * gs, cnt = min(gs, ss + ns - j0), gp = (cnt + 3) & ~3;
+        __syncthreads();  // the previous group's readers are done (and the tables are in place)
+        if (wv < 2 && lane < cnt) {
+            const double4 c = ec[j0 + lane];
+            const double dx = c.x - C.x, dy = c.y - C.y, dz = c.z - C.z, r2 = dx * dx + dy * dy + dz * dz;
+            const bool at = r2 < 1e-280;  // at the centre: theta = 0
+            const double ir = at ? 0.0 : rsq_nr(r2);
+            if (wv == 0) {
+                cth[lane] = at ? 1.0 : dz * ir;
+                bessel_j_seq_ser(k * (r2 * ir), ik * ir, p, jb + lane * (p + 2), ser);
+            } else {
+                const double2 u = cmk(dx * ir, dy * ir);
+                double2 e = cmk(1.0, 0.0);
+                double *o = E + lane * p1 * 2;
+                for (int m = 0; m <= p; ++m) {
+                    o[2 * m] = e.x;
+                    o[2 * m + 1] = e.y;
+                    e = cmul(e, u);
+                }
             }
         }
-    };
-    fetch(ss);
-    // this thread's slot
-    int sn = 0, sm = 0;
-    if (tid < TB) {
-        while ((sn + 1) * (sn + 2) / 2 <= tid) ++sn;
-        sm = tid - sn * (sn + 1) / 2;
-    }
-    double acc[4][NR][4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int rr = 0; rr < NR; ++rr)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc[q][rr][u] = 0.0;
-    const int npair = p / 2 + 1;
-    for (int j0 = ss; j0 < se; j0 += CH) {
-        const int cnt = min(CH, se - j0);
-        __syncthreads();  // the previous chunk's readers are done (and lt is in place)
-        if (tid < cnt) {
-            const double4 c = pc, nv = pn;
-            double r, ct, st;
-            double2 eph;
-            sph_frame(c.x - C.x, c.y - C.y, c.z - C.z, r, ct, st, eph);
-            cth[tid] = ct;
-            bessel_j_seq_tab(k * r, p, jb + tid * (p + 2), bc);
-            const double2 u = cscale(eph, st);
-            double2 e = cmk(1.0, 0.0);
-            for (int m = 0; m <= p; ++m) {
-                E[tid * p1 + m] = e;
-                e = cmul(e, u);
+        for (int e = tid - 128; e < gp * 4 * (NC / 8); e += 128) {  // (source, vector, weight)
+            if (e < 0) break;
+            const int s = e / (NC / 2), rk = e - s * (NC / 2), r = rk >> 2, kk = rk & 3;
+            double2 al = cmk(0.0, 0.0);
+            if (s < cnt && r < NR) {
+                const int64_t j = j0 + s;
+                const double4 nv = en[j];
+                const double a = ec[j].w;
+                if (kk == 0) al = cscale(sigma[j * NR + r], a);
+                else {
+                    const double2 w = cscale(mu[j * NR + r], a);
+                    al = kk == 1 ? cscale(w, nv.z) : cmul(w, cmk(0.5 * nv.x, kk == 2 ? -0.5 * nv.y : 0.5 * nv.y));
+                }
             }
-#pragma unroll
-            for (int rr = 0; rr < NR; ++rr) {
-                const double2 q = cscale(pq[rr], c.w), w = cscale(pw[rr], c.w);
-                al[(tid * 4) * NR + rr] = q;
-                al[(tid * 4 + 1) * NR + rr] = cscale(w, nv.z);
-                al[(tid * 4 + 2) * NR + rr] = cmul(w, cmk(0.5 * nv.x, -0.5 * nv.y));
-                al[(tid * 4 + 3) * NR + rr] = cmul(w, cmk(0.5 * nv.x, 0.5 * nv.y));
-            }
+            W[s * NC + 2 * rk] = al.x;
+            W[s * NC + 2 * rk + 1] = al.y;
         }
         __syncthreads();
-        fetch(j0 + CH);
-        for (int w = tid; w < cnt * npair; w += blockDim.x) {
+        for (int w = tid; w < cnt * npair; w += 256) {
             const int s = w / npair, pr = w - s * npair;
             const double ct = cth[s];
             const double *js = jb + s * (p + 2);
-            double *out = Rb + s * TB;
+            double *out = Rb + s * LDR;
             for (int h = 0; h < 2; ++h) {
                 const int mp = h == 0 ? pr : p - pr;
                 if (h == 1 && mp == pr) break;
-                double P1 = lt[3 * leg_tri(mp, mp) + 2], P2 = 0.0;
-                out[leg_tri(mp, mp)] = js[mp] * P1;
+                int t = leg_tri(mp, mp);
+                double P1 = lt[3 * t + 2], P2 = 0.0;
+                out[t] = js[mp] * P1;
+#pragma unroll 4
                 for (int n = mp + 1; n <= p; ++n) {
-                    const int t = leg_tri(n, mp);
+                    t += n;
                     const double P = fma(lt[3 * t] * ct, P1, -lt[3 * t + 1] * P2);
                     P2 = P1;
                     P1 = P;
@@ -1430,50 +1529,66 @@ __global__ void __launch_bounds__(256) k_p2m(int nleaf, int p, int CH, const int
                 }
             }
         }
+        if (tid >= 128)
+            for (int e = tid - 128; e < cnt * npad; e += 128) Rb[e / npad * LDR + TB + e % npad] = 0.0;
         __syncthreads();
-        if (tid < TB)
-            for (int s = 0; s < cnt; ++s) {
-                const double2 B = cscale(E[s * p1 + sm], Rb[s * TB + tid]);
+        for (int i = 0; i < gp; i += 4) {
+            const int s = min(i + kq, cnt - 1);  // past the group: a zero row of W
+            double bv[NCB];
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+            for (int cb = 0; cb < NCB; ++cb) bv[cb] = W[(i + kq) * NC + 16 * cb + l16];
+            const double *Rs = Rb + s * LDR, *Es = E + s * p1 * 2;
 #pragma unroll
-                    for (int rr = 0; rr < NR; ++rr) {
-                        const double2 a = al[(s * 4 + q) * NR + rr];
-                        acc[q][rr][0] = fma(a.x, B.x, acc[q][rr][0]);
-                        acc[q][rr][1] = fma(a.y, B.y, acc[q][rr][1]);
-                        acc[q][rr][2] = fma(a.x, B.y, acc[q][rr][2]);
-                        acc[q][rr][3] = fma(a.y, B.x, acc[q][rr][3]);
-                    }
+            for (int q = 0; q < NBW; ++q) {
+                const double av = Rs[slot[q]] * Es[eo[q]];
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb)
+                    acc[q][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[cb], acc[q][cb], 0, 0, 0);
             }
+        }
     }
-    // coefficient c = seven factor-weighted slot sums (entry i of term t from sum type k(t):
-    // t = 0 monopole, 1-2 n_z d_z, 3-4 (d_x + i d_y), 5-6 (d_x - i d_y)), one vector at a time
-    const int kt[7] = {0, 1, 1, 2, 2, 3, 3};
+    // coefficient c = seven factor-weighted slot sums (term t from weight kt(t): t = 0 monopole, 1-2
+    // n_z d_z, 3-4 (d_x + i d_y), 5-6 (d_x - i d_y)), VP vectors at a time
+    const double *tf = tab;
+    const int32_t *tslot = (const int32_t *)(tab + 7 * cap);
     const int ncoef = p * p;
-    double2 *Mb = Mout + (int64_t)b * NR * ncoef;
+    CO *Mb = Mout + (int64_t)b * NR * ncoef;
 #pragma unroll
-    for (int rr = 0; rr < NR; ++rr) {
+    for (int v0 = 0; v0 < NR; v0 += VP) {
         __syncthreads();
-        if (tid < TB)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const double A = acc[q][rr][0], Bq = acc[q][rr][1], Cq = acc[q][rr][2], D = acc[q][rr][3];
-                SL[(2 * q) * TS + tid] = cmk(A - Bq, Cq + D);      // sum al_k R
-                SL[(2 * q + 1) * TS + tid] = cmk(A + Bq, Cq - D);  // sum conj(al_k) R
+        for (int q = 0; q < NBW; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = 16 * (wv + 4 * q) + kq + 4 * i, col = l16 - 8 * (v0 & 1);
+                if (row < 2 * TBP && col >= 0 && col < 8 * VP) Dl[row * LDD + col] = acc[q][v0 >> 1][i];
             }
-        if (tid < 8) SL[tid * TS + TB] = cmk(0.0, 0.0);
         __syncthreads();
-        for (int c = tid; c < ncoef; c += blockDim.x) {
-            P2mTerms T;
-            p2m_terms(p, TB, c, k, T);
-            double2 a = cmk(0, 0);
+        for (int c = tid; c < ncoef; c += 256) {
+            double2 a[VP];
+#pragma unroll
+            for (int v = 0; v < VP; ++v) a[v] = cmk(0.0, 0.0);
 #pragma unroll
             for (int t = 0; t < 7; ++t) {
-                const bool cj = T.fy[t] != T.fx[t];  // conjugated entry: conj of the Q sum
-                const double2 v = SL[(2 * kt[t] + (cj ? 1 : 0)) * TS + T.i[t]];
-                a = cadd(a, cmk(T.fx[t] * v.x, T.fy[t] * v.y));
+                const int kt = (t + 1) >> 1;
+                const double f = t == 0 ? 1.0 : k * tf[t * cap + c];
+                const int sl = tslot[t * cap + c];
+                const double sg = sl & 1 ? -1.0 : 1.0;
+                const double *x = Dl + (sl >> 1) * LDD + 2 * kt, *y = x + TBP * LDD;
+#pragma unroll
+                for (int v = 0; v < VP; ++v) {
+                    // P = (A - B, C + D), conj(Q) = (A + B, -(C - D))
+                    a[v].x = fma(f, x[8 * v] - sg * y[8 * v + 1], a[v].x);
+                    a[v].y = fma(f, sg * y[8 * v] + x[8 * v + 1], a[v].y);
+                }
             }
-            Mb[rr * ncoef + c] = cmuli(cscale(a, k));  // i k sum
+#pragma unroll
+            for (int v = 0; v < VP; ++v) {  // i k sum
+                CO o;
+                o.x = -k * a[v].y;
+                o.y = k * a[v].x;
+                Mb[(v0 + v) * ncoef + c] = o;
+            }
         }
     }
 }
@@ -2178,44 +2293,51 @@ size_t p2m_stage_bytes(int nr, int p) {
 }
 size_t p2m_fixed_bytes(int p) { return (size_t)3 * (p + 1) * (p + 2) / 2 * sizeof(double); }
 
-// LDS of the slot-owner kernel: per staged source E (p+1 complex), the weights (4 NR complex), the
-// real basis (TB), j_n (p+2) and cos(th); the recurrence table; the slot sums of one vector
-// ([8][TB+1] complex) reuse the staging area after the last chunk.
-static size_t p2m_slot_stage(int nr, int p) {
-    const int TB = (p + 1) * (p + 2) / 2;
-    return (size_t)(p + 1) * 16 + (size_t)nr * 64 + (size_t)TB * 8 + (size_t)(p + 2) * 8 + 8;
+static bool p2m_slot_ok(int p) { return (p + 1) * (p + 2) / 2 <= P2M_SLOTS; }
+// the largest group of sources with four (one vector) or three workgroups per CU (the registers
+// allow no more: three instead of four costs one vector 625 -> 694 us, four instead of three costs
+// four vectors 990 -> 1,414 us)
+static int p2m_group(int nr, int p, size_t &sh) {
+    int G = 64;
+    while (G > 4 && P2mLayout(p, G, nr).total * sizeof(double) > 163840 / (nr > 1 ? 3 : 4)) --G;
+    sh = P2mLayout(p, G, nr).total * sizeof(double);
+    return G;
 }
-static bool p2m_slot_ok(int p) { return (p + 1) * (p + 2) / 2 <= 256; }
-static int p2m_slot_chunk(int nr, int p, size_t &sh) {
-    const int TB = (p + 1) * (p + 2) / 2;
-    const size_t per = p2m_slot_stage(nr, p), fixed = (size_t)(3 * TB + 2 * BS_TERMS) * 8, sums = (size_t)8 * (TB + 1) * 16;
-    // about 40 KB per workgroup (four resident per CU), at least the slot sums' area
-    int CH = (int)std::max<size_t>(1, std::min<size_t>(64, (40000 - std::min<size_t>(fixed, 39000)) / per));
-    while ((size_t)CH * per < sums) ++CH;
-    sh = (size_t)CH * per + fixed;
-    return CH;
+bool p2m_writes_fp32(int p) { return p2m_slot_ok(p); }
+void build_p2m_table(double *tab, hipStream_t st) {
+    k_p2m_table<<<ceil_div(P2M_CAP, 64), 64, 0, st>>>(tab);
+    LAUNCH_OK();
 }
 
 bool p2m_fits(int nr, int p) {
     if (p2m_slot_ok(p)) {
         size_t sh;
-        p2m_slot_chunk(nr, p, sh);
+        p2m_group(nr, p, sh);
         return sh <= 65536;
     }
     return p2m_stage_bytes(nr, p) + p2m_fixed_bytes(p) <= 60000;
 }
 
+// Mout: the multipoles; M32 instead (FP32, Mout unused) where p2m_writes_fp32(p)
 void launch_p2m(int nr, int nleaf, int p, const int32_t *leaf_start, const double4 *center, const double4 *ec,
                 const double4 *en, const double2 *sigma, const double2 *mu, double k, const double *leg,
-                double2 *Mout, hipStream_t st) {
+                const double *tab, double2 *Mout, float2 *M32, hipStream_t st) {
     if (nleaf <= 0) return;
     if (p2m_slot_ok(p)) {
         size_t sh;
-        const int CH = p2m_slot_chunk(nr, p, sh);
-#define P2M_CALL(R) \
-    k_p2m<R><<<nleaf, 256, sh, st>>>(nleaf, p, CH, leaf_start, center, ec, en, sigma, mu, k, leg, Mout)
+        const int G = p2m_group(nr, p, sh);
+        const int nbw = (P2mLayout(p, G, nr).TBP / 8 + 3) / 4;  // 16-row blocks per wavefront
+#define P2M_CALL2(R, B)                                                                                               \
+    if (M32) k_p2m<R, B, float2><<<nleaf, 256, sh, st>>>(p, G, leaf_start, center, ec, en, sigma, mu, k, 1.0 / k, leg, \
+                                                         tab, M32);                                                   \
+    else k_p2m<R, B, double2><<<nleaf, 256, sh, st>>>(p, G, leaf_start, center, ec, en, sigma, mu, k, 1.0 / k, leg,    \
+                                                      tab, Mout)
+#define P2M_CALL(R)                 \
+    if (nbw <= 5) { P2M_CALL2(R, 5); } \
+    else { P2M_CALL2(R, 8); }
         FMM_NR_DISPATCH(nr, P2M_CALL)
 #undef P2M_CALL
+#undef P2M_CALL2
     } else {
         const size_t per = p2m_stage_bytes(nr, p), fixed = p2m_fixed_bytes(p);
         const int CH = (int)std::max<size_t>(1, std::min<size_t>(32, (60000 - fixed) / per));

@@ -159,6 +159,9 @@ constexpr int SEG_ALIGN = 8;
 // field at points: workgroups wanted before the elements are left in one piece, and the most partial
 // sums a call writes (2 MiB)
 constexpr int64_t FIELD_WGS = 8192, FIELD_PART = (int64_t)1 << 17;
+// tables of P2M (p <= 21): coefficients, series terms, offset of the series and size in doubles
+constexpr int P2M_PMAX = 21, P2M_CAP = (P2M_PMAX * P2M_PMAX + 1) / 2 * 2, P2M_SER = 24, P2M_OSER = 7 * P2M_CAP + 7 * P2M_CAP / 2;
+constexpr int P2M_SLOTS = 256, P2M_OORD = P2M_OSER + (P2M_PMAX + 1) * P2M_SER, P2M_TABLE = P2M_OORD + P2M_SLOTS / 2;
 // up to four monopole sources of one right-hand side pass
 struct Monopoles {
     double rs[4][3];
