@@ -49,11 +49,6 @@ __global__ void k_scale_beta(int64_t, const int32_t *, const double2 *, int, con
 __global__ void k_diag_bm_inv(int64_t, const int32_t *, const int32_t *, const int32_t *, const double2 *,
                               const double2 *, const double2 *, const double2 *, const double2 *, double, double2,
                               double, double2 *);
-__global__ void k_local_derivs(int64_t, int, const double2 *, double, double2 *, double2 *, double2 *);
-__global__ void k_l2p_n(int, int, const int32_t *, const double4 *, const double4 *, const double4 *, const double2 *,
-                        const double2 *, const double2 *, const double2 *, double, const double *, const double2 *,
-                        const double2 *, int, const int32_t *, int64_t, const double2 *, const double2 *, const double2 *,
-                        double2 *, int);
 __global__ void k_diag2_inv(int64_t, const int32_t *, const int32_t *, const double2 *, const double2 *,
                             const double2 *, const double2 *, double, double, double2 *);
 __global__ void k_mul_diag2(int64_t, const int32_t *, const double2 *, const double2 *, double2 *);
@@ -73,11 +68,15 @@ void launch_p2m(int nr, int nleaf, int p, const int32_t *leaf_start, const doubl
 bool p2m_writes_fp32(int p);
 void build_p2m_table(double *tab, hipStream_t st);
 void launch_l2p(int nr, int nleaf, int p, const int32_t *leaf_start, const double4 *center, const double4 *ec,
-                const double2 *Lc, double k, const double *leg, const double2 *ynear, int nsplit,
-                double half, const int32_t *perm, int64_t n, const double2 *x, double2 *y, int has_far,
-                hipStream_t st);
+                const double2 *Lc, const float2 *L32, double k, const double *leg, const double *tab,
+                const double2 *ynear, int nsplit, double half, const int32_t *perm, int64_t n, const double2 *x,
+                double2 *y, int has_far, hipStream_t st);
+void launch_l2p_n(int nleaf, int p, const int32_t *leaf_start, const double4 *center, const double4 *ec,
+                  const double4 *en, const double2 *Lc, const float2 *L32, double2 *E, double k, const double *leg,
+                  const double *tab, const double2 *ynear, const double2 *ynearn, int nsplit, const int32_t *perm,
+                  int64_t n, const double2 *x, const double2 *bm, const double2 *bp, double2 *y, int has_far,
+                  hipStream_t st);
 __global__ void k_cvt_d2f(int64_t, const double2 *, float2 *);
-__global__ void k_cvt_f2d(int64_t, const float2 *, double2 *);
 __global__ void k_cvt_real_d2f(int64_t, const double *, float *);
 void launch_field(int64_t nt, int64_t nr, const FieldTree &tree, const double *pts, const double4 *ec,
                   const double4 *en, const double *ev, const double2 *sigma, const double2 *mu, double k, double rc2,
@@ -898,12 +897,6 @@ void convert<double2, float2>(fmmbem_ctx *c, int64_t n, const double2 *a, float2
     LAUNCH_OK();
 }
 template <>
-void convert<float2, double2>(fmmbem_ctx *c, int64_t n, const float2 *a, double2 *b) {
-    if (n <= 0) return;
-    k_cvt_f2d<<<ceil_div(n, 256), 256, 0, c->cur>>>(n, a, b);
-    LAUNCH_OK();
-}
-template <>
 void convert<double, float>(fmmbem_ctx *c, int64_t n, const double *a, float *b) {
     if (n <= 0) return;
     k_cvt_real_d2f<<<ceil_div(n, 256), 256, 0, c->cur>>>(n, a, b);
@@ -1134,11 +1127,6 @@ static void fmm_pass(fmmbem_ctx *c, int nr, const double2 *sigma, const double2 
         rec(c, 3);
         if (mixed) far_field<float>(c, nr, true, near_field);
         else far_field<double>(c, nr, false, near_field);
-        if (mixed) {
-            pe = prof_begin(c);
-            convert(c, (int64_t)LL.nbox * nr * pp, (const float2 *)LL.L32, LL.L);
-            prof_end(c, pe, "k_cvt", 0.0, 24.0 * LL.nbox * pp * nr);
-        }
         rec(c, 5);
     } else {
         for (int e = 3; e <= 5; ++e) rec(c, e);
@@ -1146,8 +1134,8 @@ static void fmm_pass(fmmbem_ctx *c, int nr, const double2 *sigma, const double2 
     rec(c, 6);
     LevelDev &LL = c->lev[L];
     pe = prof_begin(c);
-    launch_l2p(nr, nleaf, LL.p, I32("leaf_start"), LL.center, ec, LL.L, c->k, leg_table(c), ynear, nsplit,
-               half, I32("perm"), n, x, y, exact_far ? 0 : 1, A);
+    launch_l2p(nr, nleaf, LL.p, I32("leaf_start"), LL.center, ec, LL.L, mixed ? LL.L32 : nullptr, c->k, leg_table(c),
+               (double *)c->buf.find("p2mtab"), ynear, nsplit, half, I32("perm"), n, x, y, exact_far ? 0 : 1, A);
     prof_end(c, pe, "k_l2p", (double)n * LL.p * LL.p * 8.0 * nr,
              32.0 * n + 16.0 * n * 3 * nr + 16.0 * nleaf * LL.p * LL.p * nr);
     rec(c, 7);
@@ -1349,8 +1337,7 @@ static void fmm_pass_ind(fmmbem_ctx *c, const double2 *sigma, const double2 *mu,
     LevelDev &LL = c->lev[L];
     const int p = LL.p;
     const size_t q1 = (size_t)(p + 1) * (p + 1), pp = (size_t)p * p;
-    double2 *Dz = dget<double2>(c->scratch, "ind_Dz", LL.nbox * q1), *Dp = dget<double2>(c->scratch, "ind_Dp", LL.nbox * q1),
-            *Dm = dget<double2>(c->scratch, "ind_Dm", LL.nbox * q1);
+    double2 *E = dget<double2>(c->scratch, "ind_D", 4 * LL.nbox * q1);
     if (!exact_far) {
         pe = prof_begin(c);
         check_p2m(1, p);
@@ -1364,21 +1351,15 @@ static void fmm_pass_ind(fmmbem_ctx *c, const double2 *sigma, const double2 *mu,
                 prof_end(c, pe, "k_cvt", 0.0, 24.0 * LL.nbox * pp);
             }
             far_field<float>(c, 1, true);
-            pe = prof_begin(c);
-            convert(c, (int64_t)LL.nbox * pp, (const float2 *)LL.L32, LL.L);
-            prof_end(c, pe, "k_cvt", 0.0, 24.0 * LL.nbox * pp);
         } else {
             far_field<double>(c, 1, false);
         }
-        // the far field's join made the main stream wait for the side stream (near field included)
-        k_local_derivs<<<nleaf, 256, 0, A>>>(nleaf, p, LL.L, c->k, Dz, Dp, Dm);
-        LAUNCH_OK();
     }
+    // the far field's join made the main stream wait for the side stream (near field included)
     pe = prof_begin(c);
-    k_l2p_n<<<nleaf, 64, ((size_t)64 * (p + 3) + (size_t)3 * (p + 1) * (p + 2) / 2) * sizeof(double), A>>>(
-        nleaf, p, I32("leaf_start"), LL.center, ec, en, LL.L, Dz, Dp, Dm, c->k, leg_table(c), yv, yn, nsplit, I32("perm"), n, x,
-        (double2 *)c->buf.find("beta"), (double2 *)c->buf.find("betap"), y, exact_far ? 0 : 1);
-    LAUNCH_OK();
+    launch_l2p_n(nleaf, p, I32("leaf_start"), LL.center, ec, en, LL.L, mixed ? LL.L32 : nullptr, E, c->k, leg_table(c),
+                 (double *)c->buf.find("p2mtab"), yv, yn, nsplit, I32("perm"), n, x, (double2 *)c->buf.find("beta"),
+                 (double2 *)c->buf.find("betap"), y, exact_far ? 0 : 1, A);
     prof_end(c, pe, "k_l2p_n", (double)n * q1 * 8.0 * 4, 0.0);
 }
 

@@ -934,10 +934,6 @@ __global__ void k_cvt_d2f(int64_t n, const double2 *a, float2 *b) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) b[i] = make_float2((float)a[i].x, (float)a[i].y);
 }
-__global__ void k_cvt_f2d(int64_t n, const float2 *a, double2 *b) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) b[i] = make_double2(a[i].x, a[i].y);
-}
 __global__ void k_cvt_real_d2f(int64_t n, const double *a, float *b) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) b[i] = (float)a[i];
@@ -964,11 +960,10 @@ __device__ inline double jn_series(int n, double h, int kmax) {
     return s;
 }
 
-// j_0(x) .. j_N(x), x >= 0.  Small x: every order from its series (orders that underflow are
-// zero to working precision).  x < 4 and N <= 40: j_N and j_{N-1} from their series, then the
-// downward recurrence j_{n-1} = (2n+1)/x j_n - j_{n+1}, which is stable for this (minimal)
-// solution.  Otherwise Miller's normalised recurrence.
-__device__ inline void bessel_j_seq(double x, int N, double *j) {
+// j_0(x) .. j_N(x), 0 <= x < 4, N <= 40.  Small x: every order from its series (orders that
+// underflow are zero to working precision).  Otherwise j_N and j_{N-1} from their series, then the
+// downward recurrence j_{n-1} = (2n+1)/x j_n - j_{n+1}, which is stable for this (minimal) solution.
+__device__ inline void bessel_j_small(double x, int N, double *j) {
     const double h = -0.5 * x * x;
     if (x < 1e-2) {
         double pre = 1.0;  // x^n / (2n+1)!!
@@ -976,10 +971,6 @@ __device__ inline void bessel_j_seq(double x, int N, double *j) {
             if (n > 0) pre *= x * rcp_nr(2.0 * n + 1.0);
             j[n] = pre * jn_series(n, h, 6);
         }
-        return;
-    }
-    if (x >= 4.0 || N > 40) {
-        sph_jn_seq(x, N, j);
         return;
     }
     if (N == 0) {
@@ -1003,6 +994,12 @@ __device__ inline void bessel_j_seq(double x, int N, double *j) {
         jh = jl;
         jl = jm;
     }
+}
+
+// j_0(x) .. j_N(x), x >= 0: bessel_j_small, or Miller's normalised recurrence
+__device__ inline void bessel_j_seq(double x, int N, double *j) {
+    if (x < 1e-2 || (x < 4.0 && N <= 40)) bessel_j_small(x, N, j);
+    else sph_jn_seq(x, N, j);
 }
 
 // spherical coordinates of (dx, dy, dz) about the expansion centre: r, cos/sin of the polar
@@ -1252,7 +1249,7 @@ __global__ void __launch_bounds__(256) k_p2m_wide(int nleaf, int p, int CH, cons
 // worst relative error, near zeros of j_n, as starting 40 + 4 sqrt(max(N, x) + 1) above).
 __device__ inline void bessel_j_seq_fast(double x, int N, double *j) {
     if (x < 4.0 && N <= 40) {
-        bessel_j_seq(x, N, j);
+        bessel_j_small(x, N, j);
         return;
     }
     const int top = N > (int)x ? N : (int)x;
@@ -1277,56 +1274,9 @@ __device__ inline void bessel_j_seq_fast(double x, int N, double *j) {
     for (int n = 0; n <= N; ++n) j[n] *= scale;
 }
 
-// Coefficients of the power series of x^{-n} (2n+1)!! j_n(x) (t_q = t_{q-1} h c_q) for the orders N
-// and N - 1: c[o BS_TERMS + q - 1] = 1 / (q (2n + 2q + 1)), n = N - o, q = 1 .. BS_TERMS.  Computed
-// once per workgroup, so that each series term costs two multiplications.
-constexpr int BS_TERMS = 40;
-__device__ inline void bessel_series_coeffs(int N, double *c, int tid, int nthreads) {
-    for (int e = tid; e < 2 * BS_TERMS; e += nthreads) {
-        const int o = e / BS_TERMS, q = e % BS_TERMS + 1, n = N - o;
-        c[e] = 1.0 / ((double)q * (2.0 * n + 2.0 * q + 1.0));
-    }
-}
-
-// j_0(x) .. j_N(x): for 1e-2 <= x < 4 and 1 <= N <= 40 the method of bessel_j_seq (j_N and j_{N-1}
-// from their series, then the downward recurrence) with both series summed in one loop from the
-// coefficients c of bessel_series_coeffs(N); otherwise bessel_j_seq_fast.
-__device__ inline void bessel_j_seq_tab(double x, int N, double *j, const double *c) {
-    if (x < 1e-2 || x >= 4.0 || N > 40 || N < 1) {
-        bessel_j_seq_fast(x, N, j);
-        return;
-    }
-    const double h = -0.5 * x * x;
-    double sh = 1.0, th = 1.0, sl = 1.0, tl = 1.0;  // orders N and N - 1
-    for (int q = 0; q < BS_TERMS; ++q) {
-        th *= h * c[q];
-        tl *= h * c[BS_TERMS + q];
-        sh += th;
-        sl += tl;
-        if (fabs(th) <= 1e-17 * fabs(sh) && fabs(tl) <= 1e-17 * fabs(sl)) break;
-    }
-    double xn = 1.0, df = 1.0;  // x^{N-1} and (2N-1)!!
-    for (int n = 1; n < N; ++n) {
-        xn *= x;
-        df *= 2.0 * n + 1.0;
-    }
-    const double pre = xn / df;
-    double jh = pre * x / (2.0 * N + 1.0) * sh;
-    double jl = pre * sl;
-    j[N] = jh;
-    j[N - 1] = jl;
-    const double ix = 1.0 / x;
-    for (int n = N - 1; n >= 1; --n) {
-        const double jm = fma((2.0 * n + 1.0) * ix, jl, -jh);
-        j[n - 1] = jm;
-        jh = jl;
-        jl = jm;
-    }
-}
-
 // Constant tables of P2M (P2M_TABLE doubles): the seven terms of every coefficient c < P2M_CAP
 // (p2m_terms without the factor k, independent of p) as factors f[7][cap] and int32 slots[7][cap] =
-// 2 slot + (conjugated entry), a missing entry with factor 0; the Bessel series, for n <= P2M_PMAX
+// 2 slot + (conjugated entry), a missing entry with factor 0; the Bessel series, for n <= SER_NMAX
 // ser[n][q - 1] = 1 / (q (2n + 2q + 1)) and, last in the row, 1 / (2n + 1)!!; the orders of the slots.
 __global__ void k_p2m_table(double *tab) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x, cap = P2M_CAP;
@@ -1341,31 +1291,37 @@ __global__ void k_p2m_table(double *tab) {
             slot[t * cap + c] = T.i[t] == none ? 0 : 2 * T.i[t] + (T.fy[t] != T.fx[t]);
         }
     }
-    if (c <= P2M_PMAX) {
+    if (c <= SER_NMAX) {
         double df = 1.0;
         for (int q = 1; q <= c; ++q) df *= 2.0 * q + 1.0;
         for (int q = 1; q < P2M_SER; ++q) ser[c * P2M_SER + q - 1] = 1.0 / ((double)q * (2.0 * c + 2.0 * q + 1.0));
         ser[c * P2M_SER + P2M_SER - 1] = 1.0 / df;
+    }
+    if (c <= P2M_PMAX) {
         for (int m = 0; m <= c; ++m) order[leg_tri(c, m)] = m;
         for (int t = leg_tri(P2M_PMAX + 1, 0) + c; t < P2M_SLOTS; t += P2M_PMAX + 1) order[t] = 0;
     }
 }
 
-// x^m by squaring, m < 32
+// x^m by squaring, m < 64
 __device__ inline double pow_small(double x, int m) {
     double r = m & 1 ? x : 1.0;
-    for (int b = 1; b < 5; ++b) {
+    for (int b = 1; b < 6; ++b) {
         x *= x;
         r = (m >> b) & 1 ? r * x : r;
     }
     return r;
 }
 
-// j_0(x) .. j_N(x), 1 <= N <= P2M_PMAX, by the method of bessel_j_seq: for 1e-2 <= x < 4 j_N and j_{N-1}
-// from their series (tables of the orders N - 1 and N, P2M_SER each, at ser) and the downward
-// recurrence; ix = 1 / x
-__device__ inline void bessel_j_seq_ser(double x, double ix, int N, double *j, const double *ser) {
-    if (x < 1e-2 || x >= 4.0) {
+// a read-only array whose elements are read by scalar loads where the index is the wavefront's
+typedef const __attribute__((address_space(4))) double *sc_f64;
+
+// j_0(x) .. j_N(x): for 1e-2 <= x < 4 and 1 <= N <= SER_NMAX the method of bessel_j_small with both
+// series summed in one loop from a table of the terms' factors (the rows of the orders N - 1 and N,
+// P2M_SER each, at ser); otherwise bessel_j_seq_fast.  ix = 1 / x.
+template <class SER>
+__device__ inline void bessel_j_seq_ser(double x, double ix, int N, double *j, SER ser) {
+    if (x < 1e-2 || x >= 4.0 || N < 1 || N > SER_NMAX) {
         bessel_j_seq_fast(x, N, j);
         return;
     }
@@ -1478,7 +1434,7 @@ k_p2m(int p, int G, const int32_t *leaf_start, const double4 *center, const doub
             const double ir = at ? 0.0 : rsq_nr(r2);
             if (wv == 0) {
                 cth[lane] = at ? 1.0 : dz * ir;
-                bessel_j_seq_ser(k * (r2 * ir), ik * ir, p, jb + lane * (p + 2), ser);
+                bessel_j_seq_ser(k * (r2 * ir), ik * ir, p, jb + lane * (p + 2), (const double *)ser);
             } else {
                 const double2 u = cmk(dx * ir, dy * ir);
                 double2 e = cmk(1.0, 0.0);
@@ -1594,110 +1550,204 @@ k_p2m(int p, int G, const int32_t *leaf_start, const double4 *center, const doub
 }
 
 // ------------------------------------------------------------------ L2P + combine
-// y[perm[i]] = half * x[perm[i]] + y_near[i] + sum_{n,m} D_n^m R_n^m(c_i - C).
-// One thread per target; the recurrence table and (STAGE) the leaf's expansions are staged in LDS
-// (every thread reads the same entry at once: broadcasts), the degree loop unrolled so that its
-// reads overlap.  Without STAGE (expansions too large for LDS) they are read from global memory.
-template <int NR, bool STAGE>
-__global__ void __launch_bounds__(64) k_l2p(int nleaf, int p, const int32_t *leaf_start, const double4 *center,
-                                            const double4 *ec, const double2 *Lc, double k, const double *leg,
-                                            const double2 *ynear, int nsplit, double half, const int32_t *perm,
-                                            int64_t n, const double2 *x, double2 *y, int has_far) {
-    extern __shared__ double2 l2p_sm[];
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const double4 C = center[b];
-    const int ts = leaf_start[b], te = leaf_start[b + 1];
-    const int pp = p * p, TB = p * (p + 1) / 2;
-    const double2 *Dg = Lc + (int64_t)b * NR * pp;   // NR expansions of this leaf
-    double2 *Dl = l2p_sm;
-    double *lt = STAGE ? (double *)(Dl + NR * pp) : (double *)l2p_sm;  // 3 TB: Legendre recurrence (degrees < p)
-    double *bc = lt + 3 * TB;                                           // series coefficients of j_{p-1}, j_{p-2}
-    double *jb = bc + 2 * BS_TERMS + tid * (p + 2);
-    const double2 *D = STAGE ? (const double2 *)Dl : Dg;
-    if (has_far) {
-        for (int e = tid; e < 3 * TB; e += blockDim.x) lt[e] = leg[e];
-        bessel_series_coeffs(p - 1, bc, tid, blockDim.x);
-        if (STAGE)
-            for (int e = tid; e < NR * pp; e += blockDim.x) Dl[e] = Dg[e];
-        __syncthreads();
+// One wavefront takes a leaf's targets (up to 16 TLM at a time).  First one target per lane: frame
+// and j_n(k r), to LDS.  Then 16 targets side by side, TL targets per lane, and the orders split over
+// the four groups of 16 lanes (group g takes m = g, g + 4, ...): an entry pair D_n^{+-m} and a
+// recurrence entry read from LDS serve TL points, which also hide each other's latency.  A butterfly
+// over the groups adds the orders, and group i finishes the lane's target i.  Bound by LDS reads (an
+// entry is the same for 16 lanes) and the FP64 instructions together, at 2 to 3 wavefronts per SIMD;
+// the orders' unequal lengths cost a sixth (p = 16: 40 steps where 34 would do).
+// Measured against one target per lane with the orders split over half-filled wavefronts only, and
+// FP32 expansions converted by another kernel, p = 16: 56 leaves of 48 targets 54 -> 20 us (four
+// workgroups per leaf), 3,416 leaves of 27 50 -> 37 us, 29,626 leaves of 34 330 -> 187 us, four vectors
+// in mixed precision on 29,626 leaves of 21 1,195 -> 452 us; with the normal derivative (four
+// expansions) 56 leaves 130 -> 38 us, 3,416 leaves 224 -> 116 us.  Three and two targets per lane (one
+// or two, four vectors): a target more costs 187 -> 215 and 452 -> 475 us, a wavefront more per SIMD (fewer
+// registers) 187 -> 314 and 452 -> 702 us.  Entries through the scalar cache, all lanes at the same
+// one: 259 and 1,345 us (its misses).
+
+constexpr int l2p_tlm(int nv) { return nv > 2 ? 2 : 3; }
+
+// LDS of k_l2p and k_l2p_n, degrees < p, NV expansions of elements T (STAGE: copied there); offsets
+// in bytes
+struct L2pLayout {
+    int JS, oF, oT, oS, oD, total;  // Bessel rows (stride JS); frames; recurrence pairs; seeds; expansions
+    __host__ __device__ L2pLayout(int p, int nt, size_t dbytes) {
+        JS = (p + 1) | 1;
+        oF = nt * JS * 8;
+        oT = (oF + nt * 24 + 15) & ~15;
+        oS = oT + p * (p + 1) / 2 * 16;
+        oD = (oS + p * 8 + 15) & ~15;
+        total = oD + (int)dbytes;
     }
-    // A leaf of at most 32 (16) targets splits the orders m over 2 (4) lane groups of 32 (16)
-    // targets, group g taking m = g, g + S, ..., and adds the groups' sums at the end (leaves hold
-    // about 34 targets on average: one target per lane leaves half the lanes idle)
-    __shared__ double2 red[64 * NR];
-    const int nt = te - ts, S = nt <= 16 ? 4 : (nt <= 32 ? 2 : 1), TP = 64 / S, g = tid / TP;
-    for (int t0 = ts; t0 < te; t0 += TP) {
-        const int t = t0 + tid % TP;
-        const bool act = t < te;
-        double2 far[NR];
+};
+
+// far[i][v] = this lane's orders of sum_{n < p, m} D_n^m R_n^m at its targets l + 16 i (of nt), NV
+// expansions ps entries apart, then summed over the four groups
+template <int NV, int TL, class T2>
+__device__ inline void l2p_sums(int p, int nt, const T2 *D, int ps, const double2 *lt, const double *seed,
+                                const double *jb, int JS, const double *fr, double2 (&far)[TL][NV]) {
+    const int lane = threadIdx.x & 63, g = lane >> 4;
+    double ct[TL];
+    double2 e[TL], u4[TL];
+    const double *jt[TL];
 #pragma unroll
-        for (int rr = 0; rr < NR; ++rr) far[rr] = cmk(0, 0);
-        if (has_far && act) {
-            const double4 c = ec[t];
-            double r, ct, st;
-            double2 eph;
-            sph_frame(c.x - C.x, c.y - C.y, c.z - C.z, r, ct, st, eph);
-            bessel_j_seq_tab(k * r, p - 1, jb, bc);
-            double2 e = cmk(1.0, 0.0);
-            double sp = 1.0;
-            for (int q = 0; q < g; ++q) {
-                e = cmul(e, eph);
-                sp *= st;
-            }
-            for (int mp = g; mp < p; mp += S) {
-                if (mp > g)
-                    for (int q = 0; q < S; ++q) {  // e^{i m phi} and sin^m by the same products as for S = 1
-                        e = cmul(e, eph);
-                        sp *= st;
-                    }
-                double P1 = lt[3 * leg_tri(mp, mp) + 2] * sp, P2 = 0.0;
-                double2 sa[NR], sb[NR];
+    for (int i = 0; i < TL; ++i) {
+        const int t = min((lane & 15) + 16 * i, nt - 1);
+        jt[i] = jb + t * JS;
+        ct[i] = fr[3 * t];
+        const double2 u = cmk(fr[3 * t + 1], fr[3 * t + 2]), u2 = cmul(u, u);
+        u4[i] = cmul(u2, u2);
+        e[i] = cmul(cmk(g & 1 ? u.x : 1.0, g & 1 ? u.y : 0.0), cmk(g & 2 ? u2.x : 1.0, g & 2 ? u2.y : 0.0));
 #pragma unroll
-                for (int rr = 0; rr < NR; ++rr) {
-                    sa[rr] = cscale(D[rr * pp + cidx(mp, mp)], jb[mp] * P1);
-                    sb[rr] = mp > 0 ? cscale(D[rr * pp + cidx(mp, -mp)], jb[mp] * P1) : cmk(0, 0);
+        for (int v = 0; v < NV; ++v) far[i][v] = cmk(0.0, 0.0);
+    }
+#pragma unroll 1
+    for (int m = g; m < p; m += 4) {
+        double P1[TL], P2[TL];
+        double2 sa[TL][NV], sb[TL][NV];  // orders m and -m
+        const double sd = seed[m];
+#pragma unroll
+        for (int i = 0; i < TL; ++i) {
+            P1[i] = sd;
+            P2[i] = 0.0;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) sa[i][v] = sb[i][v] = cmk(0.0, 0.0);
+        }
+        int q = leg_tri(m, m);
+        const T2 *Da = D + cidx(m, m), *Db = D + cidx(m, -m);
+#pragma unroll 1
+        for (int n = m;;) {
+            double R[TL];
+#pragma unroll
+            for (int i = 0; i < TL; ++i) R[i] = jt[i][n] * P1[i];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const T2 a = Da[v * ps], b = Db[v * ps];
+#pragma unroll
+                for (int i = 0; i < TL; ++i) {
+                    sa[i][v].x = fma((double)a.x, R[i], sa[i][v].x);
+                    sa[i][v].y = fma((double)a.y, R[i], sa[i][v].y);
+                    sb[i][v].x = fma((double)b.x, R[i], sb[i][v].x);
+                    sb[i][v].y = fma((double)b.y, R[i], sb[i][v].y);
                 }
+            }
+            if (++n >= p) break;
+            q += n;
+            Da += 2 * n;
+            Db += 2 * n;
+            const double2 ab = lt[q];
+#pragma unroll
+            for (int i = 0; i < TL; ++i) {
+                const double P = fma(ab.x * ct[i], P1[i], -ab.y * P2[i]);
+                P2[i] = P1[i];
+                P1[i] = P;
+            }
+        }
+        // sum_n D_n^m R e^{i m phi} + D_n^{-m} R e^{-i m phi}
+#pragma unroll
+        for (int i = 0; i < TL; ++i) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                far[i][v] = cfma(sa[i][v], e[i], far[i][v]);
+                if (m > 0) far[i][v] = cfma(sb[i][v], cconj(e[i]), far[i][v]);
+            }
+            e[i] = cmul(e[i], u4[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < TL; ++i)
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int o = 16; o < 64; o *= 2) {
+                far[i][v].x += __shfl_xor(far[i][v].x, o);
+                far[i][v].y += __shfl_xor(far[i][v].y, o);
+            }
+}
+
+// sum of the near field's pieces at t
+__device__ inline double2 near_sum(const double2 *y, int64_t t, int64_t stride, int nsplit) {
+    double2 v = y[t];
 #pragma unroll 4
-                for (int nn = mp + 1; nn < p; ++nn) {
-                    const int q = leg_tri(nn, mp);
-                    const double P = fma(lt[3 * q] * ct, P1, -lt[3 * q + 1] * P2);
-                    P2 = P1;
-                    P1 = P;
-                    const double R = jb[nn] * P;
-#pragma unroll
-                    for (int rr = 0; rr < NR; ++rr) {
-                        sa[rr] = cadd(sa[rr], cscale(D[rr * pp + cidx(nn, mp)], R));
-                        if (mp > 0) sb[rr] = cadd(sb[rr], cscale(D[rr * pp + cidx(nn, -mp)], R));
-                    }
-                }
-                // sum_n D_n^m R e^{i m phi} + D_n^{-m} R e^{-i m phi}
-#pragma unroll
-                for (int rr = 0; rr < NR; ++rr) {
-                    far[rr] = cfma(sa[rr], e, far[rr]);
-                    if (mp > 0) far[rr] = cfma(sb[rr], cconj(e), far[rr]);
-                }
-            }
+    for (int g = 1; g < nsplit; ++g) v = cadd(v, y[g * stride + t]);
+    return v;
+}
+
+// the far field of a leaf's targets in chunks: fin(t, far) for every target t with its NV sums.
+// Workgroup y of gy takes the chunks y, y + gy, ...; a chunk holds at most cs <= 16 TLM targets.
+template <int NV, bool STAGE, class T2, class FIN>
+__device__ inline void l2p_leaf(int p, int cs, int ts, int te, double4 C, const double4 *ec, const T2 *Dg, double k,
+                                double ik, const double *leg, const double *ser, char *sm, FIN fin) {
+    constexpr int TLM = l2p_tlm(NV);
+    const int tid = threadIdx.x, pp = p * p, TB = p * (p + 1) / 2;
+    const L2pLayout Y(p, cs, STAGE ? (size_t)NV * pp * sizeof(T2) : 0);
+    double *jb = (double *)sm, *fr = (double *)(sm + Y.oF), *seed = (double *)(sm + Y.oS);
+    double2 *lt = (double2 *)(sm + Y.oT);
+    T2 *Dl = (T2 *)(sm + Y.oD);
+    const int nch = (te - ts + cs - 1) / cs, size = (te - ts + nch - 1) / nch;
+    if ((int)blockIdx.y >= nch) return;
+    if (STAGE)
+        for (int e = tid; e < NV * pp; e += 64) Dl[e] = Dg[e];
+    for (int e = tid; e < TB; e += 64) lt[e] = cmk(leg[3 * e], leg[3 * e + 1]);
+    for (int m = tid; m < p; m += 64) seed[m] = leg[3 * leg_tri(m, m) + 2];
+    const T2 *D = STAGE ? (const T2 *)Dl : Dg;
+    for (int ch = blockIdx.y; ch < nch; ch += gridDim.y) {
+        const int t0 = ts + ch * size, nt = min(size, te - t0);
+        if (nt <= 0) break;
+        __syncthreads();
+        if (tid < nt) {
+            const double4 c = ec[t0 + tid];
+            const double dx = c.x - C.x, dy = c.y - C.y, dz = c.z - C.z, r2 = dx * dx + dy * dy + dz * dz;
+            const bool at = r2 < 1e-280;  // at the centre: theta = 0
+            const double ir = at ? 0.0 : rsq_nr(r2);
+            fr[3 * tid] = at ? 1.0 : dz * ir;
+            fr[3 * tid + 1] = dx * ir;
+            fr[3 * tid + 2] = dy * ir;
+            bessel_j_seq_ser(k * (r2 * ir), ik * ir, p - 1, jb + tid * Y.JS, (sc_f64)ser + max(p - 2, 0) * P2M_SER);
         }
-        if (S > 1) {  // group 0 adds the other groups' sums
-            __syncthreads();
+        __syncthreads();
+        auto run = [&](auto tl) {
+            constexpr int TL = decltype(tl)::value;
+            double2 far[TL][NV];
+            l2p_sums<NV, TL>(p, nt, D, pp, lt, seed, jb, Y.JS, fr, far);
 #pragma unroll
-            for (int rr = 0; rr < NR; ++rr) red[tid * NR + rr] = far[rr];
-            __syncthreads();
-            if (g == 0)
-                for (int gg = 1; gg < S; ++gg)
-#pragma unroll
-                    for (int rr = 0; rr < NR; ++rr) far[rr] = cadd(far[rr], red[(tid + gg * TP) * NR + rr]);
-        }
-        if (!act || g > 0) continue;
+            for (int i = 0; i < TL; ++i)
+                if ((tid >> 4) == i && tid < nt) fin(t0 + tid, far[i]);
+        };
+        if (nt <= 16) run(std::integral_constant<int, 1>());
+        else if (TLM == 2 || nt <= 32) run(std::integral_constant<int, 2>());
+        else if constexpr (TLM > 2) run(std::integral_constant<int, 3>());
+    }
+}
+
+// y[perm[i]] = half * x[perm[i]] + y_near[i] + sum_{n,m} D_n^m R_n^m(c_i - C); T2: entry of the
+// expansions (float2 where the translations ran in FP32).  Without STAGE (expansions too large for
+// LDS) they are read from global memory.
+template <int NR, bool STAGE, class T2>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NR > 1 ? 2 : 3)))
+k_l2p(int p, int cs, const int32_t *leaf_start, const double4 *center,
+                                            const double4 *ec, const T2 *Lc, double k, double ik, const double *leg,
+                                            const double *ser, const double2 *ynear, int nsplit, double half,
+                                            const int32_t *perm, int64_t n, const double2 *x, double2 *y, int has_far) {
+    extern __shared__ char l2p_sm[];
+    const int b = blockIdx.x, ts = leaf_start[b], te = leaf_start[b + 1];
+    auto fin = [&](int t, const double2 *far) {
         const int64_t u = perm[t];
 #pragma unroll
-        for (int rr = 0; rr < NR; ++rr) {
-            double2 v = ynear[(int64_t)t * NR + rr];
-            for (int g2 = 1; g2 < nsplit; ++g2) v = cadd(v, ynear[(g2 * n + t) * NR + rr]);
-            v = cadd(v, far[rr]);
-            if (x) v = cadd(v, cscale(x[rr * n + u], half));  // the right-hand side pass has no identity term
-            y[rr * n + u] = v;
+        for (int r = 0; r < NR; ++r) {
+            double2 v = cadd(near_sum(ynear + r, (int64_t)t * NR, n * NR, nsplit), far[r]);
+            if (x) v = cadd(v, cscale(x[r * n + u], half));  // the right-hand side pass has no identity term
+            y[r * n + u] = v;
         }
+    };
+    if (has_far) {
+        l2p_leaf<NR, STAGE>(p, cs, ts, te, center[b], ec, Lc + (int64_t)b * NR * p * p, k, ik, leg, ser, l2p_sm, fin);
+    } else {
+        double2 far[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) far[r] = cmk(0.0, 0.0);
+        for (int t = ts + threadIdx.x + 64 * blockIdx.y; t < te; t += 64 * gridDim.y) fin(t, far);
     }
 }
 
@@ -2038,15 +2088,19 @@ __global__ void k_bm_rhs(int64_t n, const int32_t *perm, const double2 *gam, dou
 // derivative local expansions of a leaf (degree p + 1) from its local expansion D (degree p):
 //   d_z R_n^m = k (a_{n-1}^m R_{n-1}^m - a_n^m R_{n+1}^m), etc. (the P2M recurrences), collected
 //   per output coefficient (n, m)
-__device__ inline double2 dget_nm(const double2 *D, int p, int n, int m) {
+template <class T>
+__device__ inline double2 dget_nm(const T *D, int p, int n, int m) {
     if (n < 0 || n >= p || (m < 0 ? -m : m) > n) return cmk(0, 0);
-    return D[cidx(n, m)];
+    const T d = D[cidx(n, m)];
+    return cmk(d.x, d.y);
 }
-__global__ void k_local_derivs(int64_t nleaf, int p, const double2 *D, double k, double2 *Dz, double2 *Dp,
-                               double2 *Dm) {
+// E: per leaf D itself (its degree p zero), then the z, + and - derivatives, (p + 1)^2 entries each
+template <class T>
+__global__ void k_local_derivs(int64_t nleaf, int p, const T *D, double k, double2 *E) {
     const int64_t b = blockIdx.x;
     const int q1 = (p + 1) * (p + 1);
-    const double2 *Db = D + b * p * p;
+    const T *Db = D + b * p * p;
+    E += b * 4 * q1;
     for (int c = threadIdx.x; c < q1; c += blockDim.x) {
         int n = (int)sqrt((double)c);
         while (n * n > c) --n;
@@ -2057,99 +2111,33 @@ __global__ void k_local_derivs(int64_t nleaf, int p, const double2 *D, double k,
                                 cscale(dget_nm(Db, p, n + 1, m - 1), coef_b(n + 1, m - 1)));
         const double2 mi = csub(cscale(dget_nm(Db, p, n - 1, m + 1), coef_b(n, m)),
                                 cscale(dget_nm(Db, p, n + 1, m + 1), coef_b(n + 1, -m - 1)));
-        Dz[b * q1 + c] = cscale(z, k);
-        Dp[b * q1 + c] = cscale(pl, k);
-        Dm[b * q1 + c] = cscale(mi, k);
+        E[c] = dget_nm(Db, p, n, m);
+        E[q1 + c] = cscale(z, k);
+        E[2 * q1 + c] = cscale(pl, k);
+        E[3 * q1 + c] = cscale(mi, k);
     }
 }
 
-// potential (local expansion D, degree p) and normal derivative (derivative expansions, degree
-// p + 1) at the targets, plus the near part and the local terms of both block rows
-__global__ void __launch_bounds__(64) k_l2p_n(int nleaf, int p, const int32_t *leaf_start, const double4 *center,
-                                              const double4 *ec, const double4 *en, const double2 *Lc,
-                                              const double2 *Dz, const double2 *Dp, const double2 *Dm, double k,
-                                              const double *leg, const double2 *ynear, const double2 *ynearn,
-                                              int nsplit, const int32_t *perm, int64_t n, const double2 *x, const double2 *bm, const double2 *bp,
-                                              double2 *y, int has_far) {
-    extern __shared__ double jbuf[];
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const double4 C = center[b];
-    const int ts = leaf_start[b], te = leaf_start[b + 1];
-    const int q1 = (p + 1) * (p + 1);
-    const double2 *D = Lc + (int64_t)b * p * p, *Ez = Dz + (int64_t)b * q1, *Ep = Dp + (int64_t)b * q1,
-                  *Em = Dm + (int64_t)b * q1;
-    const int TB = (p + 1) * (p + 2) / 2;
-    double *lt = jbuf;  // 3 TB: Legendre recurrence table (degrees <= p)
-    double *jb = jbuf + 3 * TB + tid * (p + 3);
-    if (has_far) {
-        for (int e = tid; e < 3 * TB; e += blockDim.x) lt[e] = leg[e];
-        __syncthreads();
-    }
-    for (int t = ts + tid; t < te; t += 64) {
-        double2 far = cmk(0, 0), fz = cmk(0, 0), fp = cmk(0, 0), fm = cmk(0, 0);
-        if (has_far) {
-            const double4 c = ec[t];
-            double r, ct, st;
-            double2 eph;
-            sph_frame(c.x - C.x, c.y - C.y, c.z - C.z, r, ct, st, eph);
-            bessel_j_seq(k * r, p, jb);
-            double2 e = cmk(1.0, 0.0);
-            double spw = 1.0;
-            for (int mp = 0; mp <= p; ++mp) {
-                if (mp > 0) {
-                    e = cmul(e, eph);
-                    spw *= st;
-                }
-                double pm1 = lt[3 * leg_tri(mp, mp) + 2] * spw, pm2 = 0.0;
-                double2 sv[2] = {cmk(0, 0), cmk(0, 0)}, sz_[2] = {cmk(0, 0), cmk(0, 0)},
-                        sp_[2] = {cmk(0, 0), cmk(0, 0)}, sm_[2] = {cmk(0, 0), cmk(0, 0)};
-                for (int nn = mp; nn <= p; ++nn) {
-                    if (nn > mp) {
-                        const int q = leg_tri(nn, mp);
-                        const double P = fma(lt[3 * q] * ct, pm1, -lt[3 * q + 1] * pm2);
-                        pm2 = pm1;
-                        pm1 = P;
-                    }
-                    const double R = jb[nn] * pm1;
-                    if (nn < p) {
-                        sv[0] = cadd(sv[0], cscale(D[cidx(nn, mp)], R));
-                        if (mp > 0) sv[1] = cadd(sv[1], cscale(D[cidx(nn, -mp)], R));
-                    }
-                    sz_[0] = cadd(sz_[0], cscale(Ez[cidx(nn, mp)], R));
-                    sp_[0] = cadd(sp_[0], cscale(Ep[cidx(nn, mp)], R));
-                    sm_[0] = cadd(sm_[0], cscale(Em[cidx(nn, mp)], R));
-                    if (mp > 0) {
-                        sz_[1] = cadd(sz_[1], cscale(Ez[cidx(nn, -mp)], R));
-                        sp_[1] = cadd(sp_[1], cscale(Ep[cidx(nn, -mp)], R));
-                        sm_[1] = cadd(sm_[1], cscale(Em[cidx(nn, -mp)], R));
-                    }
-                }
-                const double2 ep = e, em = cconj(e);
-                far = cadd(far, cmul(sv[0], ep));
-                fz = cadd(fz, cmul(sz_[0], ep));
-                fp = cadd(fp, cmul(sp_[0], ep));
-                fm = cadd(fm, cmul(sm_[0], ep));
-                if (mp > 0) {
-                    far = cadd(far, cmul(sv[1], em));
-                    fz = cadd(fz, cmul(sz_[1], em));
-                    fp = cadd(fp, cmul(sp_[1], em));
-                    fm = cadd(fm, cmul(sm_[1], em));
-                }
-            }
-        }
+// potential and normal derivative at the targets from the expansions E of k_local_derivs (degree
+// p + 1), plus the near part and the local terms of both block rows; the split of k_l2p
+template <bool STAGE>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+k_l2p_n(int p, int cs, const int32_t *leaf_start, const double4 *center,
+                                              const double4 *ec, const double4 *en, const double2 *E, double k,
+                                              double ik, const double *leg, const double *ser, const double2 *ynear,
+                                              const double2 *ynearn, int nsplit, const int32_t *perm, int64_t n,
+                                              const double2 *x, const double2 *bm, const double2 *bp, double2 *y,
+                                              int has_far) {
+    extern __shared__ char l2p_sm[];
+    const int b = blockIdx.x, ts = leaf_start[b], te = leaf_start[b + 1], q1 = (p + 1) * (p + 1);
+    auto fin = [&](int t, const double2 *f) {  // f: potential, d_z, d_x + i d_y, d_x - i d_y
         const double4 nt = en[t];
         // n.grad = n_z d_z + (n_x - i n_y)/2 (d_x + i d_y) + (n_x + i n_y)/2 (d_x - i d_y)
-        double2 farn = cscale(fz, nt.z);
-        farn = cadd(farn, cmul(cmk(0.5 * nt.x, -0.5 * nt.y), fp));
-        farn = cadd(farn, cmul(cmk(0.5 * nt.x, 0.5 * nt.y), fm));
+        double2 farn = cscale(f[1], nt.z);
+        farn = cadd(farn, cmul(cmk(0.5 * nt.x, -0.5 * nt.y), f[2]));
+        farn = cadd(farn, cmul(cmk(0.5 * nt.x, 0.5 * nt.y), f[3]));
         const int64_t u = perm[t];
-        double2 v1 = ynear[t], v2 = ynearn[t];
-        for (int g = 1; g < nsplit; ++g) {
-            v1 = cadd(v1, ynear[g * n + t]);
-            v2 = cadd(v2, ynearn[g * n + t]);
-        }
-        v1 = cadd(v1, far);
-        v2 = cadd(v2, farn);
+        double2 v1 = cadd(near_sum(ynear, t, n, nsplit), f[0]), v2 = cadd(near_sum(ynearn, t, n, nsplit), farn);
         if (x) {
             const double2 pm = x[u], pp = x[n + u];
             v1 = cadd(v1, cscale(cadd(pm, pp), 0.5));
@@ -2159,6 +2147,12 @@ __global__ void __launch_bounds__(64) k_l2p_n(int nleaf, int p, const int32_t *l
         }
         y[u] = v1;
         y[n + u] = v2;
+    };
+    if (has_far) {
+        l2p_leaf<4, STAGE>(p + 1, cs, ts, te, center[b], ec, E + (int64_t)b * 4 * q1, k, ik, leg, ser, l2p_sm, fin);
+    } else {
+        const double2 f[4] = {cmk(0, 0), cmk(0, 0), cmk(0, 0), cmk(0, 0)};
+        for (int t = ts + threadIdx.x + 64 * blockIdx.y; t < te; t += 64 * gridDim.y) fin(t, f);
     }
 }
 
@@ -2350,25 +2344,63 @@ void launch_p2m(int nr, int nleaf, int p, const int32_t *leaf_start, const doubl
     LAUNCH_OK();
 }
 
+// targets of a chunk and workgroups of a leaf: with fewer leaves than L2P_FEW (two per CU) there is room
+// for four workgroups per leaf, of 16 targets at a time
+static dim3 l2p_grid(int nv, int nleaf, int &cs) {
+    const bool few = nleaf < L2P_FEW;
+    cs = few ? 16 : 16 * l2p_tlm(nv);
+    return dim3(nleaf, few ? 4 : 1);
+}
+constexpr size_t L2P_STAGE = 48 * 1024;  // LDS up to which the expansions are staged
+
+// Lc: the local expansions; L32 instead where the translations ran in FP32; tab: build_p2m_table's
 void launch_l2p(int nr, int nleaf, int p, const int32_t *leaf_start, const double4 *center, const double4 *ec,
-                const double2 *Lc, double k, const double *leg, const double2 *ynear, int nsplit, double half,
-                const int32_t *perm, int64_t n, const double2 *x, double2 *y, int has_far, hipStream_t st) {
+                const double2 *Lc, const float2 *L32, double k, const double *leg, const double *tab,
+                const double2 *ynear, int nsplit, double half, const int32_t *perm, int64_t n, const double2 *x,
+                double2 *y, int has_far, hipStream_t st) {
     if (nleaf <= 0) return;
-    const size_t base = ((size_t)64 * (p + 2) + (size_t)3 * p * (p + 1) / 2 + 2 * BS_TERMS) * sizeof(double);
-    const size_t staged = base + (size_t)nr * p * p * 16;
-    if (staged <= 48 * 1024) {
-#define L2P_CALL(R)                                                                                                   \
-    k_l2p<R, true><<<nleaf, 64, staged, st>>>(nleaf, p, leaf_start, center, ec, Lc, k, leg, ynear, nsplit, half, perm, n, \
-                                              x, y, has_far)
-        FMM_NR_DISPATCH(nr, L2P_CALL)
+    int cs;
+    const dim3 grid = l2p_grid(nr, nleaf, cs);
+    const size_t dbytes = (size_t)nr * p * p * (L32 ? sizeof(float2) : sizeof(double2));
+    const bool stage = L2pLayout(p, cs, dbytes).total <= (int)L2P_STAGE;
+    const size_t sh = L2pLayout(p, cs, stage ? dbytes : 0).total;
+#define L2P_CALL2(R, T, D)                                                                                              \
+    if (stage) k_l2p<R, true, T><<<grid, 64, sh, st>>>(p, cs, leaf_start, center, ec, D, k, 1.0 / k, leg, tab + P2M_OSER, \
+                                                       ynear, nsplit, half, perm, n, x, y, has_far);                    \
+    else k_l2p<R, false, T><<<grid, 64, sh, st>>>(p, cs, leaf_start, center, ec, D, k, 1.0 / k, leg, tab + P2M_OSER,     \
+                                                  ynear, nsplit, half, perm, n, x, y, has_far)
+#define L2P_CALL(R)                               \
+    if (L32) { L2P_CALL2(R, float2, L32); }       \
+    else { L2P_CALL2(R, double2, Lc); }
+    FMM_NR_DISPATCH(nr, L2P_CALL)
 #undef L2P_CALL
-    } else {
-#define L2P_CALL(R)                                                                                                  \
-    k_l2p<R, false><<<nleaf, 64, base, st>>>(nleaf, p, leaf_start, center, ec, Lc, k, leg, ynear, nsplit, half, perm, n, \
-                                             x, y, has_far)
-        FMM_NR_DISPATCH(nr, L2P_CALL)
-#undef L2P_CALL
+#undef L2P_CALL2
+    LAUNCH_OK();
+}
+
+// potential and normal derivative of local expansions; E: 4 (p + 1)^2 entries per leaf of scratch
+void launch_l2p_n(int nleaf, int p, const int32_t *leaf_start, const double4 *center, const double4 *ec,
+                  const double4 *en, const double2 *Lc, const float2 *L32, double2 *E, double k, const double *leg,
+                  const double *tab, const double2 *ynear, const double2 *ynearn, int nsplit, const int32_t *perm,
+                  int64_t n, const double2 *x, const double2 *bm, const double2 *bp, double2 *y, int has_far,
+                  hipStream_t st) {
+    if (nleaf <= 0) return;
+    if (has_far) {
+        if (L32) k_local_derivs<<<nleaf, 256, 0, st>>>(nleaf, p, L32, k, E);
+        else k_local_derivs<<<nleaf, 256, 0, st>>>(nleaf, p, Lc, k, E);
+        LAUNCH_OK();
     }
+    int cs;
+    const dim3 grid = l2p_grid(4, nleaf, cs);
+    const size_t dbytes = (size_t)4 * (p + 1) * (p + 1) * sizeof(double2);
+    const bool stage = L2pLayout(p + 1, cs, dbytes).total <= (int)L2P_STAGE;
+    const size_t sh = L2pLayout(p + 1, cs, stage ? dbytes : 0).total;
+#define L2P_CALL(S)                                                                                                    \
+    k_l2p_n<S><<<grid, 64, sh, st>>>(p, cs, leaf_start, center, ec, en, E, k, 1.0 / k, leg, tab + P2M_OSER, ynear, ynearn, \
+                                     nsplit, perm, n, x, bm, bp, y, has_far)
+    if (stage) L2P_CALL(true);
+    else L2P_CALL(false);
+#undef L2P_CALL
     LAUNCH_OK();
 }
 

@@ -161,7 +161,9 @@ constexpr int SEG_ALIGN = 8;
 constexpr int64_t FIELD_WGS = 8192, FIELD_PART = (int64_t)1 << 17;
 // tables of P2M (p <= 21): coefficients, series terms, offset of the series and size in doubles
 constexpr int P2M_PMAX = 21, P2M_CAP = (P2M_PMAX * P2M_PMAX + 1) / 2 * 2, P2M_SER = 24, P2M_OSER = 7 * P2M_CAP + 7 * P2M_CAP / 2;
-constexpr int P2M_SLOTS = 256, P2M_OORD = P2M_OSER + (P2M_PMAX + 1) * P2M_SER, P2M_TABLE = P2M_OORD + P2M_SLOTS / 2;
+constexpr int P2M_SLOTS = 256, SER_NMAX = 40, P2M_OORD = P2M_OSER + (SER_NMAX + 1) * P2M_SER, P2M_TABLE = P2M_OORD + P2M_SLOTS / 2;
+// leaves below which L2P takes 16 targets per workgroup (two wavefronts per CU)
+constexpr int L2P_FEW = 512;
 // up to four monopole sources of one right-hand side pass
 struct Monopoles {
     double rs[4][3];
