@@ -498,7 +498,7 @@ def main():
 
     y_h = y.cpu().numpy()
 
-    # the same product in mixed precision (FP32 near field and translations)
+    # the same product in mixed precision (FP32 translations)
     ym = torch.empty_like(x)
     for _ in range(args.warmup):
         ctx.fmmbem_matvec_dev(x.data_ptr(), ym.data_ptr(), precision=F.FMMBEM_MIXED, stream=sp)

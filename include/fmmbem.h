@@ -79,8 +79,8 @@ enum {
 /* arithmetic of the matrix-vector product */
 enum {
     FMMBEM_FP64 = 0,  /* every step in FP64 */
-    FMMBEM_MIXED = 1  /* near field and translations in FP32 with FP32 accumulation; tables,
-                         recursions and the Krylov algebra stay FP64 */
+    FMMBEM_MIXED = 1  /* translations in FP32 with FP32 accumulation; near field, tables, recursions
+                         and the Krylov algebra stay FP64 */
 };
 
 /* preconditioner slot of flexible GMRES (Section 4.3 names an inner FMM-GMRES and a diagonal one) */
@@ -201,8 +201,7 @@ int fmmbem_rhs(fmmbem_ctx *ctx, fmmbem_c64 *b);
 int fmmbem_rhs_dev(fmmbem_ctx *ctx, void *b_dev, void *stream);
 
 /* y = A x for nrhs vectors (x, y: nrhs*N, host memory).  precision: FMMBEM_FP64 / FMMBEM_MIXED
- * (direct: FP32 near-field kernel and translations; indirect: FP32 translations, FP64 near field;
- * both keep densities, P2M, L2P and the output FP64).
+ * (translations in FP32; near field, densities, P2M, L2P and the output FP64).
  * With `exact_far` != 0 the far field is summed pair by pair instead of by the FMM (all-pairs
  * O(N^2) product, for validation; FP64 only). */
 int fmmbem_matvec(fmmbem_ctx *ctx, int32_t nrhs, const fmmbem_c64 *x, fmmbem_c64 *y, int precision, int exact_far);

@@ -53,10 +53,10 @@ __global__ void k_diag2_inv(int64_t, const int32_t *, const int32_t *, const dou
                             const double2 *, const double2 *, double, double, double2 *);
 __global__ void k_mul_diag2(int64_t, const int32_t *, const double2 *, const double2 *, double2 *);
 int p2p_splits_of(int nleaf);
-void launch_p2p(int nr, bool fp32, int nleaf, int nsplit, const int32_t *leaf_start, const int32_t *nbr_start,
+void launch_p2p(int nr, int nleaf, int nsplit, const int32_t *leaf_start, const int32_t *nbr_start,
                 const int32_t *nbr_list, int all_leaves, const double4 *ec, const double4 *en, const double2 *sigma,
                 const double2 *mu, double k, double rc2, const int32_t *near_start, const int32_t *near_col,
-                const void *nL, const void *nM, double2 *y, hipStream_t st);
+                const double2 *nL, const double2 *nM, double2 *y, hipStream_t st);
 void launch_p2p_n(int nleaf, int nsplit, const int32_t *leaf_start, const int32_t *nbr_start, const int32_t *nbr_list,
                   int all_leaves, const double4 *ec, const double4 *en, const double2 *sigma, const double2 *mu,
                   double k, double rc2, const int32_t *near_start, const int32_t *near_col, const double2 *nL,
@@ -949,9 +949,6 @@ static void ensure_mixed(fmmbem_ctx *c) {
     const int64_t nph = (int64_t)NDIR * (2 * c->delta_p + 1);
     float2 *ph = dget<float2>(c->buf, "phA32", nph);
     convert(c, nph, (const double2 *)c->buf.find("phA"), ph);
-    float2 *nL = dget<float2>(c->buf, "near_L32", c->near_nnz), *nM = dget<float2>(c->buf, "near_M32", c->near_nnz);
-    convert(c, c->near_nnz, (const double2 *)c->buf.find("near_L"), nL);
-    convert(c, c->near_nnz, (const double2 *)c->buf.find("near_M"), nM);
     HIP_OK(hipStreamSynchronize(c->stream));
     c->mixed_ready = true;
 }
@@ -1081,7 +1078,7 @@ static void fmm_pass(fmmbem_ctx *c, int nr, const double2 *sigma, const double2 
     const int nleaf = (int)T.leaf_start.size() - 1;
     auto I32 = [&](const char *s) { return (int32_t *)c->buf.find(s); };
     const double4 *ec = (double4 *)c->buf.find("ec"), *en = (double4 *)c->buf.find("en");
-    const int nsplit = mixed ? 1 : p2p_splits_of(nleaf);
+    const int nsplit = p2p_splits_of(nleaf);
     double2 *ynear = dget<double2>(c->scratch, "ynear", (size_t)n * nr * nsplit);
     ensure_nr(c, nr, mixed);
     struct CurGuard {
@@ -1091,15 +1088,13 @@ static void fmm_pass(fmmbem_ctx *c, int nr, const double2 *sigma, const double2 
     auto near_field = [&]() {
         int pe = prof_begin(c);
         const double pairs = exact_far ? (double)n * n : (double)c->p2p_pairs;
-        launch_p2p(nr, mixed, nleaf, nsplit, I32("leaf_start"), I32("nbr_start"), I32("nbr_list"), exact_far ? 1 : 0, ec, en,
-                   sigma, mu, c->k, c->rc * c->rc, I32("near_start"), I32("near_col"),
-                   c->buf.find(mixed ? "near_L32" : "near_L"), c->buf.find(mixed ? "near_M32" : "near_M"), ynear,
-                   c->cur);
+        launch_p2p(nr, nleaf, nsplit, I32("leaf_start"), I32("nbr_start"), I32("nbr_list"), exact_far ? 1 : 0, ec, en,
+                   sigma, mu, c->k, c->rc * c->rc, I32("near_start"), I32("near_col"), (double2 *)c->buf.find("near_L"),
+                   (double2 *)c->buf.find("near_M"), ynear, c->cur);
         // one-point pairs: ~40 flops each (sincos counted as 20), kernel shared by the nr vectors;
         // bytes: element data, densities, near table and output, each read once
-        const double tb = mixed ? 16.0 : 32.0;
-        prof_end(c, pe, mixed ? "k_p2p32" : "k_p2p", (40.0 + 16.0 * (nr - 1)) * pairs + 16.0 * nr * c->near_nnz,
-                 80.0 * n + 48.0 * n * nr + (8.0 + tb) * c->near_nnz);
+        prof_end(c, pe, "k_p2p", (40.0 + 16.0 * (nr - 1)) * pairs + 16.0 * nr * c->near_nnz,
+                 80.0 * n + 48.0 * n * nr + 40.0 * c->near_nnz);
     };
     // The near field of a product runs on the main stream after the M2L of the deep levels, beside
     // the side stream's L2L chain (few workgroups per level), and L2P follows both; P2M and the M2M

@@ -597,6 +597,9 @@ __device__ inline void eikr(double r, double2 kk, const double2 *tab, double &c,
 // in order.  Measured against one wavefront per leaf, one target per lane and the polynomial sincos
 // (FP64, one vector): 2,664 elements 255 -> 13.6 us, 90,972 241 -> 73 us, 1M L-room 1.20 -> 0.67 ms
 // (5.4e11 pairs/s); with normal derivatives 2,664 elements 431 -> 19.5 us, 90,972 412 -> 140 us.
+// Mixed-precision products take it too: the vector units issue FP64 as fast as FP32, and the pairs in
+// FP32 (its accurate sincos, compensated sums, one wavefront per leaf) took four vectors of 90,972
+// elements 276 us where this takes 146, of 612,540 elements 690 and 632.
 constexpr int P2P_WG = 256, P2P_T = 2;
 // lanes per group TP and groups S of a leaf of nt targets, for the number of passes over the sources
 // P (the fewest possible, or up to three more) with the least lane work P / S; a further pass
@@ -792,136 +795,6 @@ k_p2p(int nleaf, const int32_t *leaf_start, const int32_t *nbr_start, const int3
                         y[(g * n + t[u]) * NR + rr] = acc[u][rr];
                         if (NRM) yn[(g * n + t[u]) * NR + rr] = accn[u][rr];
                     }
-    }
-}
-
-// ------------------------------------------------------------------ P2P, FP32 arithmetic
-// Mixed-precision near field: the near/far classification uses the exact FP64 squared distance
-// (so it matches the near table), the kernel evaluation runs in FP32, and the accumulation is
-// Kahan-compensated in FP32.  Near-table entries are stored in FP32.
-__device__ inline void kahan_add(float &s, float &c, float v) {
-    const float y = v - c;
-    const float t = s + y;
-    c = (t - s) - y;
-    s = t;
-}
-
-// Source splits S of a leaf of nt targets: lane groups of TP = floor(64 / S) targets, each group
-// summing every S-th source, ceil(nt / TP) passes over the sources; S in 1..8 minimises the lane
-// work ceil(nt / TP) / S (ties to the smaller S, which adds fewer partial sums).  Lanes past S TP
-// (S = 3, 5, 6, 7) stay idle.
-__device__ inline int p2p_splits(int nt) {
-    int best = 1;
-    double bc = 1e30;
-    for (int S = 1; S <= 8; ++S) {
-        const int TP = 64 / S;
-        const double c = (double)((nt + TP - 1) / TP) / S;
-        if (c < bc - 1e-12) {
-            bc = c;
-            best = S;
-        }
-    }
-    return best;
-}
-
-template <int NR>
-__global__ void __launch_bounds__(64) k_p2p32(int nleaf, const int32_t *leaf_start, const int32_t *nbr_start,
-                                              const int32_t *nbr_list, const double4 *ec, const double4 *en,
-                                              const double2 *sigma, const double2 *mu, double k, double rc2,
-                                              const int32_t *near_start, const int32_t *near_col, const float2 *nL,
-                                              const float2 *nM, double2 *y) {
-    const int b = blockIdx.x, tid = threadIdx.x;
-    __shared__ double sx[64], sy[64], sz[64];
-    __shared__ float snx[64], sny[64], snz[64];
-    __shared__ float2 sq[64 * NR], sw[64 * NR];
-    __shared__ double2 red[64 * NR];
-    const int ts = leaf_start[b], te = leaf_start[b + 1];
-    const float kf = (float)k, inv4pi = (float)(1.0 / (4.0 * FMM_PI));
-    const int S = p2p_splits(te - ts), TP = 64 / S;  // source splits, targets per pass (as in k_p2p)
-    const int h = tid / TP;
-    for (int t0 = ts; t0 < te; t0 += TP) {
-        const int t = t0 + tid % TP;
-        const bool act = t < te && h < S;
-        double4 ct = act ? ec[t] : make_double4(0, 0, 0, 0);
-        float ar[NR], ai[NR], cr[NR], ci[NR];
-#pragma unroll
-        for (int r = 0; r < NR; ++r) ar[r] = ai[r] = cr[r] = ci[r] = 0.f;
-        for (int q = nbr_start[b]; q < nbr_start[b + 1]; ++q) {
-            const int sb = nbr_list[q];
-            const int ss = leaf_start[sb], se = leaf_start[sb + 1];
-            for (int j0 = ss; j0 < se; j0 += 64) {
-                __syncthreads();
-                int j = j0 + tid;
-                if (j < se) {
-                    double4 c = ec[j], nv = en[j];
-                    sx[tid] = c.x;
-                    sy[tid] = c.y;
-                    sz[tid] = c.z;
-                    snx[tid] = (float)nv.x;
-                    sny[tid] = (float)nv.y;
-                    snz[tid] = (float)nv.z;
-#pragma unroll
-                    for (int r = 0; r < NR; ++r) {
-                        const double2 s = sigma[(int64_t)j * NR + r], m = mu[(int64_t)j * NR + r];
-                        sq[tid * NR + r] = make_float2((float)(s.x * c.w), (float)(s.y * c.w));
-                        sw[tid * NR + r] = make_float2((float)(m.x * c.w), (float)(m.y * c.w));
-                    }
-                }
-                __syncthreads();
-                const int cnt = min(64, se - j0);
-                if (act) {
-                    for (int jj = h; jj < cnt; jj += S) {
-                        double d2 = dist2_exact(ct.x, ct.y, ct.z, sx[jj], sy[jj], sz[jj]);
-                        if (d2 < rc2) continue;
-                        const float dx = (float)(sx[jj] - ct.x), dy = (float)(sy[jj] - ct.y), dz = (float)(sz[jj] - ct.z);
-                        const float r2 = (float)d2, ir = rsqrtf(r2), r = r2 * ir;
-                        float s, c;
-                        sincosf(kf * r, &s, &c);
-                        const float gr = c * ir * inv4pi, gi = s * ir * inv4pi;
-                        const float u = (dx * snx[jj] + dy * sny[jj] + dz * snz[jj]) * ir * ir;
-                        const float kru = kf * r * u;
-#pragma unroll
-                        for (int rr = 0; rr < NR; ++rr) {
-                            // G * (q + (ikr - 1) u w)
-                            const float2 w = sw[jj * NR + rr], qq = sq[jj * NR + rr];
-                            const float tr = qq.x - u * w.x - kru * w.y;
-                            const float ti = qq.y - u * w.y + kru * w.x;
-                            kahan_add(ar[rr], cr[rr], gr * tr - gi * ti);
-                            kahan_add(ai[rr], ci[rr], gr * ti + gi * tr);
-                        }
-                    }
-                }
-            }
-        }
-        double2 acc[NR];
-#pragma unroll
-        for (int rr = 0; rr < NR; ++rr) acc[rr] = make_double2((double)ar[rr] - (double)cr[rr], (double)ai[rr] - (double)ci[rr]);
-        if (act) {
-            for (int e = near_start[t] + h; e < near_start[t + 1]; e += S) {
-                const int64_t j = near_col[e];
-                const float2 l = nL[e], m = nM[e];
-                const double2 ld = make_double2(l.x, l.y), md = make_double2(m.x, m.y);
-#pragma unroll
-                for (int rr = 0; rr < NR; ++rr) {
-                    acc[rr] = cfma(ld, sigma[j * NR + rr], acc[rr]);
-                    acc[rr] = cfma(md, mu[j * NR + rr], acc[rr]);
-                }
-            }
-        }
-        if (S > 1) {  // add the groups' partial sums (group 0 keeps the result)
-            __syncthreads();
-#pragma unroll
-            for (int rr = 0; rr < NR; ++rr) red[tid * NR + rr] = acc[rr];
-            __syncthreads();
-            if (h == 0)
-                for (int g = 1; g < S; ++g)
-#pragma unroll
-                    for (int rr = 0; rr < NR; ++rr) acc[rr] = cadd(acc[rr], red[(tid + g * TP) * NR + rr]);
-        }
-        if (act && h == 0) {
-#pragma unroll
-            for (int rr = 0; rr < NR; ++rr) y[(int64_t)t * NR + rr] = acc[rr];
-        }
     }
 }
 
@@ -2208,25 +2081,19 @@ static double2 eikr_scale(double k) {
     return make_double2(hi, (double)(v - (long double)hi));
 }
 
-// pieces of every leaf's source list in the FP64 near field: enough workgroups for every CU to hold
+// pieces of every leaf's source list in the near field: enough workgroups for every CU to hold
 // its eight (2,048), at most 16 sums for L2P to add.  56 leaves (2,664 elements): 29.6 us whole,
 // 13.6 us in 16 pieces, 16.8 us in 32; the 2,700 leaves of 90,972 elements gain nothing from pieces.
 int p2p_splits_of(int nleaf) { return std::max(1, std::min(16, ceil_div(2048, std::max(1, nleaf)))); }
 
-void launch_p2p(int nr, bool fp32, int nleaf, int nsplit, const int32_t *leaf_start, const int32_t *nbr_start,
+void launch_p2p(int nr, int nleaf, int nsplit, const int32_t *leaf_start, const int32_t *nbr_start,
                 const int32_t *nbr_list, int all_leaves, const double4 *ec, const double4 *en, const double2 *sigma,
                 const double2 *mu, double k, double rc2, const int32_t *near_start, const int32_t *near_col,
-                const void *nL, const void *nM, double2 *y, hipStream_t st) {
-    if (fp32 && all_leaves) throw FmmError(-1, "the all-pairs near field is an FP64 product");
-#define P2P_CALL(R)                                                                                                   \
-    if (fp32)                                                                                                         \
-        k_p2p32<R><<<nleaf, 64, 0, st>>>(nleaf, leaf_start, nbr_start, nbr_list, ec, en, sigma, mu, k, rc2,          \
-                                         near_start, near_col, (const float2 *)nL, (const float2 *)nM, y);           \
-    else                                                                                                              \
-        k_p2p<R, false><<<nleaf * nsplit, P2P_WG, 0, st>>>(nleaf, leaf_start, nbr_start, nbr_list, all_leaves, nsplit, \
-                                                           ec, en, sigma, mu, k, eikr_scale(k), rc2, near_start,      \
-                                                           near_col, (const double2 *)nL, (const double2 *)nM,        \
-                                                           nullptr, nullptr, y, nullptr)
+                const double2 *nL, const double2 *nM, double2 *y, hipStream_t st) {
+#define P2P_CALL(R)                                                                                               \
+    k_p2p<R, false><<<nleaf * nsplit, P2P_WG, 0, st>>>(nleaf, leaf_start, nbr_start, nbr_list, all_leaves, nsplit, ec, \
+                                                       en, sigma, mu, k, eikr_scale(k), rc2, near_start, near_col, nL, \
+                                                       nM, nullptr, nullptr, y, nullptr)
     FMM_NR_DISPATCH(nr, P2P_CALL)
 #undef P2P_CALL
     LAUNCH_OK();
