@@ -5,8 +5,8 @@
 // Arnoldi uses classical Gram-Schmidt with a second pass when the first one cancelled most of the
 // new vector (norm drop below 1/sqrt(2), the Daniel-Gragg-Kaufman-Stewart test): each pass is one
 // batched set of inner products (two-stage, fixed-order reductions, so runs are bitwise
-// reproducible) and one batched update.  Givens rotations and the small least-squares problem live on the host; one
-// short host<->device copy per pass.
+// reproducible) and one batched update, coefficients and the test kept on the device.  Givens
+// rotations and the small least-squares problem live on the host; one short copy per step.
 #include <chrono>
 #include <functional>
 #include <type_traits>
@@ -71,10 +71,10 @@ __global__ void __launch_bounds__(256) k_dot_partial(int64_t n, const S *V, int6
     if ((int)threadIdx.x < ng) partial[(int64_t)(v0 + threadIdx.x) * gridDim.x + blockIdx.x] = red[threadIdx.x][0];
 }
 
-__global__ void __launch_bounds__(256) k_dot_final(int nblk, const double2 *partial, double2 *out) {
-    const int v = blockIdx.x;
+// sum of nblk partial sums over the workgroup, in a fixed order (valid in thread 0)
+__device__ inline double2 sum_partials(int nblk, const double2 *partial) {
     double2 s = cmk(0, 0);
-    for (int i = threadIdx.x; i < nblk; i += blockDim.x) s = cadd(s, partial[(int64_t)v * nblk + i]);
+    for (int i = threadIdx.x; i < nblk; i += blockDim.x) s = cadd(s, partial[i]);
     __shared__ double2 red[256];
     red[threadIdx.x] = s;
     __syncthreads();
@@ -82,28 +82,166 @@ __global__ void __launch_bounds__(256) k_dot_final(int nblk, const double2 *part
         if ((int)threadIdx.x < q) red[threadIdx.x] = cadd(red[threadIdx.x], red[threadIdx.x + q]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[v] = red[0];
+    return red[0];
 }
 
-// w -= sum_v h[v] V_v, in the order of v; vectors are read COMBO_U at a time, all loads of a
-// group issued before the group's updates (one load per iteration would leave one 1 KB request in
-// flight per wavefront)
+__global__ void __launch_bounds__(256) k_dot_final(int nblk, const double2 *partial, double2 *out) {
+    const double2 s = sum_partials(nblk, partial + (int64_t)blockIdx.x * nblk);
+    if (threadIdx.x == 0) out[blockIdx.x] = s;
+}
+
+// One Gram-Schmidt step of up to GS_MAX systems, w against their V_0 .. V_{nv-1}: eight launches
+// (inner products, their sums, update, norm; twice) for all systems, then the next basis vector, with no
+// word from the host in between.  Results of a system, at res (m: the restart length):
+//   [0, m]                first-pass inner products
+//   [m + 1, 2 m + 1]      second-pass ones (where there was a second pass)
+//   2 m + 2, 3, 4         |w|^2 before, after the first pass, after the second (.x)
+//   2 m + 5               .x: 1 if the second pass is taken
+// The second pass's launches end at once where it is not.  Bound by launches and the one copy for small
+// n, by reading V for large n.  Measured against a host decision after every norm (five copies and host
+// waits per step for one system, four for a lock-step group): a solve of 2,664 elements in 27 steps
+// 8.4 -> 6.1 ms, four of 90,972 elements in lock step with FP32 bases 60.6 -> 53.2 ms.
+constexpr int GS_MAX = 4;
+template <class S>
+struct GsSys {
+    const S *V;
+    S *Vnext;  // V_nv: w / |w|
+    double2 *w, *res, *part;
+    int nv;
+};
+template <class S>
+struct GsArgs {
+    GsSys<S> s[GS_MAX];
+};
+constexpr int gs_len(int m) { return 2 * m + 6; }
+
+// partial sums of conj(V_v) w, v < nv, and in the first pass of |w|^2 (v = nv): k_dot_partial's
+template <class S>
+__global__ void __launch_bounds__(256) k_gs_dots(int64_t n, int m, int pass, GsArgs<S> A) {
+    const GsSys<S> q = A.s[blockIdx.z];
+    if (pass && q.res[2 * m + 5].x == 0.0) return;
+    const int v0 = blockIdx.y * DOT_G, all = q.nv + (pass == 0), ng = min(DOT_G, all - v0);
+    if (ng <= 0) return;
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, di = (int64_t)gridDim.x * blockDim.x;
+    double2 s[DOT_G];
+#pragma unroll
+    for (int g = 0; g < DOT_G; ++g) s[g] = cmk(0, 0);
+    if (v0 + DOT_G <= q.nv) {
+        // whole group: the DOT_G loads of a row are issued before any of them is used
+        for (int64_t i = i0; i < n; i += di) {
+            const double2 wi = q.w[i];
+            double2 x[DOT_G];
+#pragma unroll
+            for (int g = 0; g < DOT_G; ++g) x[g] = ldc(q.V + (int64_t)(v0 + g) * n, i);
+#pragma unroll
+            for (int g = 0; g < DOT_G; ++g) s[g] = cadd(s[g], cmulc(wi, x[g]));  // conj(V_v) w
+        }
+    } else {
+        for (int64_t i = i0; i < n; i += di) {
+            const double2 wi = q.w[i];
+#pragma unroll
+            for (int g = 0; g < DOT_G; ++g)
+                if (g < ng) s[g] = cadd(s[g], cmulc(wi, v0 + g < q.nv ? ldc(q.V + (int64_t)(v0 + g) * n, i) : wi));
+        }
+    }
+    __shared__ double2 red[DOT_G][256];
+#pragma unroll
+    for (int g = 0; g < DOT_G; ++g) red[g][threadIdx.x] = s[g];
+    __syncthreads();
+    for (int h = blockDim.x / 2; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h)
+#pragma unroll
+            for (int g = 0; g < DOT_G; ++g) red[g][threadIdx.x] = cadd(red[g][threadIdx.x], red[g][threadIdx.x + h]);
+        __syncthreads();
+    }
+    if ((int)threadIdx.x < ng) q.part[(int64_t)(v0 + threadIdx.x) * gridDim.x + blockIdx.x] = red[threadIdx.x][0];
+}
+
+template <class S>
+__global__ void __launch_bounds__(256) k_gs_final(int nblk, int m, int pass, GsArgs<S> A) {
+    const GsSys<S> q = A.s[blockIdx.y];
+    const int v = blockIdx.x;
+    if (v >= q.nv + (pass == 0) || (pass && q.res[2 * m + 5].x == 0.0)) return;
+    const double2 s = sum_partials(nblk, q.part + (int64_t)v * nblk);
+    if (threadIdx.x == 0) q.res[v == q.nv ? 2 * m + 2 : pass * (m + 1) + v] = s;
+}
+
+// w -= sum_v h[v] V_v, in the order of v, and the partial sums of the new |w|^2; vectors are read
+// COMBO_U at a time, all loads of a group issued before the group's updates (one load per iteration
+// would leave one 1 KB request in flight per wavefront)
 constexpr int COMBO_U = 8;
 template <class S>
-__global__ void k_sub_combo(int64_t n, const S *V, int64_t ldv, int nv, const double2 *h, double2 *w) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double2 s = w[i];
-    int v = 0;
-    for (; v + COMBO_U <= nv; v += COMBO_U) {
-        double2 x[COMBO_U];
+__global__ void __launch_bounds__(256) k_gs_update(int64_t n, int m, int pass, GsArgs<S> A) {
+    const GsSys<S> q = A.s[blockIdx.y];
+    if (pass && q.res[2 * m + 5].x == 0.0) return;
+    const double2 *h = q.res + pass * (m + 1);
+    double2 d = cmk(0, 0);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        double2 s = q.w[i];
+        int v = 0;
+        for (; v + COMBO_U <= q.nv; v += COMBO_U) {
+            double2 x[COMBO_U];
 #pragma unroll
-        for (int u = 0; u < COMBO_U; ++u) x[u] = ldc(V, (int64_t)(v + u) * ldv + i);
+            for (int u = 0; u < COMBO_U; ++u) x[u] = ldc(q.V, (int64_t)(v + u) * n + i);
 #pragma unroll
-        for (int u = 0; u < COMBO_U; ++u) s = csub(s, cmul(h[v + u], x[u]));
+            for (int u = 0; u < COMBO_U; ++u) s = csub(s, cmul(h[v + u], x[u]));
+        }
+        for (; v < q.nv; ++v) s = csub(s, cmul(h[v], ldc(q.V, (int64_t)v * n + i)));
+        q.w[i] = s;
+        d = cadd(d, cmulc(s, s));
     }
-    for (; v < nv; ++v) s = csub(s, cmul(h[v], ldc(V, (int64_t)v * ldv + i)));
-    w[i] = s;
+    __shared__ double2 red[256];
+    red[threadIdx.x] = d;
+    __syncthreads();
+    for (int g = blockDim.x / 2; g > 0; g >>= 1) {
+        if ((int)threadIdx.x < g) red[threadIdx.x] = cadd(red[threadIdx.x], red[threadIdx.x + g]);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) q.part[blockIdx.x] = red[0];
+}
+
+// |w|^2 after the pass and, after the first, the choice of a second one: reorth 1 where the first
+// removed most of w (|w| fell below |w_0| / sqrt(2)), 2 always, 0 never
+template <class S>
+__global__ void __launch_bounds__(256) k_gs_norm(int nblk, int m, int pass, int reorth, GsArgs<S> A) {
+    const GsSys<S> q = A.s[blockIdx.x];
+    if (pass && q.res[2 * m + 5].x == 0.0) return;
+    const double2 s = sum_partials(nblk, q.part);
+    if (threadIdx.x != 0) return;
+    q.res[2 * m + 3 + pass] = s;
+    if (pass) return;
+    const double w0 = sqrt(fmax(q.res[2 * m + 2].x, 0.0)), hn = sqrt(fmax(s.x, 0.0));
+    q.res[2 * m + 4] = s;
+    q.res[2 * m + 5] = cmk(reorth == 2 || (reorth == 1 && !(hn > 0.7071067811865476 * w0)) ? 1.0 : 0.0, 0.0);
+}
+
+// the next basis vector w / |w| (left alone where |w| is 0 or not a number: the host ends the cycle)
+template <class S>
+__global__ void __launch_bounds__(256) k_gs_next(int64_t n, int m, GsArgs<S> A) {
+    const GsSys<S> q = A.s[blockIdx.y];
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const double hn = sqrt(fmax(q.res[2 * m + 4].x, 0.0));
+    if (i < n && hn > 0.0) stc(q.Vnext, i, cscale(q.w[i], 1.0 / hn));
+}
+
+// the whole step, enqueued
+template <class S>
+static void gs_step(int64_t n, int m, int nsys, int reorth, const GsArgs<S> &A, hipStream_t st) {
+    int nv = 0;
+    for (int k = 0; k < nsys; ++k) nv = std::max(nv, A.s[k].nv);
+    const int nblk = (int)std::min<int64_t>(DOT_BLOCKS, std::max<int64_t>(1, (n + 255) / 256));
+    for (int pass = 0; pass < (reorth == 0 ? 1 : 2); ++pass) {
+        k_gs_dots<S><<<dim3(nblk, ceil_div(nv + (pass == 0), DOT_G), nsys), 256, 0, st>>>(n, m, pass, A);
+        LAUNCH_OK();
+        k_gs_final<S><<<dim3(nv + (pass == 0), nsys), 256, 0, st>>>(nblk, m, pass, A);
+        LAUNCH_OK();
+        k_gs_update<S><<<dim3(nblk, nsys), 256, 0, st>>>(n, m, pass, A);
+        LAUNCH_OK();
+        k_gs_norm<S><<<nsys, 256, 0, st>>>(nblk, m, pass, reorth, A);
+        LAUNCH_OK();
+    }
+    k_gs_next<S><<<dim3(ceil_div(n, 256), nsys), 256, 0, st>>>(n, m, A);
+    LAUNCH_OK();
 }
 
 // x += sum_v y[v] Z_v (same grouping)
@@ -477,13 +615,6 @@ struct Blas {
         return sqrt(std::max(d.x, 0.0));
     }
     template <class S>
-    void sub_combo(const S *V, int64_t ldv, int nv, const double2 *h_host, double2 *w) {
-        double2 *h = dget<double2>(scr, tag + "combo_h", std::max(nv, 1));
-        HIP_OK(hipMemcpyAsync(h, h_host, sizeof(double2) * nv, hipMemcpyHostToDevice, st));
-        k_sub_combo<S><<<ceil_div(n, 256), 256, 0, st>>>(n, V, ldv, nv, h, w);
-        LAUNCH_OK();
-    }
-    template <class S>
     void add_combo(const S *Z, int64_t ldz, int nv, const double2 *y_host, double2 *x) {
         double2 *h = dget<double2>(scr, tag + "combo_y", std::max(nv, 1));
         HIP_OK(hipMemcpyAsync(h, y_host, sizeof(double2) * nv, hipMemcpyHostToDevice, st));
@@ -531,6 +662,8 @@ static int fgmres_t(int64_t n, hipStream_t st, DeviceBuffers &scr, const char *t
     S *Z = dget<S>(scr, tg + (wide ? "fg_Z" : "fg_Z32"), (size_t)m * n);
     double2 *w = dget<double2>(scr, tg + "fg_w", n);
     double2 *r = dget<double2>(scr, tg + "fg_r", n);
+    double2 *gsr = dget<double2>(scr, tg + "fg_gs", gs_len(m));
+    double2 *gsp = dget<double2>(scr, tg + "fg_part", (size_t)DOT_BLOCKS * (m + 1));
     // FP64 copies of the current basis vector and its preconditioned image (narrow storage only)
     double2 *tv = wide ? nullptr : dget<double2>(scr, tg + "fg_tv", n);
     double2 *tz = wide ? nullptr : dget<double2>(scr, tg + "fg_tz", n);
@@ -544,7 +677,7 @@ static int fgmres_t(int64_t n, hipStream_t st, DeviceBuffers &scr, const char *t
         rel_res = 0.0;
         return FMMBEM_OK;
     }
-    std::vector<double2> H((size_t)(m + 1) * m), g(m + 1), cs(m), sn(m), h1(m + 1), h2(m + 1), y(m);
+    std::vector<double2> H((size_t)(m + 1) * m), g(m + 1), cs(m), sn(m), hr(gs_len(m)), y(m);
     auto Hc = [&](int i, int j) -> double2 & { return H[(size_t)i * m + j]; };
     int status = FMMBEM_ENOCONV;
     double est = 1.0;
@@ -590,23 +723,17 @@ static int fgmres_t(int64_t n, hipStream_t st, DeviceBuffers &scr, const char *t
             if constexpr (!wide) B.scale_copy(1.0, zj, zjs);
             matvec(zj, w);
             ++iters;
-            // classical Gram-Schmidt; reorth 1 repeats it only when the first pass removed most of w
-            // (|w| fell below |w_0|/sqrt(2): the Daniel-Gragg-Kaufman-Stewart criterion), 2 always,
-            // 0 never
-            const double w0 = reorth == 1 ? B.nrm(w) : 0.0;
-            B.dots(V, n, j + 1, w, h1.data());
-            B.sub_combo(V, n, j + 1, h1.data(), w);
-            double hn = B.nrm(w);
-            if (reorth == 2 || (reorth == 1 && !(hn > 0.7071067811865476 * w0))) {
-                B.dots(V, n, j + 1, w, h2.data());
-                B.sub_combo(V, n, j + 1, h2.data(), w);
-                for (int i = 0; i <= j; ++i) h1[i] = cadd(h1[i], h2[i]);
-                hn = B.nrm(w);
-            }
-            for (int i = 0; i <= j; ++i) Hc(i, j) = h1[i];
-            if (!std::isfinite(hn)) return FMMBEM_ENAN;
+            // classical Gram-Schmidt and the next basis vector
+            GsArgs<S> ga{};
+            ga.s[0] = {V, V + (size_t)(j + 1) * n, w, gsr, gsp, j + 1};
+            gs_step<S>(n, m, 1, reorth, ga, st);
+            HIP_OK(hipMemcpyAsync(hr.data(), gsr, sizeof(double2) * gs_len(m), hipMemcpyDeviceToHost, st));
+            HIP_OK(hipStreamSynchronize(st));
+            const bool second = hr[2 * m + 5].x != 0.0;
+            for (int i = 0; i <= j; ++i) Hc(i, j) = second ? cadd(hr[i], hr[m + 1 + i]) : hr[i];
+            const double hn = sqrt(std::max(hr[2 * m + 4].x, 0.0));
+            if (!std::isfinite(hn) || !std::isfinite(hr[2 * m + 4].x)) return FMMBEM_ENAN;
             Hc(j + 1, j) = cmk(hn, 0);
-            if (hn > 0) B.scale_copy(1.0 / hn, w, V + (size_t)(j + 1) * n);
             for (int i = 0; i < j; ++i) {
                 double2 a = Hc(i, j), c = Hc(i + 1, j);
                 Hc(i, j) = cadd(cscale(a, cs[i].x), cmul(sn[i], c));
@@ -677,7 +804,7 @@ template <class S>
 struct BatchSys {
     S *V = nullptr, *Z = nullptr;
     double2 *r = nullptr;
-    std::vector<double2> H, g, cs, sn, h1, h2, y;
+    std::vector<double2> H, g, cs, sn, y;
     double bn = 0.0, est = 1.0;
     int j = 0, cycle = 0;  // cycle = restarts so far
     bool in_cycle = false, done = false;
@@ -690,12 +817,11 @@ struct GroupSolver {
     Blas Bl;
     std::vector<BatchSys<T>> S;
     double2 *tv = nullptr, *Sin = nullptr, *Sout = nullptr;
-    double2 *part = nullptr;             // partial sums of the inner products (one stream: shared)
-    double2 *dres = nullptr;             // per system: inner products (m + 1), |w_0|^2, |w|^2
+    double2 *part = nullptr;             // partial sums of GS_MAX systems' inner products (one stream: shared)
+    double2 *dres = nullptr;             // per system: the results of a Gram-Schmidt step
     double2 *dy = nullptr;               // per system: the coefficients y of x += Z y
     double2 *hres = nullptr, *hy = nullptr;  // pinned host copies
     std::vector<int> act;                // systems whose product is in flight, in Sin/Sout order
-    std::vector<char> second;            // per system: a second Gram-Schmidt pass this step
     std::vector<int> need;               // systems whose true residual is being formed
     bool pending = false;                // work enqueued whose results the host reads next
     explicit GroupSolver(FgmresGroup &g) : G(g), Bl{g.st, *g.scr, g.n, g.tag + "bt_"} {}
@@ -703,18 +829,20 @@ struct GroupSolver {
         if (hres) (void)hipHostFree(hres);
         if (hy) (void)hipHostFree(hy);
     }
-    int RS() const { return G.m + 3; }  // stride of dres / hres per system
+    int RS() const { return gs_len(G.m); }  // stride of dres / hres per system
+    int RN() const { return 2 * G.m + 2; }  // where a norm by itself is put
+    double2 *parts(int k) { return part + (size_t)k * DOT_BLOCKS * (G.m + 1); }
     double2 *res(int s) { return dres + (size_t)s * RS(); }
     double2 *hr(int s) { return hres + (size_t)s * RS(); }
 
-    // inner products conj(V_v) w, v < nv, into out (device), enqueued only
-    template <class SV>
-    void dots_to(const SV *V, int64_t ldv, int nv, const double2 *w, double2 *out) {
+    // |w|^2 of a system, enqueued only
+    void norm_to(int s, const double2 *w) {
         const int nblk = (int)std::min<int64_t>(DOT_BLOCKS, std::max<int64_t>(1, (G.n + 255) / 256));
-        k_dot_partial<SV><<<dim3(nblk, (nv + DOT_G - 1) / DOT_G), 256, 0, G.st>>>(G.n, V, ldv, nv, w, part);
+        k_dot_partial<double2><<<dim3(nblk, 1), 256, 0, G.st>>>(G.n, w, 0, 1, w, part);
         LAUNCH_OK();
-        k_dot_final<<<nv, 256, 0, G.st>>>(nblk, part, out);
+        k_dot_final<<<1, 256, 0, G.st>>>(nblk, part, res(s) + RN());
         LAUNCH_OK();
+        to_host(s);
     }
     void to_host(int s) {  // the system's inner products and norms to the pinned copy
         HIP_OK(hipMemcpyAsync(hr(s), res(s), sizeof(double2) * RS(), hipMemcpyDeviceToHost, G.st));
@@ -729,7 +857,6 @@ struct GroupSolver {
         const int64_t n = G.n;
         const int nv = G.nv, m = G.m;
         S.assign(nv, BatchSys<T>());
-        second.assign(nv, 0);
         tv = wide ? nullptr : dget<double2>(*G.scr, G.tag + "bt_tv", n);
         G.iters.assign(nv, 0);
         G.restarts.assign(nv, 0);
@@ -737,7 +864,7 @@ struct GroupSolver {
         G.status.assign(nv, FMMBEM_ENOCONV);
         Sin = dget<double2>(*G.scr, G.tag + "bt_in", (size_t)nv * n);
         Sout = dget<double2>(*G.scr, G.tag + "bt_out", (size_t)nv * n);
-        part = dget<double2>(*G.scr, G.tag + "bt_part", (size_t)DOT_BLOCKS * (m + 1));
+        part = dget<double2>(*G.scr, G.tag + "bt_part", (size_t)std::min(nv, GS_MAX) * DOT_BLOCKS * (m + 1));
         dres = dget<double2>(*G.scr, G.tag + "bt_res", (size_t)nv * RS());
         dy = dget<double2>(*G.scr, G.tag + "bt_y", (size_t)nv * (m + 1));
         HIP_OK(hipHostMalloc((void **)&hres, sizeof(double2) * nv * RS()));
@@ -752,19 +879,16 @@ struct GroupSolver {
             q.g.assign(m + 1, cmk(0, 0));
             q.cs.assign(m, cmk(0, 0));
             q.sn.assign(m, cmk(0, 0));
-            q.h1.assign(m + 1, cmk(0, 0));
-            q.h2.assign(m + 1, cmk(0, 0));
             q.y.assign(m, cmk(0, 0));
             double2 *x = G.X + (int64_t)s * n;
             if (!G.x0_given) HIP_OK(hipMemsetAsync(x, 0, sizeof(double2) * n, G.st));
-            dots_to(G.B + (int64_t)s * n, 0, 1, G.B + (int64_t)s * n, res(s) + m + 2);
-            to_host(s);
+            norm_to(s, G.B + (int64_t)s * n);
         }
     }
     void init_done() {
         for (int s = 0; s < G.nv; ++s) {
             BatchSys<T> &q = S[s];
-            q.bn = sqrt(std::max(hr(s)[G.m + 2].x, 0.0));
+            q.bn = sqrt(std::max(hr(s)[RN()].x, 0.0));
             if (!(q.bn > 0.0)) {
                 HIP_OK(hipMemsetAsync(G.X + (int64_t)s * G.n, 0, sizeof(double2) * G.n, G.st));
                 G.rel_res[s] = 0.0;
@@ -793,14 +917,13 @@ struct GroupSolver {
             BatchSys<T> &q = S[s];
             if (!(G.x0_given || q.cycle > 0))
                 HIP_OK(hipMemcpyAsync(q.r, G.B + (int64_t)s * n, sizeof(double2) * n, hipMemcpyDeviceToDevice, G.st));
-            dots_to(q.r, 0, 1, q.r, res(s) + G.m + 2);
-            to_host(s);
+            norm_to(s, q.r);
         }
     }
     void restart_decide() {
         for (int s : need) {
             BatchSys<T> &q = S[s];
-            const double beta = sqrt(std::max(hr(s)[G.m + 2].x, 0.0));
+            const double beta = sqrt(std::max(hr(s)[RN()].x, 0.0));
             G.rel_res[s] = beta / q.bn;
             if (!std::isfinite(beta)) {
                 G.status[s] = FMMBEM_ENAN;
@@ -848,61 +971,22 @@ struct GroupSolver {
         return true;
     }
 
-    // ---- Arnoldi step of every system in flight, in phases (the host reads between phases)
-    // 1: first classical Gram-Schmidt pass: h = V^H w (and |w|^2 for the second-pass test)
-    void gs_dots() {
-        for (size_t k = 0; k < act.size(); ++k) {
-            const int s = act[k];
-            BatchSys<T> &q = S[s];
-            double2 *w = Sout + k * G.n;
-            ++G.iters[s];
-            if (G.reorth == 1) dots_to(w, 0, 1, w, res(s) + G.m + 1);
-            dots_to(q.V, G.n, q.j + 1, w, res(s));
-            to_host(s);
+    // ---- Arnoldi step of every system in flight: Gram-Schmidt and the next basis vectors
+    void gs() {
+        for (size_t k0 = 0; k0 < act.size(); k0 += GS_MAX) {
+            const int ns = (int)std::min<size_t>(GS_MAX, act.size() - k0);
+            GsArgs<T> A{};
+            for (int k = 0; k < ns; ++k) {
+                const int s = act[k0 + k];
+                BatchSys<T> &q = S[s];
+                ++G.iters[s];
+                A.s[k] = {q.V, q.V + (size_t)(q.j + 1) * G.n, Sout + (k0 + k) * G.n, res(s), parts(k), q.j + 1};
+            }
+            gs_step<T>(G.n, G.m, ns, G.reorth, A, G.st);
+            for (int k = 0; k < ns; ++k) to_host(act[k0 + k]);
         }
     }
-    // 2: w -= V h, then |w|^2
-    void gs_update() {
-        for (size_t k = 0; k < act.size(); ++k) {
-            const int s = act[k];
-            BatchSys<T> &q = S[s];
-            double2 *w = Sout + k * G.n;
-            for (int i = 0; i <= q.j; ++i) q.h1[i] = hr(s)[i];
-            k_sub_combo<T><<<ceil_div(G.n, 256), 256, 0, G.st>>>(G.n, q.V, G.n, q.j + 1, res(s), w);
-            LAUNCH_OK();
-            dots_to(w, 0, 1, w, res(s) + G.m + 2);
-            to_host(s);
-        }
-    }
-    // 3: a second pass where the first removed most of w (Daniel-Gragg-Kaufman-Stewart), as in fgmres
-    bool gs_second_dots() {
-        bool any = false;
-        for (size_t k = 0; k < act.size(); ++k) {
-            const int s = act[k];
-            BatchSys<T> &q = S[s];
-            const double w0 = sqrt(std::max(hr(s)[G.m + 1].x, 0.0)), hn = sqrt(std::max(hr(s)[G.m + 2].x, 0.0));
-            second[s] = G.reorth == 2 || (G.reorth == 1 && !(hn > 0.7071067811865476 * w0));
-            if (!second[s]) continue;
-            dots_to(q.V, G.n, q.j + 1, Sout + k * G.n, res(s));
-            to_host(s);
-            any = true;
-        }
-        return any;
-    }
-    void gs_second_update() {
-        for (size_t k = 0; k < act.size(); ++k) {
-            const int s = act[k];
-            if (!second[s]) continue;
-            BatchSys<T> &q = S[s];
-            double2 *w = Sout + k * G.n;
-            for (int i = 0; i <= q.j; ++i) q.h2[i] = hr(s)[i];
-            k_sub_combo<T><<<ceil_div(G.n, 256), 256, 0, G.st>>>(G.n, q.V, G.n, q.j + 1, res(s), w);
-            LAUNCH_OK();
-            dots_to(w, 0, 1, w, res(s) + G.m + 2);
-            to_host(s);
-        }
-    }
-    // 4: Hessenberg column, Givens rotations, the next basis vector; at the end of a cycle x += Z y
+    // Hessenberg column and Givens rotations; at the end of a cycle x += Z y
     void gs_finish() {
         const int m = G.m;
         for (size_t k = 0; k < act.size(); ++k) {
@@ -910,19 +994,17 @@ struct GroupSolver {
             BatchSys<T> &q = S[s];
             auto Hc = [&](int i, int jj) -> double2 & { return q.H[(size_t)i * m + jj]; };
             const int j = q.j;
-            double2 *w = Sout + k * G.n;
-            if (second[s])
-                for (int i = 0; i <= j; ++i) q.h1[i] = cadd(q.h1[i], q.h2[i]);
-            const double hn = sqrt(std::max(hr(s)[m + 2].x, 0.0));
-            for (int i = 0; i <= j; ++i) Hc(i, j) = q.h1[i];
-            if (!std::isfinite(hn) || !std::isfinite(hr(s)[m + 2].x)) {
+            const double2 *h = hr(s);
+            const bool second = h[2 * m + 5].x != 0.0;
+            const double hn = sqrt(std::max(h[2 * m + 4].x, 0.0));
+            for (int i = 0; i <= j; ++i) Hc(i, j) = second ? cadd(h[i], h[m + 1 + i]) : h[i];
+            if (!std::isfinite(hn) || !std::isfinite(h[2 * m + 4].x)) {
                 G.status[s] = FMMBEM_ENAN;
                 q.done = true;
                 q.in_cycle = false;
                 continue;
             }
             Hc(j + 1, j) = cmk(hn, 0);
-            if (hn > 0) Bl.scale_copy(1.0 / hn, w, q.V + (size_t)(j + 1) * G.n);
             for (int i = 0; i < j; ++i) {
                 double2 a = Hc(i, j), c = Hc(i + 1, j);
                 Hc(i, j) = cadd(cscale(a, q.cs[i].x), cmul(q.sn[i], c));
@@ -999,15 +1081,8 @@ void fgmres_groups(std::vector<FgmresGroup> &groups) {
     wait_all();
     all([](auto &g) { g.restart_decide(); });
     while (any_of([](auto &g) { return g.products(); })) {
-        all([](auto &g) { g.gs_dots(); });
+        all([](auto &g) { g.gs(); });
         wait_all();
-        all([](auto &g) { g.gs_update(); });
-        wait_all();
-        if (any_of([](auto &g) { return g.gs_second_dots(); })) {
-            wait_all();
-            all([](auto &g) { g.gs_second_update(); });
-            wait_all();
-        }
         all([](auto &g) { g.gs_finish(); });
         all([](auto &g) { g.restart_products(); });
         wait_all();
