@@ -841,6 +841,9 @@ constexpr int TM_LD = 130;  // LDS row stride of the staged B chunks
 // Half the matrix instructions of the (2n+1)^2 product; bound by the work rows' memory traffic and
 // staging all the same: levels 2-5 of the 1M L-room, ms per product against the full matrices,
 // FP64 forward 1.30 -> 1.15, back 1.60 -> 1.58; FP32, four vectors at 2 kHz, 1.32 -> 1.03 and 1.65 -> 1.39.
+// A third of the back rotation was its end: with one phase load for both signs, and the sums over the
+// jobs that begin a run only (not idle threads for the others), 1.58 -> 1.37 ms; FP32, levels 2-6,
+// 2.20 -> 1.99.
 // K chunks of 4 (FP64; 22 KB of LDS) or 8 rows (FP32, and 32-job tiles).  Held to four wavefronts per
 // SIMD the FP64 kernels spill 12-23 registers and lose 25-40 %, so three are allowed.
 template <class R, bool FWD, int RBG, int TMJ, int KC>
@@ -861,7 +864,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 4))
     __shared__ R lds[LDSN];
     __shared__ int64_t soff[TMJ];
     __shared__ int32_t sdir[TMJ];
-    __shared__ int segl[TMJ];
+    __shared__ int segl[TMJ], runs[FWD ? 1 : TMJ];  // jobs of the run that a job begins (0: none); such jobs
     auto Bs = [&](int buf, int p, int k, int c) -> R & { return lds[((2 * buf + p) * KC + k) * TM_LD + c]; };
     auto As = [&](int buf, int p, int k, int r) -> R & { return lds[LDSB + ((2 * buf + p) * KC + k) * LA + r]; };
     int tile, nq;
@@ -879,6 +882,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 4))
         segl[tid] = (!FWD && J < a.njob) ? a.jseg[J / a.nr] : 0;
     }
     __syncthreads();
+    int nrun = 0;
+    if (!FWD) {
+        const unsigned long long has = __ballot(lane < TMJ && segl[lane % TMJ] > 0);
+        nrun = __popcll(has);
+        if (wv == 0 && (has >> lane & 1)) runs[__popcll(has & ((1ull << lane) - 1))] = lane;
+    }
     const int tr = a.tile_rot[tile / a.nr];
     // M[k][r] = H[r][k] (FWD, from HT) or H[k][r], centred at (m, m') = (0, 0)
     const R *Mn = (FWD ? a.HT : a.H) + (int64_t)tr * rot_table_size(a.P) + rot_block_off(n) + n * w + n;
@@ -999,6 +1008,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 4))
             // one job)
             constexpr int NE = RG * TMJ / 256;
             const int nrow = min(RG, K - r0);
+            C phv[NE];  // e^{i m a} of this thread's (row, job) pairs
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const int e = tid + 256 * i, j = e / RG, rr = e % RG;
+                phv[i] = rr < nrow ? a.ph[sdir[j] + r0 + rr] : mkc<C>(0, 0);
+            }
 #pragma unroll
             for (int sign = 0; sign < 2; ++sign) {
                 if (sign && K == 1) break;
@@ -1013,31 +1028,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 4))
                             lds[(q * 16 + Op::row(kq, i)) * TM_LD + colw + 16 * cb] = sign ? u - v : u + v;
                         }
                 __syncthreads();
-                // phase every (row, job) in place first, four phase loads in flight at a time, so
-                // that the run sums below read LDS only
-                constexpr int NG = NE < 4 ? NE : 4;
+                // phase every (row, job) in place first, so that the run sums below read LDS only
 #pragma unroll
-                for (int i0 = 0; i0 < NE; i0 += NG) {
-                    C phv[NG];
-#pragma unroll
-                    for (int i = 0; i < NG; ++i) {
-                        const int e = tid + 256 * (i0 + i), j = e / RG, rr = e % RG;
-                        phv[i] = rr < nrow ? a.ph[sdir[j] + (sign ? -(r0 + rr) : r0 + rr)] : mkc<C>(0, 0);
-                    }
-#pragma unroll
-                    for (int i = 0; i < NG; ++i) {
-                        const int e = tid + 256 * (i0 + i), j = e / RG, rr = e % RG;
-                        R *x = &lds[rr * TM_LD + 2 * j];
-                        const C v = mulcc(mkc<C>(x[0], x[1]), phv[i]);  // e^{-i m a}
-                        x[0] = v.x;
-                        x[1] = v.y;
-                    }
+                for (int i = 0; i < NE; ++i) {
+                    const int e = tid + 256 * i, j = e / RG, rr = e % RG;
+                    R *x = &lds[rr * TM_LD + 2 * j];
+                    const C c = mkc<C>(x[0], x[1]), v = sign ? mulc(phv[i], c) : mulcc(c, phv[i]);  // e^{+-i m a}
+                    x[0] = v.x;
+                    x[1] = v.y;
                 }
                 __syncthreads();
-                for (int e = tid; e < RG * TMJ; e += 256) {
-                    const int j = e / RG, rr = e % RG, m = r0 + rr;
+                for (int e = tid; e < RG * nrun; e += 256) {
+                    const int j = runs[e / RG], rr = e % RG, m = r0 + rr;
                     const int len = segl[j];
-                    if (rr >= nrow || len == 0 || (sign && m == 0)) continue;
+                    if (rr >= nrow || (sign && m == 0)) continue;
                     C v = mkc<C>(0, 0);
                     for (int t = 0; t < len; ++t) {
                         const int jj = j + t * a.nr;
