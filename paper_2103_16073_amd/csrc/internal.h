@@ -339,6 +339,7 @@ struct fmmbem_ctx {
     int pmax = 0, delta_p = 0;
     size_t lds_max = 65536;
     int64_t near_nnz = 0;
+    bool near_ready = false;  // the near pair lists are this octree's
     int64_t p2p_pairs = 0;
     bool precond_ready_nb = false, precond_ready_diag = false;
     std::vector<double> history;  // Arnoldi residual estimate per outer iteration of the last solve
