@@ -363,6 +363,26 @@ static void layout_batch(fmmbem_ctx *c, const std::string &name, const std::vect
     b.tile_rot = upload(c->buf, name + "_trot", tr, st);
 }
 
+// jobs of a sorted list with every class (coaxial table, polar angle) padded to 64, 32 and 8
+struct ClassPadding {
+    int64_t p64 = 0, p32 = 0, p8 = 0;
+};
+static ClassPadding class_padding(const std::vector<JobH> &jobs) {
+    ClassPadding p;
+    for (size_t q = 0; q < jobs.size();) {
+        size_t e = q;
+        while (e < jobs.size() && jobs[e].tab == jobs[q].tab && jobs[e].rot == jobs[q].rot) ++e;
+        p.p64 += (int64_t)((e - q + 63) / 64) * 64;
+        p.p32 += (int64_t)((e - q + 31) / 32) * 32;
+        p.p8 += (int64_t)((e - q + 7) / 8) * 8;
+        q = e;
+    }
+    return p;
+}
+// the p = 16 fused tiles are taken while their padding to 8 jobs is at most this many times the jobs
+// (their work rows are padded to 64; beyond, the classes hold a job or two and nothing is shared)
+constexpr int64_t TQ_PAD = 4;
+
 // Sort jobs by (coaxial table, polar angle, target), pad every class to whole tiles, build the
 // rotation tables of the batch's distinct polar angles.
 static void make_batch(fmmbem_ctx *c, const std::string &name, std::vector<JobH> jobs, int psrc, int ptgt, int PT,
@@ -407,20 +427,16 @@ static void make_batch(fmmbem_ctx *c, const std::string &name, std::vector<JobH>
     // times faster than the LDS tiles there and no slower than the lane kernels: a level-3 M2L of
     // 5,326 jobs and four vectors at p = 18, 0.78 -> 0.35 ms; 56,616 jobs at p = 21 in FP32, 1.90
     // against 1.95 ms), at most half of it (32-job tiles where the 64-job padding would exceed a
-    // third); otherwise whole-vector tiles while at least 8 jobs fit the
-    // LDS budget, per-degree slices beyond.
-    int64_t pad64 = 0, pad32 = 0;
-    for (size_t q = 0; q < jobs.size();) {
-        size_t e = q;
-        while (e < jobs.size() && jobs[e].tab == jobs[q].tab && jobs[e].rot == jobs[q].rot) ++e;
-        pad64 += (int64_t)((e - q + 63) / 64) * 64;
-        pad32 += (int64_t)((e - q + 31) / 32) * 32;
-        q = e;
-    }
+    // third); the p = 16 fused tiles work on 8 jobs at a time and skip what is padding throughout, so
+    // small classes cost them their padding to 8 (the one M2L of 56 boxes: 77 us in whole-vector tiles,
+    // three launches, 16 us in one); otherwise whole-vector tiles while at least 8 jobs fit the LDS
+    // budget, per-degree slices beyond.
+    const auto [pad64, pad32, pad8] = class_padding(jobs);
     const int64_t nj = (int64_t)jobs.size();
     const bool mf = c->opt.mfma == 2 || (c->opt.mfma == 1 && b.P >= 17);
     b.lane = !jobs.empty() && (c->opt.lane_tiles == 2 ||
-                               (c->opt.lane_tiles == 1 && (pad64 * 4 <= nj * 5 || (mf && pad32 <= 2 * nj))));
+                               (c->opt.lane_tiles == 1 && (pad64 * 4 <= nj * 5 || (mf && pad32 <= 2 * nj) ||
+                                                           (c->opt.fused && rcr_ok(b) && pad8 <= TQ_PAD * nj))));
     if (b.lane) {
         b.whole = 0;
         b.JT = 64;
@@ -835,14 +851,7 @@ static void autotune_batches(fmmbem_ctx *c) {
             int lane, whole, jt, mfma;
         };
         std::vector<Shape> cand;
-        int64_t pad64 = 0, pad32 = 0;
-        for (size_t q = 0; q < jobs.size();) {
-            size_t e = q;
-            while (e < jobs.size() && jobs[e].tab == jobs[q].tab && jobs[e].rot == jobs[q].rot) ++e;
-            pad64 += (int64_t)((e - q + 63) / 64) * 64;
-            pad32 += (int64_t)((e - q + 31) / 32) * 32;
-            q = e;
-        }
+        const auto [pad64, pad32, pad8] = class_padding(jobs);
         if (pad64 <= 2 * (int64_t)jobs.size()) {
             cand.push_back({1, 0, 64, 0});
             if (c->opt.mfma != 0) cand.push_back({1, 0, 64, 1});
@@ -851,6 +860,8 @@ static void autotune_batches(fmmbem_ctx *c) {
                 cand.push_back({1, 0, 64, 3});
                 cand.push_back({1, 0, 64, 4});
             }
+        } else if (c->opt.fused && rcr_ok(b) && pad8 <= TQ_PAD * (int64_t)jobs.size()) {
+            cand.push_back({1, 0, 64, 4});
         }
         // matrix-core tiles of 32 jobs where classes are small (less padding, less reuse per tile)
         if (c->opt.mfma != 0 && pad32 < pad64 && pad32 <= 2 * (int64_t)jobs.size()) cand.push_back({1, 0, 32, 1});

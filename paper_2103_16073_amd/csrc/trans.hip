@@ -1844,6 +1844,11 @@ __global__ void __launch_bounds__(64 * NW) k_tq_lds(TransArgsT<R> a) {
     const int nr = a.nr, rt = tile / nr, rv = tile - rt * nr;
     const int64_t nj = a.njob / nr, J0 = (int64_t)rt * LANE_JT + part * NJ;
     if (J0 >= nj) return;  // the whole workgroup
+    // nothing but padding (the last workgroups of a class's last tile): no job here begins a run
+    {
+        const int l = threadIdx.x & 63;
+        if (!__any(l < NJ && J0 + l < nj && a.jseg[J0 + l] > 0)) return;
+    }
     // NW wavefronts share the 8 jobs' vectors: wavefront h takes the degrees (orders) n = h mod NW of
     // every step, and the jobs JW h .. JW h + JW - 1 of the first and last steps
     const int tid = threadIdx.x, lane = tid & 63, h = tid >> 6, g = lane >> 4, col = lane & 15, im = col & 1;

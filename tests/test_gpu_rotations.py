@@ -34,3 +34,23 @@ def test_products_over_truncation_numbers(F, f, opt):
             err = np.linalg.norm(y - ref[:nr], axis=1) / np.linalg.norm(ref[:nr], axis=1)
             assert err.max() < tol, (nr, prec, err, list(ctx.fmmbem_get_info().p)[:4])
     ctx.close()
+
+
+# classes of a few jobs (octrees of depth 2 and 3 at p = 16): the fused tiles with most of their padding
+# skipped against whole-vector tiles; same sums, other order of rounding (a product's own: 1e-14)
+@pytest.mark.parametrize("h,depth", [(0.5, 2), (0.2, 2), (0.2, 3)])
+def test_small_classes_vs_whole_tiles(F, h, depth):
+    room = synth.shoebox(3.0, 2.5, 2.0, h)
+    X = synth.complex_normal(room.n, 5, count=4)
+    out = []
+    for opt in ({}, dict(lane_tiles=0)):
+        ctx = F.Context(0, leaf_max=1, max_depth=depth, **opt)
+        ctx.fmmbem_set_mesh(room.vertices, room.triangles)
+        ctx.fmmbem_set_wavenumber(synth.wavenumber(150.0))
+        ctx.fmmbem_set_admittance(room.beta)
+        assert ctx.fmmbem_get_info().depth == depth
+        out.append([ctx.fmmbem_matvec(X[:nr], precision=prec) for nr in (1, 2, 4)
+                    for prec in (F.FMMBEM_FP64, F.FMMBEM_MIXED)])
+        ctx.close()
+    for i, (a, b) in enumerate(zip(*out)):
+        assert np.linalg.norm(a - b) < (1e-12 if i % 2 == 0 else 1e-5) * np.linalg.norm(b), i
