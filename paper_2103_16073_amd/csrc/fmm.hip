@@ -2157,10 +2157,12 @@ size_t p2m_fixed_bytes(int p) { return (size_t)3 * (p + 1) * (p + 2) / 2 * sizeo
 static bool p2m_slot_ok(int p) { return (p + 1) * (p + 2) / 2 <= P2M_SLOTS; }
 // the largest group of sources with four (one vector) or three workgroups per CU (the registers
 // allow no more: three instead of four costs one vector 625 -> 694 us, four instead of three costs
-// four vectors 990 -> 1,414 us)
-static int p2m_group(int nr, int p, size_t &sh) {
+// four vectors 990 -> 1,414 us); with two leaves per CU or fewer up to 64 KB (56 leaves: 27 -> 23 us, and
+// no less with every source of a leaf in one group)
+static int p2m_group(int nr, int p, int nleaf, size_t &sh) {
     int G = 64;
-    while (G > 4 && P2mLayout(p, G, nr).total * sizeof(double) > 163840 / (nr > 1 ? 3 : 4)) --G;
+    const size_t room = nleaf <= 512 ? 65536 : 163840 / (nr > 1 ? 3 : 4);
+    while (G > 4 && P2mLayout(p, G, nr).total * sizeof(double) > room) --G;
     sh = P2mLayout(p, G, nr).total * sizeof(double);
     return G;
 }
@@ -2173,7 +2175,7 @@ void build_p2m_table(double *tab, hipStream_t st) {
 bool p2m_fits(int nr, int p) {
     if (p2m_slot_ok(p)) {
         size_t sh;
-        p2m_group(nr, p, sh);
+        p2m_group(nr, p, 1, sh);
         return sh <= 65536;
     }
     return p2m_stage_bytes(nr, p) + p2m_fixed_bytes(p) <= 60000;
@@ -2186,7 +2188,7 @@ void launch_p2m(int nr, int nleaf, int p, const int32_t *leaf_start, const doubl
     if (nleaf <= 0) return;
     if (p2m_slot_ok(p)) {
         size_t sh;
-        const int G = p2m_group(nr, p, sh);
+        const int G = p2m_group(nr, p, nleaf, sh);
         const int nbw = (P2mLayout(p, G, nr).TBP / 8 + 3) / 4;  // 16-row blocks per wavefront
 #define P2M_CALL2(R, B)                                                                                               \
     if (M32) k_p2m<R, B, float2><<<nleaf, 256, sh, st>>>(p, G, leaf_start, center, ec, en, sigma, mu, k, 1.0 / k, leg, \
