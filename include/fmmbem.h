@@ -111,7 +111,7 @@ typedef struct {
                             share tables more but leave fewer workgroups per compute unit */
     int graphs;          /* nonzero: products on device vectors (solves, fmmbem_matvec_dev) replay a
                             captured HIP graph per (vector count, precision) through staging
-                            buffers; per-phase timings then report only the total.  default 1 */
+                            buffers (octrees of depth 3 or more); per-phase timings then report only the total.  default 1 */
     int autotune;        /* nonzero: at setup, time each translation batch under the candidate tile
                             shapes and keep the fastest (adds setup time); default 0 */
     int lane_tiles;      /* 1: translation batches whose table classes hold many jobs (padding to

@@ -1232,7 +1232,10 @@ static void matvec_graph(fmmbem_ctx *c, int nr, const double2 *x, double2 *y, bo
 static void matvec_dev(fmmbem_ctx *c, int nrhs, const double2 *x, double2 *y, bool exact_far, bool mixed = false,
                        bool allow_graph = true) {
     const int64_t n = c->nt;
-    const bool graph = allow_graph && c->opt.graphs && !c->prof_on && !exact_far;
+    // at depth 2 (one translation batch) a product is six launches, cheaper than the two staging copies
+    // and a graph's launch: 2,664 elements 172 -> 166 us, a solve in 27 steps 3 % less; at depth 5
+    // (38 launches) the graph is the better one, 1,043 against 1,053 us
+    const bool graph = allow_graph && c->opt.graphs && !c->prof_on && !exact_far && c->tree.depth > 2;
     int r = 0;
     while (r < nrhs) {
         const int left = nrhs - r, nr = left >= 4 ? 4 : left >= 2 ? 2 : 1;
