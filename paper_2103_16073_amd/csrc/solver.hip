@@ -101,7 +101,11 @@ __global__ void __launch_bounds__(256) k_dot_final(int nblk, const double2 *part
 // n, by reading V for large n.  Measured against a host decision after every norm (five copies and host
 // waits per step for one system, four for a lock-step group): a solve of 2,664 elements in 27 steps
 // 8.4 -> 6.1 ms, four of 90,972 elements in lock step with FP32 bases 60.6 -> 53.2 ms.
-constexpr int GS_MAX = 4;
+// Vectors of at most GS_FEW partial sums (FEW): the kernels that need a sum add it up themselves, in every
+// workgroup, so that a step is five launches instead of nine (2,664 elements, 27 steps: its kernels 1.12 ->
+// 0.71 ms, the solve 3 % less; the line: N = 8,192, where every workgroup reads 32 sums a vector); with
+// more, every workgroup would read the whole array of partial sums.
+constexpr int GS_MAX = 4, GS_FEW = 32, GS_FEW_NV = 256;
 template <class S>
 struct GsSys {
     const S *V;
@@ -114,12 +118,35 @@ struct GsArgs {
     GsSys<S> s[GS_MAX];
 };
 constexpr int gs_len(int m) { return 2 * m + 6; }
+// FEW: sum of nblk partial sums, by every thread
+__device__ inline double2 sum_few(int nblk, const double2 *partial) {
+    double2 s = cmk(0, 0);
+#pragma unroll 4
+    for (int i = 0; i < nblk; ++i) s = cadd(s, partial[i]);
+    return s;
+}
+// the choice of a second pass: reorth 1 where the first removed most of w (|w| fell below
+// |w_0| / sqrt(2)), 2 always, 0 never
+__device__ inline bool gs_second(int reorth, double w0sq, double hsq) {
+    return reorth == 2 || (reorth == 1 && !(sqrt(fmax(hsq, 0.0)) > 0.7071067811865476 * sqrt(fmax(w0sq, 0.0))));
+}
 
-// partial sums of conj(V_v) w, v < nv, and in the first pass of |w|^2 (v = nv): k_dot_partial's
-template <class S>
-__global__ void __launch_bounds__(256) k_gs_dots(int64_t n, int m, int pass, GsArgs<S> A) {
+// partial sums of conj(V_v) w, v < nv, and in the first pass of |w|^2 (v = nv): k_dot_partial's.  The
+// update's partial sums of |w|^2 are at part + (FEW ? nv + 1 : 0) gridDim.x.
+template <class S, bool FEW>
+__global__ void __launch_bounds__(256) k_gs_dots(int64_t n, int m, int pass, int reorth, GsArgs<S> A) {
     const GsSys<S> q = A.s[blockIdx.z];
-    if (pass && q.res[2 * m + 5].x == 0.0) return;
+    if (FEW && pass) {
+        const double2 h = sum_few(gridDim.x, q.part + (int64_t)(q.nv + 1) * gridDim.x);
+        const bool second = gs_second(reorth, q.res[2 * m + 2].x, h.x);
+        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+            q.res[2 * m + 3] = q.res[2 * m + 4] = h;
+            q.res[2 * m + 5] = cmk(second ? 1.0 : 0.0, 0.0);
+        }
+        if (!second) return;
+    } else if (pass && q.res[2 * m + 5].x == 0.0) {
+        return;
+    }
     const int v0 = blockIdx.y * DOT_G, all = q.nv + (pass == 0), ng = min(DOT_G, all - v0);
     if (ng <= 0) return;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, di = (int64_t)gridDim.x * blockDim.x;
@@ -170,11 +197,22 @@ __global__ void __launch_bounds__(256) k_gs_final(int nblk, int m, int pass, GsA
 // COMBO_U at a time, all loads of a group issued before the group's updates (one load per iteration
 // would leave one 1 KB request in flight per wavefront)
 constexpr int COMBO_U = 8;
-template <class S>
+template <class S, bool FEW>
 __global__ void __launch_bounds__(256) k_gs_update(int64_t n, int m, int pass, GsArgs<S> A) {
     const GsSys<S> q = A.s[blockIdx.y];
     if (pass && q.res[2 * m + 5].x == 0.0) return;
-    const double2 *h = q.res + pass * (m + 1);
+    __shared__ double2 hs[FEW ? GS_FEW_NV : 1];
+    if (FEW) {
+        const int all = q.nv + (pass == 0);
+        if ((int)threadIdx.x < all) {
+            const int v = threadIdx.x;
+            const double2 d = sum_few(gridDim.x, q.part + (int64_t)v * gridDim.x);
+            hs[v] = d;
+            if (blockIdx.x == 0) q.res[v == q.nv ? 2 * m + 2 : pass * (m + 1) + v] = d;
+        }
+        __syncthreads();
+    }
+    const double2 *h = FEW ? hs : q.res + pass * (m + 1);
     double2 d = cmk(0, 0);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         double2 s = q.w[i];
@@ -197,11 +235,10 @@ __global__ void __launch_bounds__(256) k_gs_update(int64_t n, int m, int pass, G
         if ((int)threadIdx.x < g) red[threadIdx.x] = cadd(red[threadIdx.x], red[threadIdx.x + g]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) q.part[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) q.part[(FEW ? (int64_t)(q.nv + 1) * gridDim.x : 0) + blockIdx.x] = red[0];
 }
 
-// |w|^2 after the pass and, after the first, the choice of a second one: reorth 1 where the first
-// removed most of w (|w| fell below |w_0| / sqrt(2)), 2 always, 0 never
+// |w|^2 after the pass and, after the first, the choice of a second one
 template <class S>
 __global__ void __launch_bounds__(256) k_gs_norm(int nblk, int m, int pass, int reorth, GsArgs<S> A) {
     const GsSys<S> q = A.s[blockIdx.x];
@@ -210,17 +247,30 @@ __global__ void __launch_bounds__(256) k_gs_norm(int nblk, int m, int pass, int 
     if (threadIdx.x != 0) return;
     q.res[2 * m + 3 + pass] = s;
     if (pass) return;
-    const double w0 = sqrt(fmax(q.res[2 * m + 2].x, 0.0)), hn = sqrt(fmax(s.x, 0.0));
     q.res[2 * m + 4] = s;
-    q.res[2 * m + 5] = cmk(reorth == 2 || (reorth == 1 && !(hn > 0.7071067811865476 * w0)) ? 1.0 : 0.0, 0.0);
+    q.res[2 * m + 5] = cmk(gs_second(reorth, q.res[2 * m + 2].x, s.x) ? 1.0 : 0.0, 0.0);
 }
 
 // the next basis vector w / |w| (left alone where |w| is 0 or not a number: the host ends the cycle)
-template <class S>
-__global__ void __launch_bounds__(256) k_gs_next(int64_t n, int m, GsArgs<S> A) {
+template <class S, bool FEW>
+__global__ void __launch_bounds__(256) k_gs_next(int64_t n, int m, int nblk, int reorth, GsArgs<S> A) {
     const GsSys<S> q = A.s[blockIdx.y];
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const double hn = sqrt(fmax(q.res[2 * m + 4].x, 0.0));
+    double h2;
+    if (FEW && (reorth == 0 || q.res[2 * m + 5].x != 0.0)) {  // the last update's norm is not summed yet
+        const double2 s = sum_few(nblk, q.part + (int64_t)(q.nv + 1) * nblk);
+        h2 = s.x;
+        if (i == 0) {
+            q.res[2 * m + 4] = s;
+            if (reorth == 0) {
+                q.res[2 * m + 3] = s;
+                q.res[2 * m + 5] = cmk(0.0, 0.0);
+            }
+        }
+    } else {
+        h2 = q.res[2 * m + 4].x;
+    }
+    const double hn = sqrt(fmax(h2, 0.0));
     if (i < n && hn > 0.0) stc(q.Vnext, i, cscale(q.w[i], 1.0 / hn));
 }
 
@@ -230,17 +280,28 @@ static void gs_step(int64_t n, int m, int nsys, int reorth, const GsArgs<S> &A, 
     int nv = 0;
     for (int k = 0; k < nsys; ++k) nv = std::max(nv, A.s[k].nv);
     const int nblk = (int)std::min<int64_t>(DOT_BLOCKS, std::max<int64_t>(1, (n + 255) / 256));
+    const bool few = nblk <= GS_FEW && nv < GS_FEW_NV;
     for (int pass = 0; pass < (reorth == 0 ? 1 : 2); ++pass) {
-        k_gs_dots<S><<<dim3(nblk, ceil_div(nv + (pass == 0), DOT_G), nsys), 256, 0, st>>>(n, m, pass, A);
+        const dim3 gd(nblk, ceil_div(nv + (pass == 0), DOT_G), nsys), gu(nblk, nsys);
+        if (few) {
+            k_gs_dots<S, true><<<gd, 256, 0, st>>>(n, m, pass, reorth, A);
+            LAUNCH_OK();
+            k_gs_update<S, true><<<gu, 256, 0, st>>>(n, m, pass, A);
+            LAUNCH_OK();
+            continue;
+        }
+        k_gs_dots<S, false><<<gd, 256, 0, st>>>(n, m, pass, reorth, A);
         LAUNCH_OK();
         k_gs_final<S><<<dim3(nv + (pass == 0), nsys), 256, 0, st>>>(nblk, m, pass, A);
         LAUNCH_OK();
-        k_gs_update<S><<<dim3(nblk, nsys), 256, 0, st>>>(n, m, pass, A);
+        k_gs_update<S, false><<<gu, 256, 0, st>>>(n, m, pass, A);
         LAUNCH_OK();
         k_gs_norm<S><<<nsys, 256, 0, st>>>(nblk, m, pass, reorth, A);
         LAUNCH_OK();
     }
-    k_gs_next<S><<<dim3(ceil_div(n, 256), nsys), 256, 0, st>>>(n, m, A);
+    const dim3 gn(ceil_div(n, 256), nsys);
+    if (few) k_gs_next<S, true><<<gn, 256, 0, st>>>(n, m, nblk, reorth, A);
+    else k_gs_next<S, false><<<gn, 256, 0, st>>>(n, m, nblk, reorth, A);
     LAUNCH_OK();
 }
 
