@@ -146,13 +146,14 @@ __device__ inline void tri_series(const double *x, const double *nx, const doubl
         s1[e] = s0[e] + le;
         d[e] = a[e][0] * nu[0] + a[e][1] * nu[1] + a[e][2] * nu[2];
         rho2[e] = fma(d[e], d[e], h2);
-        // log((r1 + s1) / (r0 + s0)) without cancellation on either side of the foot; its factors
-        // vanish when x lies on the edge's line
-        const bool on = rho2[e] <= 1e-26 * le2, right = s0[e] + s1[e] >= 0.0;
+        // log((r1 + s1) / (r0 + s0)) without cancellation on either side of the foot.  On the edge's line
+        // beyond its ends it is finite, and the leading term of L' (d and c_e vanish there, n_x.nu_e need
+        // not); with x on the edge itself the line integrals diverge, and the edge is left out of them
+        const bool line = rho2[e] <= 1e-26 * le2, right = s0[e] + s1[e] >= 0.0;
         const double sa = right ? s0[e] : -s1[e], sb = right ? s1[e] : -s0[e];  // |sa| <= sb
         const double ra = right ? r[e] : r[f], rb = right ? r[f] : r[e];
         const double num = sa >= 0.0 ? rb + sb : (rb + sb) * (ra - sa), den = sa >= 0.0 ? ra + sa : rho2[e];
-        K[e][1] = on ? 0.0 : log(num / den);
+        K[e][1] = line && sa <= 1e-13 * le ? 0.0 : log(num / den);
         K[e][0] = 0.0;
         I1 = fma(d[e], K[e][1], I1);
         if (NRM) {
@@ -161,7 +162,7 @@ __device__ inline void tri_series(const double *x, const double *nx, const doubl
             ce[e] = 0.0;
             for (int q = 0; q < 3; ++q) ce[e] += (a[e][q] - s0[e] * t[q]) * tn[q];
             l0r = fma(cn[e], K[e][1], l0r);
-            if (!on) m2r = fma(-ce[e], (s1[e] / r[f] - s0[e] / r[e]) / rho2[e], m2r);
+            if (!line) m2r = fma(-ce[e], (s1[e] / r[f] - s0[e] / r[e]) / rho2[e], m2r);
         }
     }
     double Lr = I1, Li = 0.0, Mr = 0.0, Mi = 0.0, t = 1.0, pm = 1.0, pw[3] = {1.0, 1.0, 1.0};
