@@ -90,10 +90,12 @@ __device__ inline void sincos_red(double x, double &s, double &c) {
 //   L' = -(n_x.n) M - sum_e (n_x.nu_e) int_e G dl,
 //   M' = k^2 (n_x.n) L + sum_e c_e int_e G (ikr - 1)/r^2 dl,
 // whose edge integrals are the same sums over K.  On the element itself (self: h = 0, M = L' = 0) M'
-// is the Hadamard finite part.  About 30 instructions per term and 20-33 terms; against 113-bit sums
-// the error is below 4e-15 of L for k r <= 4 on lattice neighbours, corner neighbours and points off
-// the surface (the 192-node quadrature below: the same on neighbours, 1e-4 of L for a point 1e-9 off
-// the plane through an edge), and grows by cancellation beyond, where the quadrature takes over.
+// is the Hadamard finite part.  About 30 instructions per term and 20-33 terms.  Against an extended-
+// precision sum, for k r <= 4, as multiples of |L|, of |L| / edge (M, L') and of |L| / edge^2 (M'): L, M
+// and L' within 1e-14 on neighbours in the plane and across it and on and next to the edges' lines beyond
+// the ends, M' within 1e-13 there (next to an edge itself, where M' grows like the inverse distance, 3e-10 at
+// 1e-3 edges); the quadrature below with eight panels an edge was 1e-4 of L off for a point 1e-9 off the
+// plane through an edge.  Beyond k r = 4 the terms cancel, and the quadrature takes over.
 // Bound by FP64 instructions.  Measured on the near table of the 228,412-element shoebox (4.8 million
 // entries): 7.85 ms by quadrature (192 nodes an entry), 0.27 ms by the series.
 constexpr double TRI_SERIES_KR = 4.0;
@@ -162,7 +164,10 @@ __device__ inline void tri_series(const double *x, const double *nx, const doubl
             ce[e] = 0.0;
             for (int q = 0; q < 3; ++q) ce[e] += (a[e][q] - s0[e] * t[q]) * tn[q];
             l0r = fma(cn[e], K[e][1], l0r);
-            if (!line) m2r = fma(-ce[e], (s1[e] / r[f] - s0[e] / r[e]) / rho2[e], m2r);
+            // (s1 / r1 - s0 / r0) / rho^2: beyond the edge's ends both quotients tend to the same +-1 towards
+            // its line, so there in the equal form without their difference
+            if (sa > 1e-13 * le) m2r = fma(-ce[e], le * (s0[e] + s1[e]) / (r[e] * r[f] * fma(s1[e], r[e], s0[e] * r[f])), m2r);
+            else if (!line) m2r = fma(-ce[e], (s1[e] / r[f] - s0[e] / r[e]) / rho2[e], m2r);
         }
     }
     double Lr = I1, Li = 0.0, Mr = 0.0, Mi = 0.0, t = 1.0, pm = 1.0, pw[3] = {1.0, 1.0, 1.0};

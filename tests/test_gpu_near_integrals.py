@@ -21,12 +21,13 @@ EDGES = [((0, 0, 0), (1, 0, 0)), ((1, 0, 0), (0, 1, 0)), ((0, 1, 0), (0, 0, 0))]
 
 def probes(points, normals):
     """The right triangle of unit legs (element 0), a small triangle centred at every point with the given
-    normal, and two far ones that make the octree's leaves larger than r_c."""
+    normal, and two far ones that make the octree's leaves larger than r_c and the volume positive."""
     V, T = [np.array(p, float) for p in ((0, 0, 0), (1, 0, 0), (0, 1, 0))], [(0, 1, 2)]
-    far = [np.array([-6.0, -6.0, -6.0]), np.array([6.0, 6.0, 6.0])]
-    for x, n in list(zip(points, normals)) + [(f, np.array([0.0, 0.0, 1.0])) for f in far]:
+    out = np.full(3, 3 ** -0.5)
+    faces = [(x, n, 0.2) for x, n in zip(points, normals)] + [(-9.0 * out, -out, 1.5), (9.0 * out, out, 1.5)]
+    for x, n, size in faces:
         a = np.cross(n, [0.3, -0.2, 0.9] if abs(n[2]) < 0.9 else [1.0, 0.0, 0.0])
-        a *= 0.2 / np.linalg.norm(a)
+        a *= size / np.linalg.norm(a)
         b = np.cross(n, a)
         i = len(V)
         V += [x + a, x - 0.5 * a + np.sqrt(0.75) * b, x - 0.5 * a - np.sqrt(0.75) * b]
@@ -81,6 +82,13 @@ def worst(F, V, T, k):
 @pytest.mark.parametrize("k", [0.3, 1.0, 1.6])
 def test_on_the_lines_of_edges(F, k):
     V, T = probes(*near_lines(np.random.default_rng(1), [0.0] * 3))
+    w = worst(F, V, T, k)
+    assert w.max() < 1.0, w
+
+
+@pytest.mark.parametrize("k", [0.3, 1.0, 1.6])
+def test_close_to_the_lines_of_edges(F, k):
+    V, T = probes(*near_lines(np.random.default_rng(1), [1e-2, 1e-4, 1e-6, 1e-8, 1e-9, 1e-10, 1e-11, 1e-12, 3e-13, 1e-13]))
     w = worst(F, V, T, k)
     assert w.max() < 1.0, w
 
