@@ -93,6 +93,27 @@ def test_close_to_the_lines_of_edges(F, k):
     assert w.max() < 1.0, w
 
 
+def around(rng):
+    """Points beside, above and next to the triangle (0.02 to 1 edges off), in its plane, close to its
+    edges' lines and on them."""
+    P, N = near_lines(rng, [0.0, 1e-10, 1e-6, 1e-3])
+    for z in (0.02, 0.1, 0.4, 1.0):
+        for x, y in rng.uniform(-0.3, 1.2, (8, 2)):
+            P.append(np.array([x, y, z]))
+    for phi in rng.uniform(0, 2 * np.pi, 12):
+        P.append(np.array([1 / 3, 1 / 3, 0.0]) + rng.uniform(0.95, 1.6) * np.array([np.cos(phi), np.sin(phi), 0.0]))
+    N += [np.array([0.0, 0.0, 1.0]) if i % 3 == 0 else unit(rng, 1)[0] for i in range(len(P) - len(N))]
+    return P, N
+
+
+# either side of the largest k r of the series (4; the farthest vertices at 2.5 k) and far beyond
+@pytest.mark.parametrize("k", [0.5, 1.5, 1.9, 2.3, 4.0, 6.0, 10.0, 18.0, 28.0])
+def test_wavenumbers(F, k):
+    V, T = probes(*around(np.random.default_rng(4)))
+    w = worst(F, V, T, k)
+    assert w.max() < 1.0, w
+
+
 @pytest.mark.parametrize("form", ["bm", "indirect"])
 def test_products_with_a_point_on_an_edges_line(F, form):
     """An element on another surface that lies on the line of an edge: the rows of the product."""
