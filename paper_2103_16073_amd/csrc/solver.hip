@@ -27,54 +27,8 @@ __device__ inline double2 ldc(const float2 *p, int64_t i) {
 __device__ inline void stc(double2 *p, int64_t i, double2 v) { p[i] = v; }
 __device__ inline void stc(float2 *p, int64_t i, double2 v) { p[i] = make_float2((float)v.x, (float)v.y); }
 
-// partial[v * gridDim.x + blk] = sum_{i in blk's stride} conj(V_v[i]) w[i].  A workgroup takes
-// DOT_G vectors (blockIdx.y group): each element of w it loads serves all of them, so w is read
-// nv / DOT_G times rather than nv times (with FP32 Krylov vectors, w's 16 bytes per element would
-// otherwise be twice the vector's own 8).
-constexpr int DOT_G = 8;
-template <class S>
-__global__ void __launch_bounds__(256) k_dot_partial(int64_t n, const S *V, int64_t ldv, int nv, const double2 *w,
-                                                     double2 *partial) {
-    const int v0 = blockIdx.y * DOT_G, ng = min(DOT_G, nv - v0);
-    double2 s[DOT_G];
-#pragma unroll
-    for (int g = 0; g < DOT_G; ++g) s[g] = cmk(0, 0);
-    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, di = (int64_t)gridDim.x * blockDim.x;
-    if (ng == DOT_G) {
-        // whole group: the DOT_G loads of a row are issued before any of them is used
-        for (int64_t i = i0; i < n; i += di) {
-            const double2 wi = w[i];
-            double2 x[DOT_G];
-#pragma unroll
-            for (int g = 0; g < DOT_G; ++g) x[g] = ldc(V + (int64_t)(v0 + g) * ldv, i);
-#pragma unroll
-            for (int g = 0; g < DOT_G; ++g) s[g] = cadd(s[g], cmulc(wi, x[g]));  // conj(V_v) w
-        }
-    } else {
-        for (int64_t i = i0; i < n; i += di) {
-            const double2 wi = w[i];
-#pragma unroll
-            for (int g = 0; g < DOT_G; ++g)
-                if (g < ng) s[g] = cadd(s[g], cmulc(wi, ldc(V + (int64_t)(v0 + g) * ldv, i)));
-        }
-    }
-    __shared__ double2 red[DOT_G][256];
-#pragma unroll
-    for (int g = 0; g < DOT_G; ++g) red[g][threadIdx.x] = s[g];
-    __syncthreads();
-    for (int q = blockDim.x / 2; q > 0; q >>= 1) {
-        if ((int)threadIdx.x < q)
-#pragma unroll
-            for (int g = 0; g < DOT_G; ++g) red[g][threadIdx.x] = cadd(red[g][threadIdx.x], red[g][threadIdx.x + q]);
-        __syncthreads();
-    }
-    if ((int)threadIdx.x < ng) partial[(int64_t)(v0 + threadIdx.x) * gridDim.x + blockIdx.x] = red[threadIdx.x][0];
-}
-
-// sum of nblk partial sums over the workgroup, in a fixed order (valid in thread 0)
-__device__ inline double2 sum_partials(int nblk, const double2 *partial) {
-    double2 s = cmk(0, 0);
-    for (int i = threadIdx.x; i < nblk; i += blockDim.x) s = cadd(s, partial[i]);
+// sum of the workgroup's 256 values, halving the range each step (valid in thread 0)
+__device__ inline double2 sum_workgroup(double2 s) {
     __shared__ double2 red[256];
     red[threadIdx.x] = s;
     __syncthreads();
@@ -85,9 +39,25 @@ __device__ inline double2 sum_partials(int nblk, const double2 *partial) {
     return red[0];
 }
 
-__global__ void __launch_bounds__(256) k_dot_final(int nblk, const double2 *partial, double2 *out) {
-    const double2 s = sum_partials(nblk, partial + (int64_t)blockIdx.x * nblk);
-    if (threadIdx.x == 0) out[blockIdx.x] = s;
+// partial[blk] = sum_{i in blk's stride} |w[i]|^2
+__global__ void __launch_bounds__(256) k_norm_partial(int64_t n, const double2 *w, double2 *partial) {
+    double2 s = cmk(0, 0);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        s = cadd(s, cmulc(w[i], w[i]));
+    s = sum_workgroup(s);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+}
+
+// sum of nblk partial sums over the workgroup, in a fixed order (valid in thread 0)
+__device__ inline double2 sum_partials(int nblk, const double2 *partial) {
+    double2 s = cmk(0, 0);
+    for (int i = threadIdx.x; i < nblk; i += blockDim.x) s = cadd(s, partial[i]);
+    return sum_workgroup(s);
+}
+
+__global__ void __launch_bounds__(256) k_norm_final(int nblk, const double2 *partial, double2 *out) {
+    const double2 s = sum_partials(nblk, partial);
+    if (threadIdx.x == 0) *out = s;
 }
 
 // One Gram-Schmidt step of up to GS_MAX systems, w against their V_0 .. V_{nv-1}: eight launches
@@ -106,6 +76,7 @@ __global__ void __launch_bounds__(256) k_dot_final(int nblk, const double2 *part
 // 0.71 ms, the solve 3 % less; the line: N = 8,192, where every workgroup reads 32 sums a vector); with
 // more, every workgroup would read the whole array of partial sums.
 constexpr int GS_MAX = 4, GS_FEW = 32, GS_FEW_NV = 256;
+constexpr int DOT_G = 8;
 template <class S>
 struct GsSys {
     const S *V;
@@ -131,7 +102,10 @@ __device__ inline bool gs_second(int reorth, double w0sq, double hsq) {
     return reorth == 2 || (reorth == 1 && !(sqrt(fmax(hsq, 0.0)) > 0.7071067811865476 * sqrt(fmax(w0sq, 0.0))));
 }
 
-// partial sums of conj(V_v) w, v < nv, and in the first pass of |w|^2 (v = nv): k_dot_partial's.  The
+// partial[v * gridDim.x + blk] = sum_{i in blk's stride} conj(V_v[i]) w[i], v < nv, and in the first pass of
+// |w|^2 (v = nv).  A workgroup takes DOT_G vectors (blockIdx.y group): each element of w it loads serves
+// all of them, so w is read nv / DOT_G times rather than nv times (with FP32 Krylov vectors, w's 16 bytes
+// per element would otherwise be twice the vector's own 8).  The
 // update's partial sums of |w|^2 are at part + (FEW ? nv + 1 : 0) gridDim.x.
 template <class S, bool FEW>
 __global__ void __launch_bounds__(256) k_gs_dots(int64_t n, int m, int pass, int reorth, GsArgs<S> A) {
@@ -228,14 +202,8 @@ __global__ void __launch_bounds__(256) k_gs_update(int64_t n, int m, int pass, G
         q.w[i] = s;
         d = cadd(d, cmulc(s, s));
     }
-    __shared__ double2 red[256];
-    red[threadIdx.x] = d;
-    __syncthreads();
-    for (int g = blockDim.x / 2; g > 0; g >>= 1) {
-        if ((int)threadIdx.x < g) red[threadIdx.x] = cadd(red[threadIdx.x], red[threadIdx.x + g]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) q.part[(FEW ? (int64_t)(q.nv + 1) * gridDim.x : 0) + blockIdx.x] = red[0];
+    d = sum_workgroup(d);
+    if (threadIdx.x == 0) q.part[(FEW ? (int64_t)(q.nv + 1) * gridDim.x : 0) + blockIdx.x] = d;
 }
 
 // |w|^2 after the pass and, after the first, the choice of a second one
@@ -658,21 +626,16 @@ struct Blas {
     DeviceBuffers &scr;
     int64_t n;
     std::string tag;  // scratch-name prefix, so nested solves keep separate buffers
-    template <class S>
-    void dots(const S *V, int64_t ldv, int nv, const double2 *w, double2 *host_out) {
-        double2 *part = dget<double2>(scr, tag + "dot_part", (size_t)DOT_BLOCKS * std::max(nv, 1));
-        double2 *res = dget<double2>(scr, tag + "dot_res", std::max(nv, 1));
-        int nblk = (int)std::min<int64_t>(DOT_BLOCKS, std::max<int64_t>(1, (n + 255) / 256));
-        k_dot_partial<S><<<dim3(nblk, (nv + DOT_G - 1) / DOT_G), 256, 0, st>>>(n, V, ldv, nv, w, part);
-        LAUNCH_OK();
-        k_dot_final<<<nv, 256, 0, st>>>(nblk, part, res);
-        LAUNCH_OK();
-        HIP_OK(hipMemcpyAsync(host_out, res, sizeof(double2) * nv, hipMemcpyDeviceToHost, st));
-        HIP_OK(hipStreamSynchronize(st));
-    }
     double nrm(const double2 *w) {
+        double2 *part = dget<double2>(scr, tag + "dot_part", DOT_BLOCKS), *res = dget<double2>(scr, tag + "dot_res", 1);
+        const int nblk = (int)std::min<int64_t>(DOT_BLOCKS, std::max<int64_t>(1, (n + 255) / 256));
+        k_norm_partial<<<nblk, 256, 0, st>>>(n, w, part);
+        LAUNCH_OK();
+        k_norm_final<<<1, 256, 0, st>>>(nblk, part, res);
+        LAUNCH_OK();
         double2 d;
-        dots(w, 0, 1, w, &d);
+        HIP_OK(hipMemcpyAsync(&d, res, sizeof(double2), hipMemcpyDeviceToHost, st));
+        HIP_OK(hipStreamSynchronize(st));
         return sqrt(std::max(d.x, 0.0));
     }
     template <class S>
@@ -899,9 +862,9 @@ struct GroupSolver {
     // |w|^2 of a system, enqueued only
     void norm_to(int s, const double2 *w) {
         const int nblk = (int)std::min<int64_t>(DOT_BLOCKS, std::max<int64_t>(1, (G.n + 255) / 256));
-        k_dot_partial<double2><<<dim3(nblk, 1), 256, 0, G.st>>>(G.n, w, 0, 1, w, part);
+        k_norm_partial<<<nblk, 256, 0, G.st>>>(G.n, w, part);
         LAUNCH_OK();
-        k_dot_final<<<1, 256, 0, G.st>>>(nblk, part, res(s) + RN());
+        k_norm_final<<<1, 256, 0, G.st>>>(nblk, part, res(s) + RN());
         LAUNCH_OK();
         to_host(s);
     }
