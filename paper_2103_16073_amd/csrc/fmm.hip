@@ -1154,7 +1154,7 @@ __global__ void __launch_bounds__(256) k_p2m_wide(int nleaf, int p, int CH, cons
 // start against a reference sequence for N <= 60, 4 <= x <= 1.2 N + 5 finds the same ~1e-12
 // worst relative error, near zeros of j_n, as starting 40 + 4 sqrt(max(N, x) + 1) above).
 __device__ inline void bessel_j_seq_fast(double x, int N, double *j) {
-    if (x < 1e-2 || (x < 4.0 && N <= 40)) {  // small x at any N: 1/x is no number at x = 0
+    if (x < (N <= 40 ? 4.0 : 1e-2)) {  // small x at any N: 1/x is no number at x = 0
         bessel_j_small(x, N, j);
         return;
     }
