@@ -221,15 +221,17 @@ __device__ inline void tri_series(const double *x, const double *nx, const doubl
     }
 }
 
-// Panels of 8 points for an edge of extent w in the variable of s = d sinh(w), at most s away from the
-// foot: short beside the distance of the integrand's poles (pi/2 off the axis; 0.75), and TRI_PHASE of the
-// phase k r each at most (dr/dw <= |s|).  Errors against an adaptive quadrature, points around a triangle,
-// as multiples of (|L| without its oscillation) (k + 1 / edge)^(0, 1, 1, 2) for L, M, L', M': below 2e-13
-// for k r to 69 (8 panels an edge: 2e-12 at k r = 15, 1e-9 at 25, 5e-7 at 44; panels 0.75 long whatever
-// k: 3e-10, 5e-8, 3e-5).  An edge at k r = 8 takes 5 to 10 panels.  The count is bounded (k s w of 768).
-constexpr double TRI_PHASE = 1.5;
-__device__ inline int tri_panels(double w, double k, double s) {
-    return max(1, (int)fmin(512.0, ceil(w * fmax(1.0 / 0.75, k * s * (1.0 / TRI_PHASE)))));
+// Panels of 8 points for an edge of extent w in the variable of s = d sinh(w), kr = k times the farthest
+// vertex's distance: short beside the distance of the integrand's poles (pi/2 off the axis; 0.75), and
+// TRI_PHASE of the phase k r each at most (dr/dw <= r).  Errors against an adaptive quadrature, points
+// around a triangle, as multiples of (|L| without its oscillation) (k + 1 / edge)^(0, 1, 1, 2) for L, M, L',
+// M': below 2e-13 for k r to 69 (8 panels an edge: 2e-12 at k r = 15, 1e-9 at 25, 5e-7 at 44; panels 0.75
+// long whatever k: 3e-10, 5e-8, 3e-5).  At most 2.5 of phase is at rounding with room (3: the same, 4e-13 next
+// to k r = 4); an edge at k r = 8 takes 4 to 10 panels.  The count is bounded (kr w of 1,280).  In FP32, and
+// with the one kr for every edge: the field kernel's near part has no registers to spare.
+constexpr float TRI_PHASE = 2.5f;
+__device__ inline int tri_panels(double w, float kr) {
+    return max(1, (int)fminf(512.0f, ceilf((float)w * fmaxf(1.0f / 0.75f, kr * (1.0f / TRI_PHASE)))));
 }
 
 // The same L and M by quadrature, for k r beyond the series: polar coordinates
@@ -240,7 +242,7 @@ __device__ inline int tri_panels(double w, double k, double s) {
 // leaving an angular integral per edge (signed by the edge orientation seen from x_p), done by
 // 8-point Gauss-Legendre panels (tri_panels) after the substitution tan(psi) = sinh(w).
 // self != 0: x is the triangle's centroid (h = 0, M = 0 by the principal value).
-__device__ void tri_gauss(const double *x, const double *v, double k, int self, double2 &Lout, double2 &Mout) {
+__device__ void tri_gauss(const double *x, const double *v, double k, float kr, int self, double2 &Lout, double2 &Mout) {
     double e1[3] = {v[3] - v[0], v[4] - v[1], v[5] - v[2]};
     double e2[3] = {v[6] - v[0], v[7] - v[1], v[8] - v[2]};
     double nn[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2], e1[0] * e2[1] - e1[1] * e2[0]};
@@ -272,7 +274,7 @@ __device__ void tri_gauss(const double *x, const double *v, double k, int self, 
         // dpsi = dw / cosh(w); this grades the panels logarithmically along edges that are long
         // compared with their distance d from x_p, where the integrand varies fastest
         const double w0 = asinh(s0 / d), w1 = asinh(s1 / d);
-        const int NPAN = tri_panels(w1 - w0, k, fmax(fabs(s0), fabs(s1)));
+        const int NPAN = tri_panels(w1 - w0, kr);
         double hw = 0.5 * (w1 - w0) / NPAN;
         for (int pan = 0; pan < NPAN; ++pan) {
             double mid = w0 + (2 * pan + 1) * hw;
@@ -308,9 +310,9 @@ __device__ void tri_gauss(const double *x, const double *v, double k, int self, 
 
 // L' and M' in the same way: the edge integrals by Gauss panels with s = d sinh(w) (d = distance from x
 // to the edge's line, ds = r dw).
-__device__ void tri_gauss_n(const double *x, const double *nx, const double *v, double k, int self, double2 &L,
-                            double2 &M, double2 &Lp, double2 &Mp) {
-    tri_gauss(x, v, k, self, L, M);
+__device__ void tri_gauss_n(const double *x, const double *nx, const double *v, double k, float kr, int self,
+                            double2 &L, double2 &M, double2 &Lp, double2 &Mp) {
+    tri_gauss(x, v, k, kr, self, L, M);
     double e1[3] = {v[3] - v[0], v[4] - v[1], v[5] - v[2]};
     double e2[3] = {v[6] - v[0], v[7] - v[1], v[8] - v[2]};
     double nn[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2], e1[0] * e2[1] - e1[1] * e2[0]};
@@ -333,10 +335,9 @@ __device__ void tri_gauss_n(const double *x, const double *nx, const double *v, 
         const double ce = fx[0] * tn[0] + fx[1] * tn[1] + fx[2] * tn[2];
         const double cnu = nx[0] * nu[0] + nx[1] * nu[1] + nx[2] * nu[2];
         double2 I0 = cmk(0, 0), I2 = cmk(0, 0);
-        const double sm = fmax(fabs(s0), fabs(s1));
         if (d > 1e-13 * le) {
             const double w0 = asinh(s0 / d), w1 = asinh(s1 / d);
-            const int NPAN = tri_panels(w1 - w0, k, sm);
+            const int NPAN = tri_panels(w1 - w0, kr);
             const double hw = 0.5 * (w1 - w0) / NPAN;
             for (int pan = 0; pan < NPAN; ++pan) {
                 const double mid = w0 + (2 * pan + 1) * hw;
@@ -352,8 +353,8 @@ __device__ void tri_gauss_n(const double *x, const double *nx, const double *v, 
             }
         } else if (s0 * s1 > 0.0) {
             // x on the edge's line beyond its ends: c_e = 0, and panels in w = log|s| for I0
-            const double w0 = log(fmin(fabs(s0), fabs(s1))), w1 = log(sm);
-            const int NPAN = tri_panels(w1 - w0, k, sm);
+            const double w0 = log(fmin(fabs(s0), fabs(s1))), w1 = log(fmax(fabs(s0), fabs(s1)));
+            const int NPAN = tri_panels(w1 - w0, kr);
             const double hw = 0.5 * (w1 - w0) / NPAN;
             for (int pan = 0; pan < NPAN; ++pan) {
                 const double mid = w0 + (2 * pan + 1) * hw;
@@ -397,14 +398,14 @@ __device__ inline void tri_integrals(const double *x, const double *v, double k,
     const double rmax = tri_radii(x, v, r);
     double2 Lp, Mp;
     if (k * rmax <= TRI_SERIES_KR) tri_series<false>(x, nullptr, v, k, self, rmax, r, L, M, Lp, Mp);
-    else tri_gauss(x, v, k, self, L, M);
+    else tri_gauss(x, v, k, (float)(k * rmax), self, L, M);
 }
 __device__ inline void tri_integrals_n(const double *x, const double *nx, const double *v, double k, int self,
                                        double2 &L, double2 &M, double2 &Lp, double2 &Mp) {
     double r[3];
     const double rmax = tri_radii(x, v, r);
     if (k * rmax <= TRI_SERIES_KR) tri_series<true>(x, nx, v, k, self, rmax, r, L, M, Lp, Mp);
-    else tri_gauss_n(x, nx, v, k, self, L, M, Lp, Mp);
+    else tri_gauss_n(x, nx, v, k, (float)(k * rmax), self, L, M, Lp, Mp);
 }
 
 __global__ void __launch_bounds__(128) k_near_quad_n(int64_t nnz, const int32_t *rowv, const int32_t *col, const double4 *ec,
