@@ -1232,9 +1232,11 @@ static void matvec_graph(fmmbem_ctx *c, int nr, const double2 *x, double2 *y, bo
 static void matvec_dev(fmmbem_ctx *c, int nrhs, const double2 *x, double2 *y, bool exact_far, bool mixed = false,
                        bool allow_graph = true) {
     const int64_t n = c->nt;
-    // at depth 2 (one translation batch) a product is six launches, cheaper than the two staging copies
-    // and a graph's launch: 2,664 elements 172 -> 166 us, a solve in 27 steps 3 % less; at depth 5
-    // (38 launches) the graph is the better one, 1,043 against 1,053 us
+    // at depth 2 (one translation batch) a product is six launches, no dearer than a graph's launch and its
+    // two staging copies for one, two or four vectors (us, eager and graph: 696 elements 137-138, 148-152,
+    // 176-185; 2,664 elements 157-165, 173-181, 213-221; 38,916 elements 1,203-1,209, 1,333-1,341, 1,836-1,835).
+    // Deeper trees replay: one vector at depths 3 to 5 (7,400, 29,600, 118,400 elements) 222, 468 and 1,223 us
+    // against 215, 463 and 1,214 eager, one host call for 10 to 38 launches
     const bool graph = allow_graph && c->opt.graphs && !c->prof_on && !exact_far && c->tree.depth > 2;
     int r = 0;
     while (r < nrhs) {
@@ -1277,7 +1279,7 @@ static void launch_gamma(fmmbem_ctx *c, int nr, const int32_t *isrc, double2 *si
 
 // Right-hand sides of cnt sources (b: cnt x N), in passes of 4, 2 and 1 vectors where the work rows
 // of one vector stay below 1 GiB (N up to about 280,000): there the passes share kernel evaluations,
-// tables and launches (N = 37,272, four sources: 3.70 -> 2.38 ms).  Larger rooms keep one vector per pass:
+// tables and launches (N = 39,216, four sources: 3.70 -> 2.38 ms).  Larger rooms keep one vector per pass:
 // their passes fill the device alone (a 4-vector product of the 1M L-room costs 3.6 single ones),
 // and four vectors' work rows would be tens of GB.
 static void rhs_dev(fmmbem_ctx *c, int cnt, const int32_t *isrc, double2 *b) {

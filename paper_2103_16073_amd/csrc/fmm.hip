@@ -93,9 +93,10 @@ __device__ inline void sincos_red(double x, double &s, double &c) {
 // is the Hadamard finite part.  About 30 instructions per term and 20-33 terms.  Against an extended-
 // precision sum, for k r <= 4, as multiples of |L|, of |L| / edge (M, L') and of |L| / edge^2 (M'): L, M
 // and L' within 1e-14 on neighbours in the plane and across it and on and next to the edges' lines beyond
-// the ends, M' within 1e-13 there (next to an edge itself, where M' grows like the inverse distance, 3e-10 at
-// 1e-3 edges); the quadrature below with eight panels an edge was 1e-4 of L off for a point 1e-9 off the
-// plane through an edge.  Beyond k r = 4 the terms cancel, and the quadrature takes over.
+// the ends, M' within 1e-13 there (next to an edge itself, where M and L' grow like the logarithm of the
+// distance and M' like its inverse, 5e-13 and 3e-10 at 1e-3 edges); eight Gauss panels an edge, whatever the
+// distance, were 1e-4 of L off for a point 1e-9 off the plane through an edge.  Beyond k r = 4 the terms
+// cancel, and the quadrature below takes over.
 // Bound by FP64 instructions.  Measured on the near table of the 228,412-element shoebox (4.8 million
 // entries): 7.85 ms by quadrature (192 nodes an entry), 0.27 ms by the series.
 constexpr double TRI_SERIES_KR = 4.0;
